@@ -31,7 +31,7 @@ FLAGS = [
     "-I", os.path.join(ROOT, "include"),
 ]
 
-SOURCES = ["prims.hip", "setup.hip", "expand.hip", "rowsplit.hip", "multisplit.hip", "accumulate.hip",
+SOURCES = ["prims.hip", "setup.hip", "expand.hip", "rowsplit.hip", "multisplit.hip", "tiles.hip", "accumulate.hip",
            "plan.hip", "probe.hip", "static_plan.hip"]
 
 

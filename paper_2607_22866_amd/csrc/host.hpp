@@ -341,6 +341,53 @@ void light_symbolic(const Csr &A, const Csr &B, int64_t r0, int bin, const int64
 void light_numeric(const Csr &A, const Csr &B, int64_t r0, int bin, const int64_t *items, int64_t n,
                    const void *minc, const void *maxc, const int64_t *c_row_ptr, void *c_col, void *c_val,
                    int32_t *err, hipStream_t s);
+// ----------------------------------------------------------------- tiles.hip
+// Heavy rows accumulated straight from a chunk-major copy of the B rows they
+// use (no expansion in memory).
+constexpr int TILE_LOG2 = 14, TILE_COLS = 1 << TILE_LOG2;
+constexpr int TILE_MAX_CHUNKS = 1024;
+// region bins by product count (the big dense ones launch first)
+enum TileBin : uint8_t { TILE_EMPTY = 0, TILE_D_BIG, TILE_D, TILE_M, TILE_L, TILE_S, TILE_T, TILE_NBINS };
+constexpr int TILE_T_MAX = 256, TILE_S_MAX = 1024, TILE_M_MAX = 4096, TILE_D_MAX = 65536;
+constexpr int TILE_MERGE = 2048;  // most products of a region of several chunks
+constexpr int TILE_RANK_MAX = 7168;  // distinct columns of a large region summed by rank (two work groups per CU)
+struct TileHeavy {
+    int nc = 0;                      // column chunks
+    int slog = 0;                    // log2 of the chunks of a row whose lists are adjacent
+    int64_t ncp = 0;                 // nc rounded up to a multiple of that
+    int64_t ns = 0, nh = 0;          // slices, heavy rows
+    int64_t n_ent = 0, n_elems = 0;  // heavy entries of A, elements of the slices' B rows
+    uint16_t *cnt = nullptr;         // ns * nc: elements of a slice per chunk
+    uint32_t *part = nullptr;        // ns * nc: start of a slice's part of a chunk in col / val
+    uint32_t *scan = nullptr;        // tile_scan_words
+    uint16_t *col = nullptr;         // chunk-local columns
+    void *val = nullptr;
+    int32_t *es = nullptr, *eh = nullptr;  // entries: slice (-1: empty B row), heavy row
+    void *ea = nullptr;                    // A's values
+    const int64_t *a_ptr = nullptr;        // nh + 1: first entry of a heavy row
+    int64_t *items = nullptr;              // region ids c * nh + h by bin
+    uint32_t *nnz = nullptr;               // distinct columns of a region
+    uint8_t *grp = nullptr;                // chunks of a region
+    uint32_t *seg_end = nullptr;           // one past a list's last part
+    uint2 *seg = nullptr;                  // non-empty parts by list: start in col / val, length | chunk << 16
+    uint32_t *seg_e = nullptr;             // ... and the A entry
+    uint32_t *bitmap = nullptr;            // present columns of the regions of more than TILE_MERGE products
+    int64_t bins[TILE_NBINS + 1] = {0};
+};
+int tile_chunks(int64_t c_m);
+int64_t tile_scan_words(int64_t n);
+// t.cnt and t.part of the slices (cm: ns * nc + 1 words of scratch)
+void tile_parts(const Csr &B, const int32_t *slice_k, const TileHeavy &t, uint32_t *cm, hipStream_t s);
+void tile_fill(const Csr &B, const int32_t *slice_k, const TileHeavy &t, int32_t *long_list, hipStream_t s);
+void tile_entries(const Csr &A, const int64_t *heavy_rows, int64_t r0, const int32_t *k_to_slice, const TileHeavy &t,
+                  hipStream_t s);
+// region sizes, bins (cls) and part counts (scanned into t.seg_end); *n_seg: all parts
+void tile_regions(const TileHeavy &t, unsigned long long *size, uint8_t *cls, int64_t *n_seg, hipStream_t s);
+void tile_segments(const TileHeavy &t, hipStream_t s);
+void tile_symbolic(const TileHeavy &t, int bin, int64_t *slot, hipStream_t s);
+void tile_numeric(const TileHeavy &t, int bin, const int64_t *heavy_rows, const int64_t *c_row_ptr,
+                  const int64_t *slot, bool ci64, bool v32, void *c_col, void *c_val, int32_t *err, hipStream_t s);
+
 // Per heavy row h: in-place exclusive scan of slot[h*n_slots .. +n_slots),
 // row total into row_nnz[heavy_rows[h]].
 void slot_scan(int64_t *slot, int64_t n_heavy, int64_t n_slots, const int64_t *heavy_rows, int64_t *row_nnz,

@@ -297,6 +297,7 @@ struct gmagnus_plan_s {
     int n_slots_log2 = 0, slot_width_log2 = 0;
     int64_t *slot = nullptr;
     std::vector<LeafLevel> leaves;
+    TileHeavy tile;                   // heavy rows accumulated from chunk-major B (tile.nh > 0), instead of leaves
     // value-producing launches of the heavy path in their order, recorded
     // under GMAGNUS_FLAG_KEEP_PATTERN and replayed by gmagnus_update_values
     std::vector<std::function<void(const Csr &, const Csr &, hipStream_t)>> replay;
@@ -801,6 +802,115 @@ int32_t expansion_path(const gmagnus_params_t &P, int64_t n_heavy, int64_t produ
 
 namespace {
 
+// Whether the heavy rows are accumulated straight from a chunk-major copy of
+// the B rows they use (tiles.hip) instead of being expanded and split in
+// memory. A caller that forces a hierarchy or an order gets it.
+bool use_tiles(const gmagnus_plan_s *p, int64_t n_slices, int64_t blen_total) {
+    const gmagnus_options_t &o = p->opts;
+    const uint32_t ordered = GMAGNUS_FLAG_PAPER_HISTOGRAM | GMAGNUS_FLAG_PAPER_EXPANSION | GMAGNUS_FLAG_SLICE_SPLIT |
+                             GMAGNUS_FLAG_LEVEL_BY_LEVEL;
+    if ((o.flags & ordered) || o.dense_width_log2 > 0 || o.chunks_max_log2 > 0 || o.lds_bytes > 0) return false;
+    // (64 first-level chunks, fp32 values of more than 2^18 int32 columns: refused as before)
+    if (p->params.n_levels > 0 && p->params.v_chunks[0] >= GM_WAVE) return false;
+    const int64_t H = p->products_heavy, nc = tile_chunks(std::max<int64_t>(p->B.n_cols, 1));
+    // part positions and region ids in 31 bits, products of a region in 32
+    if (nc > TILE_MAX_CHUNKS || H >= ((int64_t)1 << 32) || blen_total >= ((int64_t)1 << 31) ||
+        p->n_heavy * nc >= ((int64_t)1 << 31) || p->nnz_heavy * nc >= ((int64_t)1 << 40))
+        return false;
+    if (H < p->nnz_heavy * nc) return false;
+    const int64_t bytes = n_slices * nc * 10 + blen_total * (2 + p->vsize) + p->nnz_heavy * (8 + p->vsize) +
+                          p->n_heavy * nc * 34 + p->nnz_heavy * nc * 12 + 2 * H;
+    return bytes <= H * (4 + p->vsize);
+}
+
+// The tiled heavy path from the slices on: chunk-major B, region sizes and
+// bins, symbolic of every region, fragment offsets.
+template <class ValuesStep>
+void tiled_symbolic(gmagnus_plan_s *p, const SliceArrays &sl, int64_t blen_total, ValuesStep &&values_step) {
+    Workspace &ws = *p->ws;
+    const hipStream_t s = p->s_heavy;
+    TileHeavy &t = p->tile;
+    const int64_t VS = p->vsize;
+    const double CS = (double)p->csize;
+    while (t.slog < 4 && (1 << t.slog) < t.nc) ++t.slog;
+    t.ncp = (((int64_t)t.nc + (1 << t.slog) - 1) >> t.slog) << t.slog;
+    const int64_t regions = t.nh * t.ncp;
+    p->n_slots = t.ncp;
+    int32_t *long_list;
+    {
+        Timed tm(p, GMAGNUS_K_HISTOGRAM, s);
+        t.cnt = ws.alloc<uint16_t>(t.ns * t.nc);
+        t.part = ws.alloc<uint32_t>(t.ns * t.nc);
+        uint32_t *cm = ws.alloc<uint32_t>(t.ns * t.nc + 1);
+        t.scan = ws.alloc<uint32_t>(tile_scan_words(std::max(t.ns * t.nc, regions)));
+        tile_parts(p->B, sl.slice_k, t, cm, s);
+        ws.free(cm);
+        p->info.kernel_launches[GMAGNUS_K_HISTOGRAM] += 1;
+        add_bytes(p, GMAGNUS_K_HISTOGRAM, CS * blen_total + 6.0 * t.ns * t.nc);
+    }
+    {
+        Timed tm(p, GMAGNUS_K_EXPAND, s);
+        t.col = ws.alloc<uint16_t>(blen_total);
+        t.val = ws.alloc_bytes(VS * std::max<int64_t>(blen_total, 1));
+        long_list = ws.alloc<int32_t>(t.ns + 1);
+        const TileHeavy tv = t;
+        const int32_t *slice_k = sl.slice_k;
+        values_step([=](const Csr &, const Csr &B, hipStream_t st) { tile_fill(B, slice_k, tv, long_list, st); });
+        ws.free(long_list);
+        p->info.kernel_launches[GMAGNUS_K_EXPAND] += 1;
+        add_bytes(p, GMAGNUS_K_EXPAND, (CS + VS + 2.0 + VS) * blen_total + 4.0 * t.ns * t.nc);
+    }
+    t.items = ws.alloc<int64_t>(regions);
+    t.nnz = ws.alloc<uint32_t>(regions);
+    p->slot = ws.alloc<int64_t>(regions);
+    {
+        Timed tm(p, GMAGNUS_K_SETUP, s);
+        unsigned long long *size = ws.alloc<unsigned long long>(regions);
+        uint8_t *cls = ws.alloc<uint8_t>(regions);
+        int64_t *bins = ws.alloc<int64_t>(TILE_NBINS + 2);  // class bounds, then the number of parts
+        int64_t *sc = ws.alloc<int64_t>(partition_scratch_elems(regions, TILE_NBINS));
+        t.seg_end = ws.alloc<uint32_t>(regions + 1);
+        t.grp = ws.alloc<uint8_t>(regions);
+        tile_regions(t, size, cls, bins + TILE_NBINS + 1, s);
+        partition_u8(cls, regions, TILE_NBINS, t.items, nullptr, bins, sc, s);
+        fill<int64_t>(p->slot, 0, regions, s);
+        int64_t got[TILE_NBINS + 2];
+        read_bins(bins, TILE_NBINS + 1, got, s);
+        std::copy(got, got + TILE_NBINS + 1, t.bins);
+        const int64_t n_seg = got[TILE_NBINS + 1];
+        ws.free(size);
+        ws.free(cls);
+        ws.free(bins);
+        ws.free(sc);
+        ws.free(t.scan);
+        t.seg = ws.alloc<uint2>(n_seg);
+        t.seg_e = ws.alloc<uint32_t>(n_seg);
+        tile_segments(t, s);
+        ws.free(t.cnt);
+        t.bitmap = ws.alloc<uint32_t>((t.bins[TILE_M + 1] - t.bins[TILE_D_BIG]) * (TILE_COLS / 32));
+    }
+    {
+        Timed tm(p, GMAGNUS_K_CHUNK_SYM, s);
+        for (int b = TILE_D_BIG; b < TILE_NBINS; ++b) {
+            const int64_t n = t.bins[b + 1] - t.bins[b];
+            tile_symbolic(t, b, p->slot, s);
+            if (n) p->info.kernel_launches[GMAGNUS_K_CHUNK_SYM] += 1;
+            (b <= TILE_D ? p->info.n_leaves_dense : p->info.n_leaves_rank) += n;
+        }
+        add_bytes(p, GMAGNUS_K_CHUNK_SYM, 2.0 * p->products_heavy + 12.0 * (double)t.n_ent * t.nc);
+    }
+    {
+        Timed tm(p, GMAGNUS_K_ROWPTR, s);
+        slot_scan(p->slot, t.nh, t.ncp, p->heavy_rows, p->row_nnz, s);
+        add_bytes(p, GMAGNUS_K_ROWPTR, 16.0 * regions);
+    }
+    p->info.levels_run = p->params.n_levels;
+    if (p->params.n_levels > 0) {
+        p->info.level_rows_in[0] = t.nh;
+        p->info.level_elems_in[0] = p->products_heavy;
+    }
+}
+
 // Heavy path of the symbolic phase: masked CSC, expansion, multisplit
 // levels, final-chunk symbolic, fragment offsets. Runs on p->s_heavy.
 void heavy_symbolic(gmagnus_plan_s *p) {
@@ -854,6 +964,7 @@ void heavy_symbolic(gmagnus_plan_s *p) {
     SliceArrays sl;
     int64_t *row_len, *a_heavy_ptr, *scratch;
     int64_t nnz_heavy_all = 0, blen_total = 0;
+    bool tiled = false;
     {
         Timed t(p, GMAGNUS_K_CSC, s);
         row_len = ws.alloc<int64_t>(nh);
@@ -903,7 +1014,23 @@ void heavy_symbolic(gmagnus_plan_s *p) {
         GM_REQUIRE(tot[1] == H, GMAGNUS_ERROR_HIP, "slice products disagree with the row products");
         GM_REQUIRE(tot[3] == nnz_heavy_all, GMAGNUS_ERROR_HIP, "heavy rows' entries disagree with the plan's count");
         int64_t *cursor = nullptr;
-        if (!rows_order) {
+        tiled = use_tiles(p, sl.n_slices, blen_total);
+        if (tiled) {
+            TileHeavy &t = p->tile;
+            t.nc = tile_chunks(p->B.n_cols);
+            t.ns = sl.n_slices;
+            t.nh = nh;
+            t.n_ent = nnz_heavy_all;
+            t.n_elems = blen_total;
+            t.a_ptr = a_heavy_ptr;
+            t.es = ws.alloc<int32_t>(nnz_heavy_all);
+            t.eh = ws.alloc<int32_t>(nnz_heavy_all);
+            t.ea = ws.alloc_bytes(VS * nnz_heavy_all);
+            const TileHeavy tv = t;
+            values_step([=](const Csr &A, const Csr &, hipStream_t st) {
+                tile_entries(A, heavy_rows, r0, k_to_slice, tv, st);
+            });
+        } else if (!rows_order) {
             cursor = ws.alloc<int64_t>(std::max<int64_t>(sl.n_slices, 1));
             sl.row_h = ws.alloc<int32_t>(sl.nnz);
             sl.a_val = ws.alloc_bytes(VS * sl.nnz);
@@ -922,7 +1049,7 @@ void heavy_symbolic(gmagnus_plan_s *p) {
                 heavy_entries(A, B, heavy_rows, nh, r0, a_heavy_ptr, nnz_heavy_all, k_to_slice, ent, st);
             });
         }
-        if (P.n_levels > 0 && !paper_hist) {
+        if (P.n_levels > 0 && !paper_hist && !tiled) {
             // level-0 (row, chunk) counts from the structure of A~ and B
             Timed t2(p, GMAGNUS_K_HISTOGRAM, s);
             const int nc0 = P.v_chunks[0];
@@ -962,7 +1089,7 @@ void heavy_symbolic(gmagnus_plan_s *p) {
         ws.free(k_to_slice);
         ws.free(sc2);
         ws.free(row_len);
-        if (rows_order)
+        if (rows_order || tiled)
             a_heavy_keep = a_heavy_ptr;  // region records need the row pointers of A~
         else
             ws.free(a_heavy_ptr);
@@ -971,6 +1098,10 @@ void heavy_symbolic(gmagnus_plan_s *p) {
     }
     p->info.n_slices = sl.n_slices;
     p->info.nnz_a_heavy = sl.nnz;
+    if (tiled) {
+        tiled_symbolic(p, sl, blen_total, values_step);
+        return;
+    }
 
     // ---- outer-product expansion into buffer 0 (C-hat row by row, or
     // already split into the first level's chunks when fused)
@@ -1496,6 +1627,13 @@ void do_numeric(gmagnus_plan_s *p, const int64_t *c_row_ptr, void *c_col, void *
     {
         const hipStream_t s = p->s_heavy;
         Timed t(p, GMAGNUS_K_CHUNK_NUM, s);
+        if (p->tile.nh > 0) {
+            for (int b = TILE_D_BIG; b < TILE_NBINS; ++b) {
+                tile_numeric(p->tile, b, p->heavy_rows, c_row_ptr, p->slot, p->B.ci64, p->B.v32, c_col, c_val, p->err, s);
+                if (p->tile.bins[b + 1] > p->tile.bins[b]) p->info.kernel_launches[GMAGNUS_K_CHUNK_NUM] += 1;
+            }
+            add_bytes(p, GMAGNUS_K_CHUNK_NUM, (2.0 + p->vsize) * p->products_heavy);
+        }
         for (auto &lv : p->leaves) {
             const int64_t nl = lv.set.hi - lv.set.lo;
             if (nl <= 0) continue;

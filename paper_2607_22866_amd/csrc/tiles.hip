@@ -1,0 +1,1178 @@
+// Heavy rows accumulated straight from a chunk-major copy of B, with no
+// expansion in memory.
+//
+// C's columns are cut into chunks of TILE_COLS = 2^14. The B rows that the
+// heavy rows use (the slices) are copied once into chunk-major order: chunk c
+// holds, slice by slice, the part of every slice's row that falls in the
+// chunk, with 16-bit chunk-local columns. A region is a heavy row of C
+// restricted to one chunk (or, for sparse rows, to several adjacent chunks);
+// its products are the parts that the row's A entries meet in it, scaled. The
+// non-empty parts of every region are listed once (start, length, A entry);
+// then a wave or a work group per region reads its parts and accumulates them
+// in LDS, counting distinct columns in the symbolic phase and summing values
+// in the numeric phase.
+//
+// Why: writing the products out, splitting them by column and reading them
+// back twice moves about 34 bytes per product through HBM. Here a product
+// costs 2 bytes of reads in the symbolic and 10 in the numeric phase, most of
+// them served by the L2s (70 % hits in the numeric kernel of the large
+// regions) because regions run in chunk order and share the chunk's part of B.
+// The price is one visit per (A entry, chunk), so the path is taken when the
+// entries' parts are long enough (use_tiles in plan.hip).
+#include <algorithm>
+#include <type_traits>
+
+#include "host.hpp"
+
+namespace gm {
+
+namespace {
+
+constexpr int TWORDS = TILE_COLS / 32;
+constexpr int TU = 4;                       // products per lane in flight (8: the same times)
+constexpr int TWIN = GM_WAVE * TU;          // products of one wave window
+constexpr int TLONG = 256;                  // longer parts are shared by the work group's waves
+constexpr int TLONG_CAP = 128;              // parts the shared list holds
+
+// ------------------------------------------------------------- chunk-major B
+constexpr int TR_WAVES = 4, TR_ILP = 8, TR_STREAM = 4096, TR_PER = 4;
+
+// Elements of every slice's B row per chunk: cnt[s * nc + c]. One wave per
+// slice. Rows of at most TR_STREAM elements are read once and counted by runs
+// (a sorted row meets every chunk in one run per 64 elements); longer rows
+// take the chunk bounds by binary searches, TR_PER per lane stepping together.
+template <typename CI>
+__global__ __launch_bounds__(TR_WAVES * GM_WAVE) void k_tile_row_counts(CsrV<CI, NoV> B, const int32_t *slice_k,
+                                                                        int64_t ns, int nc, uint16_t *cnt) {
+    extern __shared__ uint32_t tr_hist[];  // TR_WAVES * (nc + 1)
+    const int lane = threadIdx.x & (GM_WAVE - 1);
+    uint32_t *hist = tr_hist + (threadIdx.x / GM_WAVE) * (nc + 1);
+    const int64_t nwaves = (int64_t)gridDim.x * TR_WAVES;
+    for (int64_t s = blockIdx.x * (int64_t)TR_WAVES + threadIdx.x / GM_WAVE; s < ns; s += nwaves) {
+        const int32_t k = slice_k[s];
+        const int64_t b0 = B.rp[k], len = B.rp[k + 1] - b0;
+        const CI *row = B.ci + b0;
+        uint16_t *out = cnt + s * nc;
+        if (len <= TR_STREAM) {  // uniform over the wave
+            for (int f = lane; f < nc; f += GM_WAVE) hist[f] = 0;
+            wave_lds_fence();
+            for (int p0 = 0; p0 < (int)len; p0 += GM_WAVE * TR_ILP) {
+                int fc[TR_ILP];
+#pragma unroll
+                for (int u = 0; u < TR_ILP; ++u) {
+                    const int p = p0 + u * GM_WAVE + lane;
+                    const int64_t f = p < (int)len ? ((int64_t)row[p] >> TILE_LOG2) : -1;
+                    fc[u] = f < nc ? (int)f : nc - 1;
+                }
+#pragma unroll
+                for (int u = 0; u < TR_ILP; ++u) {
+                    const int fp = prev_lane(fc[u], -2);
+                    const uint64_t starts = ballot(fc[u] >= 0 && fc[u] != fp);
+                    if (fc[u] >= 0 && ((starts >> lane) & 1)) {
+                        const uint64_t above = starts & ~((lanemask_lt() << 1) | 1ull);
+                        const int left = (int)len - (p0 + u * GM_WAVE);
+                        const int end = above ? __ffsll((long long)above) - 1 : (left < GM_WAVE ? left : GM_WAVE);
+                        atomicAdd(&hist[fc[u]], (uint32_t)(end - lane));
+                    }
+                }
+            }
+            wave_lds_fence();
+            for (int f = lane; f < nc; f += GM_WAVE) out[f] = (uint16_t)hist[f];
+            wave_lds_fence();  // the counters are read before the next slice clears them
+            continue;
+        }
+        for (int f0 = 0; f0 <= nc; f0 += TR_PER * GM_WAVE) {
+            int64_t lo[TR_PER], hi[TR_PER];
+#pragma unroll
+            for (int j = 0; j < TR_PER; ++j) {
+                const int f = f0 + lane + j * GM_WAVE;
+                lo[j] = f < nc ? 0 : len;  // bound nc is the row's end
+                hi[j] = len;
+            }
+            for (int st = 64 - __clzll((long long)len); st > 0; --st) {
+#pragma unroll
+                for (int j = 0; j < TR_PER; ++j) {
+                    const int64_t mid = (lo[j] + hi[j]) >> 1;
+                    const bool go = lo[j] < hi[j];
+                    const int64_t col = go ? (int64_t)row[mid] : 0;
+                    if (go) {
+                        if (col < ((int64_t)(f0 + lane + j * GM_WAVE) << TILE_LOG2))
+                            lo[j] = mid + 1;
+                        else
+                            hi[j] = mid;
+                    }
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < TR_PER; ++j) {
+                const int f = f0 + lane + j * GM_WAVE;
+                if (f <= nc) hist[f] = (uint32_t)lo[j];
+            }
+        }
+        wave_lds_fence();
+        for (int f = lane; f < nc; f += GM_WAVE) out[f] = (uint16_t)(hist[f + 1] - hist[f]);
+        wave_lds_fence();
+    }
+}
+
+// out[c * rows + r] = in[r * cols + c], 64 x 64 tiles through LDS.
+constexpr int TT = 64;
+template <typename T>
+__global__ __launch_bounds__(256) void k_tile_transpose(const T *in, int64_t rows, int64_t cols, uint32_t *out) {
+    __shared__ uint32_t t[TT][TT + 1];
+    const int64_t n_rt = (rows + TT - 1) / TT;
+    const int64_t r0 = (blockIdx.x % n_rt) * TT, c0 = (blockIdx.x / n_rt) * TT;
+    const int x = threadIdx.x & (TT - 1), y0 = threadIdx.x / TT;
+    for (int y = y0; y < TT; y += 256 / TT)
+        if (r0 + y < rows && c0 + x < cols) t[y][x] = in[(r0 + y) * cols + c0 + x];
+    __syncthreads();
+    for (int y = y0; y < TT; y += 256 / TT)
+        if (c0 + y < cols && r0 + x < rows) out[(c0 + y) * rows + r0 + x] = t[x][y];
+}
+
+// In-place exclusive scan of uint32 values (sums below 2^32).
+constexpr int SC_BLOCK = 256, SC_ITEMS = 16;
+constexpr int64_t SC_TILE = SC_BLOCK * SC_ITEMS;
+
+GM_DEV void sc_load(const uint32_t *a, int64_t base, int64_t n, uint32_t (&v)[SC_ITEMS]) {
+    if (base + SC_ITEMS <= n) {  // base is a multiple of 16 and the array 16-byte aligned
+#pragma unroll
+        for (int j = 0; j < SC_ITEMS; j += 4) {
+            const uint4 q = *(const uint4 *)(a + base + j);
+            v[j] = q.x;
+            v[j + 1] = q.y;
+            v[j + 2] = q.z;
+            v[j + 3] = q.w;
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < SC_ITEMS; ++j) v[j] = base + j < n ? a[base + j] : 0u;
+    }
+}
+
+__global__ __launch_bounds__(SC_BLOCK) void k_tile_scan_sums(const uint32_t *a, int64_t n, uint32_t *sums) {
+    __shared__ int32_t sm[SC_BLOCK / GM_WAVE];
+    uint32_t v[SC_ITEMS];
+    sc_load(a, blockIdx.x * SC_TILE + (int64_t)threadIdx.x * SC_ITEMS, n, v);
+    uint32_t s = 0;
+#pragma unroll
+    for (int j = 0; j < SC_ITEMS; ++j) s += v[j];
+    const int32_t tot = block_reduce_sum<SC_BLOCK>((int32_t)s, sm);
+    if (threadIdx.x == 0) sums[blockIdx.x] = (uint32_t)tot;
+}
+
+__global__ __launch_bounds__(1024) void k_tile_scan_mid(uint32_t *sums, int64_t n) {
+    __shared__ int32_t sm[1024 / GM_WAVE];
+    int32_t carry = 0;
+    for (int64_t b = 0; b < n; b += 1024) {
+        const int64_t i = b + threadIdx.x;
+        const int32_t x = i < n ? (int32_t)sums[i] : 0;
+        int32_t tot;
+        const int32_t ex = block_excl_scan<1024>(x, sm, &tot);
+        if (i < n) sums[i] = (uint32_t)(carry + ex);
+        carry += tot;
+    }
+}
+
+// (also writes the total at a[n])
+__global__ __launch_bounds__(SC_BLOCK) void k_tile_scan_apply(uint32_t *a, int64_t n, const uint32_t *sums) {
+    __shared__ int32_t sm[SC_BLOCK / GM_WAVE];
+    const int64_t base = blockIdx.x * SC_TILE + (int64_t)threadIdx.x * SC_ITEMS;
+    uint32_t v[SC_ITEMS];
+    sc_load(a, base, n, v);
+    uint32_t s = 0;
+#pragma unroll
+    for (int j = 0; j < SC_ITEMS; ++j) s += v[j];
+    uint32_t run = sums[blockIdx.x] + (uint32_t)block_excl_scan<SC_BLOCK>((int32_t)s, sm);
+#pragma unroll
+    for (int j = 0; j < SC_ITEMS; ++j) {
+        const uint32_t x = v[j];
+        v[j] = run;
+        run += x;
+    }
+    if (base + SC_ITEMS <= n) {
+#pragma unroll
+        for (int j = 0; j < SC_ITEMS; j += 4) *(uint4 *)(a + base + j) = make_uint4(v[j], v[j + 1], v[j + 2], v[j + 3]);
+    } else {
+#pragma unroll
+        for (int j = 0; j < SC_ITEMS; ++j)
+            if (base + j < n) a[base + j] = v[j];
+    }
+    if (base <= n - 1 && n - 1 < base + SC_ITEMS) a[n] = run;
+}
+
+// Copies elements [p0, p1) of a slice's row (part: its parts' starts) into the chunk-major arrays, one
+// wave: an element's place is its part's start plus its index in the part.
+// `run_f`, `run_at`: the chunk that is open at p0 and the row index where it
+// starts (run_f = -1: none).
+template <typename CI, typename V>
+GM_DEV void tile_copy_row(const CI *row, const V *val, int64_t p0, int64_t p1, int nc, const uint32_t *part,
+                          int64_t n_elems, int run_f, int64_t run_at, uint16_t *out_col, V *out_val) {
+    constexpr int U = 4;
+    const int lane = threadIdx.x & (GM_WAVE - 1);
+    const uint64_t le_mask = lanemask_lt() | (uint64_t(1) << lane);
+    for (int64_t b = p0; b < p1; b += GM_WAVE * U) {
+        CI c[U];
+        V v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t p = b + u * GM_WAVE + lane;
+            c[u] = row[p < p1 ? p : p1 - 1];
+            v[u] = val[p < p1 ? p : p1 - 1];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t q = b + u * GM_WAVE;
+            if (q >= p1) break;  // uniform
+            const int64_t p = q + lane;
+            const bool in = p < p1;
+            int64_t f64 = (int64_t)c[u] >> TILE_LOG2;
+            const int f = f64 < nc ? (int)f64 : nc - 1;
+            const int fp = prev_lane(f, run_f);
+            const uint64_t heads = ballot(in && f != fp);
+            const uint64_t mine = heads & le_mask;
+            const int64_t at = mine ? q + 63 - __clzll((long long)mine) : run_at;
+            if (in) {
+                const int64_t d = (int64_t)part[f] + (p - at);
+                if (d < n_elems) {  // (always, for canonical rows)
+                    out_col[d] = (uint16_t)((int64_t)c[u] & (TILE_COLS - 1));
+                    out_val[d] = v[u];
+                }
+            }
+            const int last = p1 - q < GM_WAVE ? (int)(p1 - q) - 1 : GM_WAVE - 1;
+            run_f = __builtin_amdgcn_readlane(f, last);
+            if (heads) run_at = q + 63 - __clzll((long long)heads);
+        }
+    }
+}
+
+constexpr int TF_WAVES = 4;
+constexpr int64_t TF_LONG = 2048;  // longer rows are copied in pieces of this many elements by many waves
+
+// Rows of at most TF_LONG elements, one wave each; longer ones are listed.
+template <typename CI, typename V>
+__global__ __launch_bounds__(TF_WAVES * GM_WAVE) void k_tile_fill(CsrV<CI, V> B, const int32_t *slice_k, int64_t ns,
+                                                                  int nc, const uint32_t *part, int64_t n_elems,
+                                                                  uint16_t *out_col, V *out_val, int32_t *n_long,
+                                                                  int32_t *long_list) {
+    const int64_t nwaves = (int64_t)gridDim.x * TF_WAVES;
+    for (int64_t s = blockIdx.x * (int64_t)TF_WAVES + threadIdx.x / GM_WAVE; s < ns; s += nwaves) {
+        const int32_t k = slice_k[s];
+        const int64_t b0 = B.rp[k], len = B.rp[k + 1] - b0;
+        if (len > TF_LONG) {
+            if ((threadIdx.x & (GM_WAVE - 1)) == 0) long_list[atomicAdd(n_long, 1)] = (int32_t)s;
+            continue;
+        }
+        tile_copy_row<CI, V>(B.ci + b0, B.v + b0, 0, len, nc, part + s * nc, n_elems, -1, 0, out_col, out_val);
+    }
+}
+
+// The listed rows: blockIdx.y strides over the list, the waves of blockIdx.x
+// over a row's pieces.
+template <typename CI, typename V>
+__global__ __launch_bounds__(TF_WAVES * GM_WAVE) void k_tile_fill_long(CsrV<CI, V> B, const int32_t *slice_k,
+                                                                       int64_t ns, int nc, const uint32_t *part,
+                                                                       int64_t n_elems, uint16_t *out_col, V *out_val,
+                                                                       const int32_t *n_long,
+                                                                       const int32_t *long_list) {
+    const int n = *n_long;
+    for (int i = blockIdx.y; i < n; i += gridDim.y) {
+        const int64_t s = long_list[i];
+        const int32_t k = slice_k[s];
+        const int64_t b0 = B.rp[k], len = B.rp[k + 1] - b0;
+        const CI *row = B.ci + b0;
+        const int64_t step = (int64_t)gridDim.x * TF_WAVES * TF_LONG;
+        for (int64_t p0 = (blockIdx.x * (int64_t)TF_WAVES + threadIdx.x / GM_WAVE) * TF_LONG; p0 < len; p0 += step) {
+            // chunk open at p0 and where it starts in the row
+            const int64_t f64 = (int64_t)row[p0] >> TILE_LOG2;
+            int64_t lo = 0, hi = p0;
+            while (lo < hi) {
+                const int64_t mid = (lo + hi) >> 1;
+                if (((int64_t)row[mid] >> TILE_LOG2) < f64)
+                    lo = mid + 1;
+                else
+                    hi = mid;
+            }
+            const int64_t p1 = p0 + TF_LONG < len ? p0 + TF_LONG : len;
+            tile_copy_row<CI, V>(row, B.v + b0, p0, p1, nc, part + s * nc, n_elems, (int)(f64 < nc ? f64 : nc - 1), lo,
+                                 out_col, out_val);
+        }
+    }
+}
+
+// ------------------------------------------------------ entries and regions
+template <typename CI, typename V>
+__global__ void k_tile_entries(CsrV<CI, V> A, const int64_t *heavy_rows, int64_t n_heavy, int64_t r0,
+                               const int64_t *a_heavy_ptr, int64_t total, const int32_t *k_to_slice, int32_t *es,
+                               int32_t *eh, V *ea) {
+    for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < total;
+         e += (int64_t)gridDim.x * blockDim.x) {
+        const int64_t h = find_row(a_heavy_ptr, 0, n_heavy + 1, e);
+        const int64_t j = A.rp[r0 + heavy_rows[h]] + (e - a_heavy_ptr[h]);
+        es[e] = k_to_slice[(int64_t)A.ci[j]];
+        eh[e] = (int32_t)h;
+        ea[e] = A.v[j];
+    }
+}
+
+// Places of a region (c, h): its item id is c * nh + h (regions of one chunk
+// together, so that concurrent work groups share the chunk's part of B); its
+// list of parts is number (c / S * nh + h) * S + c % S (S = 2^slog chunks of a
+// row next to each other, so that their lists can be read as one).
+GM_DEV int64_t list_of(int64_t c, int64_t h, int64_t nh, int slog) {
+    return ((((c >> slog) * nh) + h) << slog) + (c & ((1 << slog) - 1));
+}
+
+// Products and non-empty parts of every list (size: parts << 32 | products).
+// A work group takes TE_BLOCK consecutive entries, a thread one chunk of a
+// contiguous group of them, so the chunk sizes of a slice are read coalesced;
+// one atomic per (row, chunk) and group.
+constexpr int TE_BLOCK = 256, TE_U = 8;
+__global__ __launch_bounds__(TE_BLOCK) void k_tile_sizes(const int32_t *es, const int32_t *eh, int64_t n_ent,
+                                                         const uint16_t *cnt, int nc, int ncb, int64_t nh, int slog,
+                                                         unsigned long long *size) {
+    __shared__ int32_t s_s[TE_BLOCK], s_h[TE_BLOCK];
+    const int64_t e0 = blockIdx.x * (int64_t)TE_BLOCK;
+    const int ne = (int)(n_ent - e0 < TE_BLOCK ? n_ent - e0 : TE_BLOCK);
+    const int tid = threadIdx.x;
+    if (tid < ne) {
+        s_s[tid] = es[e0 + tid];
+        s_h[tid] = eh[e0 + tid];
+    }
+    __syncthreads();
+    const int i0 = (tid / ncb) * ncb, i1 = i0 + ncb < ne ? i0 + ncb : ne;
+    const int c = blockIdx.y * ncb + tid % ncb;
+    if (i0 >= i1 || c >= nc) return;
+    int cur = s_h[i0];
+    uint32_t sum = 0, n = 0;
+    auto flush = [&]() {
+        if (n) atomicAdd(&size[list_of(c, cur, nh, slog)], ((unsigned long long)n << 32) | sum);
+        sum = n = 0;
+    };
+    for (int i = i0; i < i1; i += TE_U) {
+        uint32_t v[TE_U];
+#pragma unroll
+        for (int u = 0; u < TE_U; ++u) {
+            const int q = i + u < i1 ? i + u : i1 - 1;
+            const int32_t s = s_s[q];
+            v[u] = s >= 0 && i + u < i1 ? cnt[(int64_t)s * nc + c] : 0u;
+        }
+#pragma unroll
+        for (int u = 0; u < TE_U; ++u) {
+            if (i + u >= i1) break;
+            if (s_h[i + u] != cur) {
+                flush();
+                cur = s_h[i + u];
+            }
+            sum += v[u];
+            n += v[u] > 0;
+        }
+    }
+    flush();
+}
+
+// The lists: seg = (start of the part in the chunk-major B, its length | its
+// chunk within the S chunks << 16), seg_e = A entry; cursor[l] starts at list
+// l's first place and ends one past its last. Tiles of 64 entries x TL_C
+// chunks pass through LDS: read a slice at a time (coalesced), written a
+// chunk at a time with an entry per lane, so that a row's parts go out as one
+// contiguous store (writing them a thread per chunk, 8 bytes at a time into
+// as many lists as threads, took 3.1 ms instead of 1.9 for 1e8 parts).
+constexpr int TL_BLOCK = 256, TL_C = 128, TL_U = 8;
+__global__ __launch_bounds__(TL_BLOCK) void k_tile_lists(const int32_t *es, const int32_t *eh, int64_t n_ent,
+                                                         const uint16_t *cnt, const uint32_t *part, int nc, int64_t nh,
+                                                         int slog, uint32_t *cursor, uint2 *seg, uint32_t *seg_e) {
+    __shared__ uint32_t t_st[GM_WAVE][TL_C + 1];
+    __shared__ uint16_t t_len[GM_WAVE][TL_C + 2];
+    __shared__ int32_t s_s[GM_WAVE];
+    const int tid = threadIdx.x, lane = tid & (GM_WAVE - 1), w = tid / GM_WAVE;
+    const int64_t e0 = blockIdx.x * (int64_t)GM_WAVE;
+    const int c0 = blockIdx.y * TL_C, ncc = nc - c0 < TL_C ? nc - c0 : TL_C;
+    const int64_t e = e0 + lane;
+    const int32_t h = e < n_ent ? eh[e] : -1;
+    if (w == 0) s_s[lane] = e < n_ent ? es[e] : -1;
+    __syncthreads();
+    {
+        constexpr int RPB = TL_BLOCK / TL_C;  // slices read at a time
+        const int c = tid & (TL_C - 1);
+        for (int i0 = tid / TL_C; i0 < GM_WAVE; i0 += RPB * TL_U) {
+            uint32_t len[TL_U], st[TL_U];
+#pragma unroll
+            for (int u = 0; u < TL_U; ++u) {
+                const int32_t s = s_s[i0 + u * RPB];
+                const bool ok = s >= 0 && c < ncc;
+                len[u] = ok ? cnt[(int64_t)s * nc + c0 + c] : 0u;
+                st[u] = ok ? part[(int64_t)s * nc + c0 + c] : 0u;
+            }
+#pragma unroll
+            for (int u = 0; u < TL_U; ++u) {
+                t_len[i0 + u * RPB][c] = (uint16_t)len[u];
+                t_st[i0 + u * RPB][c] = st[u];
+            }
+        }
+    }
+    __syncthreads();
+    const uint64_t le_mask = lanemask_lt() | (uint64_t(1) << lane);
+    const int32_t hp = prev_lane(h, -2);
+    const uint64_t heads = ballot(h != hp);  // lane 0 always starts a run
+    const int first = 63 - __clzll((long long)(heads & le_mask));
+    const uint64_t above = heads & ~le_mask;
+    const int end = above ? __ffsll((long long)above) - 1 : GM_WAVE;  // lane after the run
+    const uint64_t run = (end == GM_WAVE ? ~0ull : (uint64_t(1) << end) - 1) & ~((uint64_t(1) << first) - 1);
+    // TL_U chunks at a time: their reservations are in flight together
+    for (int cb = w; cb < ncc; cb += TL_U * (TL_BLOCK / GM_WAVE)) {
+        uint32_t len[TL_U], at[TL_U];
+        uint64_t full[TL_U];
+#pragma unroll
+        for (int u = 0; u < TL_U; ++u) {
+            const int c = cb + u * (TL_BLOCK / GM_WAVE);
+            len[u] = c < ncc ? t_len[lane][c] : 0u;
+            full[u] = ballot(len[u] > 0) & run;
+            at[u] = 0;
+            if (lane == first && full[u])
+                at[u] = atomicAdd(&cursor[list_of(c0 + c, h, nh, slog)], (uint32_t)__popcll(full[u]));
+        }
+#pragma unroll
+        for (int u = 0; u < TL_U; ++u) {
+            const int c = cb + u * (TL_BLOCK / GM_WAVE);
+            const uint32_t q = (uint32_t)__shfl((int32_t)at[u], first, GM_WAVE) +
+                               (uint32_t)__popcll(full[u] & lanemask_lt());
+            if (len[u] > 0) {
+                seg[q] = make_uint2(t_st[lane][c], len[u] | (uint32_t)((c0 + c) & ((1 << slog) - 1)) << 16);
+                seg_e[q] = (uint32_t)e;
+            }
+        }
+    }
+}
+
+// Regions, bins and list lengths. The S chunks of a row are cut into aligned
+// groups of a power of two of chunks that hold at most TILE_MERGE products
+// together (one region each, at the group's first chunk; grp = its chunks), so
+// that sparse rows make few regions; chunks above that stay alone.
+template <int S>
+__global__ void k_tile_classes(const unsigned long long *size, int64_t nh, int64_t n_lists, uint8_t *cls, uint8_t *grp,
+                               uint32_t *list_len) {
+    for (int64_t g = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; g < n_lists / S;
+         g += (int64_t)gridDim.x * blockDim.x) {
+        uint32_t sum[S];
+        uint8_t len[S];
+#pragma unroll
+        for (int q = 0; q < S; ++q) {
+            const unsigned long long x = size[g * S + q];
+            sum[q] = (uint32_t)x;
+            len[q] = 1;
+            list_len[g * S + q] = (uint32_t)(x >> 32);
+        }
+#pragma unroll
+        for (int w = 2; w <= S; w *= 2)
+#pragma unroll
+            for (int q = 0; q < S; q += w) {
+                // (a sum that passed TILE_MERGE is never merged further)
+                const uint32_t a = sum[q], b = sum[q + w / 2];
+                if (len[q] == w / 2 && len[q + w / 2] == w / 2 && a <= (uint32_t)TILE_MERGE &&
+                    b <= (uint32_t)TILE_MERGE && a + b <= (uint32_t)TILE_MERGE) {
+                    sum[q] = a + b;
+                    sum[q + w / 2] = 0;
+                    len[q] = (uint8_t)w;
+                    len[q + w / 2] = 0;
+                }
+            }
+        const int64_t C = g / nh, h = g - C * nh;
+#pragma unroll
+        for (int q = 0; q < S; ++q) {
+            const uint32_t z = sum[q];
+            const int64_t i = (C * S + q) * nh + h;
+            grp[i] = len[q];
+            cls[i] = z == 0             ? TILE_EMPTY
+                     : z <= TILE_T_MAX  ? TILE_T
+                     : z <= TILE_S_MAX  ? TILE_S
+                     : z <= TILE_MERGE  ? TILE_L
+                     : z <= TILE_M_MAX  ? TILE_M
+                     : z <= TILE_D_MAX  ? TILE_D
+                                        : TILE_D_BIG;
+        }
+    }
+}
+
+__global__ void k_tile_total(const uint32_t *v, int64_t *out) { *out = (int64_t)*v; }
+
+// ------------------------------------------------------------- accumulation
+// What a region's kernel reads.
+template <typename V>
+struct TileArgs {
+    const uint16_t *col;
+    const V *val;
+    const uint2 *seg;          // the regions' parts: start, length | chunk within its S chunks << 16
+    const uint32_t *seg_e;     // A entry of a part
+    const uint32_t *seg_end;   // one past list l's last part (list l starts at seg_end[l - 1])
+    const V *ea;
+    int64_t nh;
+    int slog;                  // log2 S
+    const uint8_t *grp;        // chunks of a region
+    const int64_t *items;      // region ids c * nh + h of the bin
+    int64_t n_items;
+    uint32_t *bitmap;          // TWORDS words per item (bins of more than TILE_MERGE products), or null
+};
+
+struct Region {
+    int64_t c, h;       // first chunk, heavy row
+    uint32_t q0, q1;    // parts
+    int chunks;
+    uint32_t sub0;      // first chunk within its S chunks
+};
+template <typename V>
+GM_DEV Region region_at(const TileArgs<V> &t, int64_t i) {
+    Region g;
+    const int64_t id = t.items[i];
+    g.c = id / t.nh;
+    g.h = id - g.c * t.nh;
+    g.chunks = t.grp[id];
+    g.sub0 = (uint32_t)(g.c & ((1 << t.slog) - 1));
+    const int64_t l = list_of(g.c, g.h, t.nh, t.slog);
+    g.q0 = l > 0 ? t.seg_end[l - 1] : 0u;
+    g.q1 = t.seg_end[l + g.chunks - 1];
+    return g;
+}
+
+// Calls f(column, product) for the parts held one per lane (start
+// `st`, `len` elements, scale `a`; the lanes past the last part hold len = 0),
+// in windows of TWIN products. A product's part is the number of parts that
+// end before it: the parts' last products are marked in `ends` (one bit per
+// product of the window) and counted below the lane.
+constexpr int TENDS = TWIN / 32;
+template <bool NUM, typename V, class F>
+GM_DEV void wave_parts(const uint16_t *col, const V *val, uint32_t st, uint32_t len, V a, uint32_t *ends, F &&f) {
+    const int lane = threadIdx.x & (GM_WAVE - 1);
+    const uint32_t inc = (uint32_t)wave_incl_scan<int32_t>((int32_t)len);
+    const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)inc, GM_WAVE - 1);
+    const uint32_t rel = st - (inc - len);
+    const uint32_t st0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)st);
+    uint32_t ended = 0;  // parts that end before the window
+    for (uint32_t w0 = 0; w0 < total; w0 += TWIN) {
+        if (lane < TENDS) ends[lane] = 0u;
+        wave_lds_fence();
+        const uint32_t d = inc - 1 - w0;
+        if (d < (uint32_t)TWIN)
+            __hip_atomic_fetch_or(&ends[d >> 5], 1u << (d & 31), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+        wave_lds_fence();
+        uint32_t own[TU], pos[TU];
+#pragma unroll
+        for (int u = 0; u < TU; ++u) {
+            const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)ends[2 * u]);
+            const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)ends[2 * u + 1]);
+            own[u] = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, ended));
+            ended += (uint32_t)(__popc(lo) + __popc(hi));
+            const uint32_t t = w0 + u * GM_WAVE + lane;
+            const uint32_t p = (uint32_t)__shfl((int)rel, (int)own[u], GM_WAVE) + t;
+            pos[u] = t < total ? p : st0;
+        }
+        uint32_t c[TU];
+        V v[TU];
+#pragma unroll
+        for (int u = 0; u < TU; ++u) {
+            c[u] = col[pos[u]];
+            if (NUM) v[u] = val[pos[u]];
+        }
+#pragma unroll
+        for (int u = 0; u < TU; ++u) {
+            V p = (V)0;
+            if (NUM) p = __shfl(a, (int)own[u], GM_WAVE) * v[u];
+            const uint32_t t = w0 + u * GM_WAVE + lane;
+            if (t < total) f(c[u], p);
+        }
+    }
+}
+
+// Shared list of the tails of a region's long parts.
+template <typename V>
+struct LongParts {
+    int32_t n;
+    uint32_t st[TLONG_CAP], len[TLONG_CAP];
+    V a[TLONG_CAP];
+};
+
+// Calls f(column, product) for all products of a region of one chunk, for a
+// work group of NW waves: wave w takes parts w, w + NW, ... (the longest B
+// rows sit next to each other in a row's entries); what a part holds past
+// TLONG elements goes to the list, whose windows the waves then share. Called
+// by every thread; the list must be empty (n = 0) and a barrier behind it;
+// ends without a barrier.
+template <int NW, bool NUM, typename V, class F>
+GM_DEV void tile_products(const TileArgs<V> &t, const Region &g, uint32_t *ends, LongParts<V> *lp, F &&f) {
+    const int lane = threadIdx.x & (GM_WAVE - 1);
+    const uint32_t w = threadIdx.x / GM_WAVE;
+    for (uint32_t jb = g.q0 + w; jb < g.q1; jb += GM_WAVE * NW) {
+        const uint32_t q = jb + lane * NW;
+        uint32_t st = 0, len = 0;
+        V a = (V)0;
+        if (q < g.q1) {
+            const uint2 sg = t.seg[q];
+            st = sg.x;
+            len = sg.y & 0xffffu;
+            if (NUM) a = t.ea[t.seg_e[q]];
+        }
+        if (len > TLONG) {
+            const int i = atomicAdd(&lp->n, 1);
+            if (i < TLONG_CAP) {
+                lp->st[i] = st + TLONG;
+                lp->len[i] = len - TLONG;
+                if (NUM) lp->a[i] = a;
+                len = TLONG;
+            }
+        }
+        wave_parts<NUM>(t.col, t.val, st, len, a, ends, f);
+    }
+    __syncthreads();
+    const int n = lp->n < TLONG_CAP ? lp->n : TLONG_CAP;
+    uint32_t k = w;  // next window of this wave, counted over the listed parts
+    for (int i = 0; i < n; ++i) {
+        const uint32_t st = lp->st[i], len = lp->len[i];
+        const V a = NUM ? lp->a[i] : (V)0;
+        const uint32_t nwin = (len + TWIN - 1) / TWIN;
+        for (; k < nwin; k += NW) {
+            uint32_t cc[TU];
+            V v[TU];
+#pragma unroll
+            for (int u = 0; u < TU; ++u) {
+                const uint32_t x = k * TWIN + u * GM_WAVE + lane;
+                const uint32_t p = st + (x < len ? x : len - 1);
+                cc[u] = t.col[p];
+                if (NUM) v[u] = t.val[p];
+            }
+#pragma unroll
+            for (int u = 0; u < TU; ++u)
+                if (k * TWIN + u * GM_WAVE + lane < len) f(cc[u], NUM ? (V)(a * v[u]) : (V)0);
+        }
+        k -= nwin;
+    }
+}
+
+GM_DEV void bit_or(uint32_t *bits, uint32_t c) {
+    __hip_atomic_fetch_or(&bits[c >> 5], 1u << (c & 31), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// The bitmap with every word's rank beside it (the present columns, or words, before it).
+struct RankWord {
+    uint32_t bits, rank;
+};
+GM_DEV uint32_t rank_of(const RankWord &x, uint32_t bit) { return x.rank + (uint32_t)__popc(x.bits & ((1u << bit) - 1u)); }
+
+// Regions of at most TILE_MERGE products, up to 2^18 columns wide, one
+// thread of a work group (or lane of a wave: BLOCK = 64, several regions per
+// work group, no barrier between them) holding EPT = CAP / BLOCK products in
+// registers. The region's parts are laid out in product order (their last
+// products marked in a bitmap, which gives a product its part), so every
+// thread's loads go out at once. The 32-column words that hold columns are
+// marked in a bitmap of words; a scan numbers them, the columns are marked in
+// those words only, and a second scan gives every column its rank: the work
+// follows the products and not the columns.
+constexpr int TTOP = (16 * TILE_COLS) / 32 / 32;
+
+template <int BLOCK>
+GM_DEV void region_sync() {
+    if (BLOCK == GM_WAVE)
+        wave_lds_fence();
+    else
+        __syncthreads();
+}
+
+// Exclusive scan over the threads of a region (one wave or the work group).
+template <int BLOCK>
+GM_DEV int32_t region_scan(int32_t x, int32_t *sm, int32_t *total) {
+    if constexpr (BLOCK == GM_WAVE) {
+        const int32_t inc = wave_incl_scan<int32_t>(x);
+        *total = __builtin_amdgcn_readlane(inc, GM_WAVE - 1);
+        return inc - x;
+    } else {
+        return block_excl_scan<BLOCK>(x, sm, total);
+    }
+}
+
+template <int BLOCK, int CAP, bool NUM, typename V>
+struct SmallLds {
+    RankWord top[TTOP];
+    RankWord words[CAP];       // first the parts: (start - first product, column offset)
+    V vals[NUM ? CAP : 1];     // first the parts' scales
+    RankWord ends[CAP / 32];   // last products of the parts; rank: parts that end before the word
+    int32_t scan[BLOCK / GM_WAVE];
+};
+
+// The region's distinct columns (returned). With NUM their sums are left in
+// L.vals in order, and put(rank, column) is called once per distinct column.
+template <int BLOCK, int CAP, bool NUM, typename V, class Put>
+GM_DEV int small_region(const TileArgs<V> &t, const Region &g, SmallLds<BLOCK, CAP, NUM, V> &L, int tid, Put &&put) {
+    constexpr int EPT = CAP / BLOCK, TPT = (TTOP + BLOCK - 1) / BLOCK;
+    const int ntop = g.chunks * (TTOP / 16);
+    for (int q = tid; q < ntop; q += BLOCK) L.top[q].bits = 0u;
+    for (int q = tid; q < CAP / 32; q += BLOCK) L.ends[q].bits = 0u;
+    region_sync<BLOCK>();
+    const uint32_t np = g.q1 - g.q0 < (uint32_t)CAP ? g.q1 - g.q0 : (uint32_t)CAP;  // (parts are not empty)
+    uint32_t n = 0;  // products
+    for (uint32_t j = 0; j < np; j += BLOCK) {
+        const uint32_t q = j + tid;
+        uint32_t len = 0;
+        uint2 sg = make_uint2(0u, 0u);
+        if (q < np) {
+            sg = t.seg[g.q0 + q];
+            len = sg.y & 0xffffu;
+            if (NUM) L.vals[q] = t.ea[t.seg_e[g.q0 + q]];
+        }
+        int32_t tot;
+        const uint32_t off = n + (uint32_t)region_scan<BLOCK>((int32_t)len, L.scan, &tot);
+        if (q < np && off + len <= (uint32_t)CAP) {  // (always: a region of the bin holds at most CAP products)
+            L.words[q] = RankWord{sg.x - off, ((sg.y >> 16) - g.sub0) << TILE_LOG2};
+            __hip_atomic_fetch_or(&L.ends[(off + len - 1) >> 5].bits, 1u << ((off + len - 1) & 31), __ATOMIC_RELAXED,
+                                  __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+        n += (uint32_t)tot;
+    }
+    n = n < (uint32_t)CAP ? n : (uint32_t)CAP;
+    region_sync<BLOCK>();
+    if (tid < GM_WAVE) {  // parts that end before each word of products
+        constexpr int NE = CAP / 32, PER = (NE + GM_WAVE - 1) / GM_WAVE;
+        int32_t cnt = 0;
+        uint32_t b[PER];
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            b[q] = tid * PER + q < NE ? L.ends[tid * PER + q].bits : 0u;
+            cnt += __popc(b[q]);
+        }
+        uint32_t run = (uint32_t)(wave_incl_scan<int32_t>(cnt) - cnt);
+#pragma unroll
+        for (int q = 0; q < PER; ++q) {
+            if (tid * PER + q < NE) L.ends[tid * PER + q].rank = run;
+            run += (uint32_t)__popc(b[q]);
+        }
+    }
+    region_sync<BLOCK>();
+    uint32_t col[EPT], pos[EPT], own[EPT];
+    V val[EPT];
+#pragma unroll
+    for (int k = 0; k < EPT; ++k) {
+        const uint32_t x = tid + k * BLOCK < n ? tid + k * BLOCK : n - 1;
+        own[k] = rank_of(L.ends[x >> 5], x & 31);
+        const RankWord pt = L.words[own[k]];
+        pos[k] = pt.bits + x;
+        col[k] = pt.rank;
+    }
+    uint32_t lc[EPT];
+#pragma unroll
+    for (int k = 0; k < EPT; ++k) {
+        lc[k] = t.col[pos[k]];
+        if (NUM) val[k] = t.val[pos[k]];
+    }
+#pragma unroll
+    for (int k = 0; k < EPT; ++k) {
+        if (NUM) val[k] *= L.vals[own[k]];
+        col[k] += lc[k];
+        if (tid + k * BLOCK < n)
+            __hip_atomic_fetch_or(&L.top[col[k] >> 10].bits, 1u << ((col[k] >> 5) & 31), __ATOMIC_RELAXED,
+                                  __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+    region_sync<BLOCK>();  // (the parts are read)
+    int32_t nwords;
+    {
+        int32_t cnt = 0;
+        uint32_t b[TPT];
+#pragma unroll
+        for (int q = 0; q < TPT; ++q) {
+            b[q] = tid * TPT + q < ntop ? L.top[tid * TPT + q].bits : 0u;
+            cnt += __popc(b[q]);
+        }
+        uint32_t run = (uint32_t)region_scan<BLOCK>(cnt, L.scan, &nwords);
+#pragma unroll
+        for (int q = 0; q < TPT; ++q) {
+            if (tid * TPT + q < ntop) L.top[tid * TPT + q].rank = run;
+            run += (uint32_t)__popc(b[q]);
+        }
+    }
+    for (int q = tid; q < nwords; q += BLOCK) L.words[q].bits = 0u;
+    region_sync<BLOCK>();
+    uint32_t wd[EPT], fresh = 0;
+#pragma unroll
+    for (int k = 0; k < EPT; ++k)
+        if (tid + k * BLOCK < n) {
+            wd[k] = rank_of(L.top[col[k] >> 10], (col[k] >> 5) & 31);
+            const uint32_t bit = 1u << (col[k] & 31);
+            const uint32_t old = __hip_atomic_fetch_or(&L.words[wd[k]].bits, bit, __ATOMIC_RELAXED,
+                                                       __HIP_MEMORY_SCOPE_WORKGROUP);
+            if (!(old & bit)) fresh |= 1u << k;
+        }
+    int32_t total;
+    if constexpr (!NUM) {
+        region_scan<BLOCK>(__popc(fresh), L.scan, &total);
+        return total;
+    }
+    region_sync<BLOCK>();
+    {
+        const int per = (nwords + BLOCK - 1) / BLOCK;  // words per thread (uniform)
+        int32_t cnt = 0;
+        for (int q = 0; q < per; ++q)
+            if (tid * per + q < nwords) cnt += __popc(L.words[tid * per + q].bits);
+        uint32_t run = (uint32_t)region_scan<BLOCK>(cnt, L.scan, &total);
+        for (int q = 0; q < per; ++q)
+            if (tid * per + q < nwords) {
+                L.words[tid * per + q].rank = run;
+                run += (uint32_t)__popc(L.words[tid * per + q].bits);
+            }
+    }
+    for (int q = tid; q < total; q += BLOCK) L.vals[q] = (V)0;
+    region_sync<BLOCK>();
+#pragma unroll
+    for (int k = 0; k < EPT; ++k)
+        if (tid + k * BLOCK < n) {
+            const uint32_t rk = rank_of(L.words[wd[k]], col[k] & 31);
+            __hip_atomic_fetch_add(&L.vals[rk], val[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            if ((fresh >> k) & 1u) put(rk, col[k]);
+        }
+    region_sync<BLOCK>();
+    return total;
+}
+
+// Symbolic of small regions.
+template <int BLOCK, int CAP, int REGS>
+__global__ __launch_bounds__(BLOCK * REGS) void k_tile_sym_small(TileArgs<float> t, uint32_t *nnz, int64_t ncp,
+                                                                 int64_t *slot) {
+    static_assert(REGS == 1 || BLOCK == GM_WAVE, "several regions per work group are one wave each");
+    __shared__ __align__(16) SmallLds<BLOCK, CAP, false, float> L[REGS];
+    const int reg = REGS > 1 ? threadIdx.x / GM_WAVE : 0, tid = REGS > 1 ? threadIdx.x & (GM_WAVE - 1) : threadIdx.x;
+    const int64_t i = blockIdx.x * (int64_t)REGS + reg;
+    if (i >= t.n_items) return;  // the whole wave (one region: the whole work group)
+    const Region g = region_at(t, i);
+    const int n = small_region<BLOCK, CAP, false, float>(t, g, L[reg], tid, [](uint32_t, uint32_t) {});
+    if (tid == 0) {
+        nnz[g.c * t.nh + g.h] = (uint32_t)n;
+        slot[g.h * ncp + g.c] = n;
+    }
+}
+
+// Symbolic, one work group per region; the bitmap is kept for the numeric phase.
+template <int BLOCK>
+__global__ __launch_bounds__(BLOCK) void k_tile_sym(TileArgs<float> t, uint32_t *nnz, int64_t ncp, int64_t *slot) {
+    constexpr int NW = BLOCK / GM_WAVE;
+    __shared__ __align__(16) uint32_t bits[TWORDS];
+    __shared__ __align__(16) uint32_t ends[NW][TENDS];
+    __shared__ LongParts<float> lp;
+    __shared__ int32_t scan[NW];
+    for (int q = threadIdx.x; q < TWORDS; q += BLOCK) bits[q] = 0;
+    if (threadIdx.x == 0) lp.n = 0;
+    const Region g = region_at(t, blockIdx.x);
+    __syncthreads();
+    tile_products<NW, false, float>(t, g, ends[threadIdx.x / GM_WAVE], &lp,
+                                    [&](uint32_t c, float) {
+                                        // (most products of a large region meet a column already marked, and
+                                        // atomics of several lanes on one word take turns)
+                                        if (!(((volatile uint32_t *)bits)[c >> 5] & (1u << (c & 31)))) bit_or(bits, c);
+                                    });
+    __syncthreads();
+    int32_t n = 0;
+    uint32_t *bm = t.bitmap + blockIdx.x * (int64_t)TWORDS;
+    for (int q = threadIdx.x; q < TWORDS; q += BLOCK) {
+        const uint32_t x = bits[q];
+        bm[q] = x;
+        n += __popc(x);
+    }
+    n = block_reduce_sum<BLOCK>(n, scan);
+    if (threadIdx.x == 0) {
+        nnz[g.c * t.nh + g.h] = (uint32_t)n;
+        slot[g.h * ncp + g.c] = n;
+    }
+}
+
+// Where a region's entries of C go.
+template <typename CI, typename V>
+struct TileOut {
+    const int64_t *heavy_rows, *c_row_ptr, *slot;  // slot: exclusive offsets within the row
+    const uint32_t *nnz;
+    int64_t ncp;
+    CI *c_col;
+    V *c_val;
+    int32_t *err;
+    GM_DEV int want(const Region &g, int64_t nh) const { return (int)nnz[g.c * nh + g.h]; }
+    GM_DEV int64_t dst(const Region &g) const { return c_row_ptr[heavy_rows[g.h]] + slot[g.h * ncp + g.c]; }
+    GM_DEV CI base(const Region &g) const { return (CI)g.c << TILE_LOG2; }
+};
+
+// Numeric of small regions.
+template <int BLOCK, int CAP, int REGS, typename CI, typename V>
+__global__ __launch_bounds__(BLOCK * REGS) void k_tile_num_small(TileArgs<V> t, TileOut<CI, V> o) {
+    static_assert(REGS == 1 || BLOCK == GM_WAVE, "several regions per work group are one wave each");
+    __shared__ __align__(16) SmallLds<BLOCK, CAP, true, V> L_all[REGS];
+    const int reg = REGS > 1 ? threadIdx.x / GM_WAVE : 0, tid = REGS > 1 ? threadIdx.x & (GM_WAVE - 1) : threadIdx.x;
+    const int64_t i = blockIdx.x * (int64_t)REGS + reg;
+    if (i >= t.n_items) return;  // the whole wave (one region: the whole work group)
+    const Region g = region_at(t, i);
+    SmallLds<BLOCK, CAP, true, V> &L = L_all[reg];
+    const int want = o.want(g, t.nh);
+    const int64_t dst = o.dst(g);
+    const CI cb = o.base(g);
+    const int total = small_region<BLOCK, CAP, true, V>(t, g, L, tid, [&](uint32_t rk, uint32_t c) {
+        if ((int)rk < want) o.c_col[dst + rk] = cb + (CI)c;
+    });
+    if (tid == 0 && total != want) atomicOr(o.err, 4);
+    const int m = total < want ? total : want;
+    for (int q = tid; q < m; q += BLOCK) o.c_val[dst + q] = L.vals[q];
+}
+
+// Adds v at its column's rank.
+template <int CAP, typename V>
+GM_DEV void rank_add(const RankWord *words, V *vals, uint32_t col, V v) {
+    const uint32_t rk = rank_of(words[col >> 5], col & 31);
+    if (rk < (uint32_t)CAP) __hip_atomic_fetch_add(&vals[rk], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// cols[rank] = column for the present columns of words [w0, w0 + n)
+template <int CAP>
+GM_DEV void rank_columns(const RankWord *words, uint16_t *cols, int w0, int n) {
+    for (int wd = w0; wd < w0 + n; ++wd) {
+        const RankWord x = words[wd];
+        uint32_t b = x.bits, rk = x.rank;
+        while (b) {
+            if (rk < (uint32_t)CAP) cols[rk] = (uint16_t)(wd * 32 + __ffs((int)b) - 1);
+            b &= b - 1;
+            ++rk;
+        }
+    }
+}
+
+// Numeric of larger regions of at most CAP distinct columns: the ranks come
+// from the bitmap the symbolic phase kept, so the products are read once.
+// (Regions of more columns than CAP are left to the dense kernel.)
+template <int BLOCK, int CAP, typename CI, typename V>
+__global__ __launch_bounds__(BLOCK) void k_tile_num_rank(TileArgs<V> t, TileOut<CI, V> o) {
+    constexpr int NW = BLOCK / GM_WAVE;
+    __shared__ __align__(16) RankWord words[TWORDS];
+    __shared__ __align__(16) V vals[CAP];
+    __shared__ __align__(16) uint32_t ends[NW][TENDS];
+    __shared__ LongParts<V> lp;
+    __shared__ int32_t scan[NW];
+    const int tid = threadIdx.x;
+    const Region g = region_at(t, blockIdx.x);
+    const int want = o.want(g, t.nh);
+    if (want > CAP) return;  // uniform
+    const uint32_t bw = tid < TWORDS ? t.bitmap[blockIdx.x * (int64_t)TWORDS + tid] : 0u;
+    for (int q = tid; q < want; q += BLOCK) vals[q] = (V)0;
+    if (tid == 0) lp.n = 0;
+    static_assert(BLOCK >= TWORDS, "one bitmap word per thread");
+    int32_t total;
+    const int32_t rank = block_excl_scan<BLOCK>((int32_t)__popc(bw), scan, &total);
+    if (tid < TWORDS) words[tid] = RankWord{bw, (uint32_t)rank};
+    __syncthreads();
+    tile_products<NW, true, V>(t, g, ends[tid / GM_WAVE], &lp,
+                               [&](uint32_t c, V v) { rank_add<CAP>(words, vals, c, v); });
+    __syncthreads();
+    if (tid == 0 && total != want) atomicOr(o.err, 4);
+    const int m = total < want ? total : want;
+    const CI cb = o.base(g);
+    const int64_t dst = o.dst(g);
+    for (int q = tid; q < m; q += BLOCK) o.c_val[dst + q] = vals[q];
+    __syncthreads();  // the values' place is reused for the columns
+    uint16_t *cols = (uint16_t *)vals;
+    if (tid < TWORDS) rank_columns<CAP>(words, cols, tid, 1);
+    __syncthreads();
+    for (int q = tid; q < m; q += BLOCK) o.c_col[dst + q] = cb + (CI)cols[q];
+}
+
+// Numeric of regions of more than MIN distinct columns: one value per column
+// of the chunk.
+template <int BLOCK, int MIN, typename CI, typename V>
+__global__ __launch_bounds__(BLOCK) void k_tile_num_dense(TileArgs<V> t, TileOut<CI, V> o) {
+    constexpr int NW = BLOCK / GM_WAVE;
+    constexpr int SPAN = TILE_COLS / NW;  // columns a wave writes out
+    __shared__ __align__(16) V vals[TILE_COLS];
+    __shared__ __align__(16) uint32_t bits[TWORDS];
+    __shared__ __align__(16) uint32_t ends[NW][TENDS];
+    __shared__ LongParts<V> lp;
+    __shared__ int32_t scan[NW];
+    const int tid = threadIdx.x, lane = tid & (GM_WAVE - 1), w = tid / GM_WAVE;
+    const Region g = region_at(t, blockIdx.x);
+    const int want = o.want(g, t.nh);
+    if (want <= MIN) return;  // uniform
+    static_assert(BLOCK >= TWORDS, "one bitmap word per thread");
+    if (tid < TWORDS) bits[tid] = t.bitmap[blockIdx.x * (int64_t)TWORDS + tid];
+    for (int q = tid; q < TILE_COLS; q += BLOCK) vals[q] = (V)0;
+    if (tid == 0) lp.n = 0;
+    __syncthreads();
+    tile_products<NW, true, V>(t, g, ends[w], &lp, [&](uint32_t c, V v) {
+        __hip_atomic_fetch_add(&vals[c], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    });
+    __syncthreads();
+    // present columns in order: wave w owns columns [w * SPAN, w * SPAN + SPAN)
+    static_assert(SPAN % GM_WAVE == 0 && SPAN / 32 <= GM_WAVE, "a wave's columns in whole ballots");
+    int32_t cnt = lane < SPAN / 32 ? __popc(bits[w * (SPAN / 32) + lane]) : 0;
+    cnt = wave_reduce_sum<int32_t>(cnt);
+    int32_t total;
+    int32_t at = block_excl_scan<BLOCK>(lane == 0 ? cnt : 0, scan, &total);
+    at = __builtin_amdgcn_readfirstlane(at);
+    if (tid == 0 && total != want) atomicOr(o.err, 2);
+    const CI cb = o.base(g);
+    const int64_t dst = o.dst(g);
+    for (int x0 = 0; x0 < SPAN; x0 += GM_WAVE) {
+        const int x = w * SPAN + x0 + lane;
+        const bool p = (bits[x >> 5] >> (x & 31)) & 1u;
+        const uint64_t m = ballot(p);
+        const int pos = at + __popcll(m & lanemask_lt());
+        if (p && pos < want) {
+            o.c_col[dst + pos] = cb + (CI)x;
+            o.c_val[dst + pos] = vals[x];
+        }
+        at += __popcll(m);
+    }
+}
+
+template <class K, class... Args>
+void launch_regions(K kernel, int block, int64_t groups, hipStream_t s, Args... args) {
+    if (groups <= 0) return;
+    GM_REQUIRE(groups < (int64_t)1 << 31, GMAGNUS_ERROR_UNSUPPORTED, "too many regions for one launch");
+    hipLaunchKernelGGL(kernel, dim3((unsigned)groups), dim3(block), 0, s, args...);
+    GM_CHECK_LAUNCH();
+}
+
+template <typename V>
+TileArgs<V> tile_args(const TileHeavy &t, int bin, int64_t *n) {
+    const int64_t b0 = t.bins[bin];
+    *n = t.bins[bin + 1] - b0;
+    uint32_t *bm = bin <= TILE_M ? t.bitmap + (b0 - t.bins[TILE_D_BIG]) * TWORDS : nullptr;
+    return TileArgs<V>{t.col, static_cast<const V *>(t.val), t.seg, t.seg_e, t.seg_end, static_cast<const V *>(t.ea),
+                       t.nh, t.slog, t.grp, t.items + b0, *n, bm};
+}
+
+void scan_u32(uint32_t *a, int64_t n, uint32_t *scratch, hipStream_t s) {
+    const int64_t tiles = (n + SC_TILE - 1) / SC_TILE;
+    hipLaunchKernelGGL(k_tile_scan_sums, dim3((unsigned)tiles), dim3(SC_BLOCK), 0, s, a, n, scratch);
+    GM_CHECK_LAUNCH();
+    hipLaunchKernelGGL(k_tile_scan_mid, dim3(1), dim3(1024), 0, s, scratch, tiles);
+    GM_CHECK_LAUNCH();
+    hipLaunchKernelGGL(k_tile_scan_apply, dim3((unsigned)tiles), dim3(SC_BLOCK), 0, s, a, n, scratch);
+    GM_CHECK_LAUNCH();
+}
+
+}  // namespace
+
+int tile_chunks(int64_t c_m) { return (int)std::min<int64_t>((c_m + TILE_COLS - 1) / TILE_COLS, 1 << 20); }
+
+void tile_parts(const Csr &B, const int32_t *slice_k, const TileHeavy &t, uint32_t *cm, hipStream_t s) {
+    if (t.ns <= 0) return;
+    with_index_type(B.ci64, [&](auto ci) {
+        using CI = decltype(ci);
+        hipLaunchKernelGGL(k_tile_row_counts<CI>, dim3(grid_for(t.ns, TR_WAVES, 65536)), dim3(TR_WAVES * GM_WAVE),
+                           TR_WAVES * (t.nc + 1) * sizeof(uint32_t), s, typed<CI, NoV>(B), slice_k, t.ns, t.nc, t.cnt);
+        GM_CHECK_LAUNCH();
+    });
+    // starts of the parts: the counts chunk-major, scanned, back beside the slices
+    const int64_t tiles = ((t.ns + TT - 1) / TT) * ((t.nc + TT - 1) / TT);
+    GM_REQUIRE(tiles < (int64_t)1 << 31, GMAGNUS_ERROR_UNSUPPORTED, "too many slices");
+    hipLaunchKernelGGL(k_tile_transpose<uint16_t>, dim3((unsigned)tiles), dim3(256), 0, s, t.cnt, t.ns, (int64_t)t.nc, cm);
+    GM_CHECK_LAUNCH();
+    scan_u32(cm, t.ns * t.nc, t.scan, s);
+    hipLaunchKernelGGL(k_tile_transpose<uint32_t>, dim3((unsigned)tiles), dim3(256), 0, s, cm, (int64_t)t.nc, t.ns, t.part);
+    GM_CHECK_LAUNCH();
+}
+
+int64_t tile_scan_words(int64_t n) { return (n + SC_TILE - 1) / SC_TILE + 1; }
+
+void tile_fill(const Csr &B, const int32_t *slice_k, const TileHeavy &t, int32_t *long_list, hipStream_t s) {
+    if (t.ns <= 0) return;
+    fill<int32_t>(long_list, 0, 1, s);
+    with_types(B, [&](auto ci, auto v) {
+        using CI = decltype(ci);
+        using V = decltype(v);
+        V *ov = static_cast<V *>(t.val);
+        hipLaunchKernelGGL((k_tile_fill<CI, V>), dim3(grid_for(t.ns, TF_WAVES, 65536)), dim3(TF_WAVES * GM_WAVE), 0, s,
+                           typed<CI, V>(B), slice_k, t.ns, t.nc, t.part, t.n_elems, t.col, ov, long_list, long_list + 1);
+        GM_CHECK_LAUNCH();
+        hipLaunchKernelGGL((k_tile_fill_long<CI, V>), dim3(8, 512), dim3(TF_WAVES * GM_WAVE), 0, s, typed<CI, V>(B),
+                           slice_k, t.ns, t.nc, t.part, t.n_elems, t.col, ov, long_list, long_list + 1);
+        GM_CHECK_LAUNCH();
+    });
+}
+
+void tile_entries(const Csr &A, const int64_t *heavy_rows, int64_t r0, const int32_t *k_to_slice, const TileHeavy &t,
+                  hipStream_t s) {
+    if (t.n_ent <= 0) return;
+    with_types(A, [&](auto ci, auto v) {
+        using CI = decltype(ci);
+        using V = decltype(v);
+        hipLaunchKernelGGL((k_tile_entries<CI, V>), dim3(grid_for(t.n_ent, 256, 65536)), dim3(256), 0, s,
+                           typed<CI, V>(A), heavy_rows, t.nh, r0, t.a_ptr, t.n_ent, k_to_slice, t.es, t.eh,
+                           static_cast<V *>(t.ea));
+        GM_CHECK_LAUNCH();
+    });
+}
+
+void tile_regions(const TileHeavy &t, unsigned long long *size, uint8_t *cls, int64_t *n_seg, hipStream_t s) {
+    const int64_t n = t.nh * t.ncp;
+    fill<unsigned long long>(size, 0ull, n, s);
+    const int ncb = (int)std::min<int64_t>(ceil_pow2(t.nc), TE_BLOCK);
+    hipLaunchKernelGGL(k_tile_sizes, dim3((unsigned)((t.n_ent + TE_BLOCK - 1) / TE_BLOCK), (unsigned)((t.nc + ncb - 1) / ncb)),
+                       dim3(TE_BLOCK), 0, s, t.es, t.eh, t.n_ent, t.cnt, t.nc, ncb, t.nh, t.slog, size);
+    GM_CHECK_LAUNCH();
+    auto classes = [&](auto S) {
+        hipLaunchKernelGGL(k_tile_classes<decltype(S)::value>, dim3(grid_for(n / decltype(S)::value, 256, 65536)), dim3(256),
+                           0, s, size, t.nh, n, cls, t.grp, t.seg_end);
+        GM_CHECK_LAUNCH();
+    };
+    switch (t.slog) {
+    case 0: classes(std::integral_constant<int, 1>()); break;
+    case 1: classes(std::integral_constant<int, 2>()); break;
+    case 2: classes(std::integral_constant<int, 4>()); break;
+    case 3: classes(std::integral_constant<int, 8>()); break;
+    default: classes(std::integral_constant<int, 16>()); break;
+    }
+    scan_u32(t.seg_end, n, t.scan, s);
+    hipLaunchKernelGGL(k_tile_total, dim3(1), dim3(1), 0, s, t.seg_end + n, n_seg);
+    GM_CHECK_LAUNCH();
+}
+
+void tile_segments(const TileHeavy &t, hipStream_t s) {
+    hipLaunchKernelGGL(k_tile_lists, dim3((unsigned)((t.n_ent + GM_WAVE - 1) / GM_WAVE), (unsigned)((t.nc + TL_C - 1) / TL_C)),
+                       dim3(TL_BLOCK), 0, s, t.es, t.eh, t.n_ent, t.cnt, t.part, t.nc, t.nh, t.slog, t.seg_end, t.seg,
+                       t.seg_e);
+    GM_CHECK_LAUNCH();
+}
+
+void tile_symbolic(const TileHeavy &t, int bin, int64_t *slot, hipStream_t s) {
+    int64_t n;
+    const TileArgs<float> a = tile_args<float>(t, bin, &n);
+    if (n <= 0) return;
+    switch (bin) {
+    case TILE_T:
+        launch_regions(k_tile_sym_small<64, TILE_T_MAX, 4>, 256, (n + 3) / 4, s, a, t.nnz, t.ncp, slot);
+        break;
+    case TILE_S: launch_regions(k_tile_sym_small<256, TILE_S_MAX, 1>, 256, n, s, a, t.nnz, t.ncp, slot); break;
+    case TILE_L: launch_regions(k_tile_sym_small<512, TILE_MERGE, 1>, 512, n, s, a, t.nnz, t.ncp, slot); break;
+    case TILE_M: launch_regions(k_tile_sym<256>, 256, n, s, a, t.nnz, t.ncp, slot); break;
+    case TILE_D: launch_regions(k_tile_sym<512>, 512, n, s, a, t.nnz, t.ncp, slot); break;
+    case TILE_D_BIG: launch_regions(k_tile_sym<1024>, 1024, n, s, a, t.nnz, t.ncp, slot); break;
+    default: break;
+    }
+}
+
+void tile_numeric(const TileHeavy &t, int bin, const int64_t *heavy_rows, const int64_t *c_row_ptr,
+                  const int64_t *slot, bool ci64, bool v32, void *c_col, void *c_val, int32_t *err, hipStream_t s) {
+    with_types(ci64, v32, [&](auto ci, auto v) {
+        using CI = decltype(ci);
+        using V = decltype(v);
+        int64_t n;
+        const TileArgs<V> a = tile_args<V>(t, bin, &n);
+        if (n <= 0) return;
+        const TileOut<CI, V> o{heavy_rows, c_row_ptr, slot, t.nnz, t.ncp, static_cast<CI *>(c_col),
+                               static_cast<V *>(c_val), err};
+        switch (bin) {
+        case TILE_T:
+            launch_regions(k_tile_num_small<64, TILE_T_MAX, 4, CI, V>, 256, (n + 3) / 4, s, a, o);
+            break;
+        case TILE_S: launch_regions(k_tile_num_small<256, TILE_S_MAX, 1, CI, V>, 256, n, s, a, o); break;
+        case TILE_L: launch_regions(k_tile_num_small<512, TILE_MERGE, 1, CI, V>, 512, n, s, a, o); break;
+        case TILE_M: launch_regions(k_tile_num_rank<512, TILE_M_MAX, CI, V>, 512, n, s, a, o); break;
+        case TILE_D:
+        case TILE_D_BIG:
+            launch_regions(k_tile_num_dense<1024, TILE_RANK_MAX, CI, V>, 1024, n, s, a, o);
+            launch_regions(k_tile_num_rank<1024, TILE_RANK_MAX, CI, V>, 1024, n, s, a, o);
+            break;
+        default: break;
+        }
+    });
+}
+
+}  // namespace gm

@@ -1,0 +1,100 @@
+"""Heavy rows accumulated from the chunk-major copy of B (the default path of
+rows of more than 3456 products when a row's entries meet a chunk of 2^14
+columns with one product or more on average), at the sizes where it can go
+wrong: column counts around whole chunks and whole groups of 16 chunks, every
+region size (one wave up to the dense accumulator), parts long enough to be
+shared by a work group's waves (and more of them than the shared list holds),
+B rows copied in pieces, all type pairs, new values on kept patterns. Every
+entry against the oracle, and the structure against the level-by-level order."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads as wl
+from tests.parity import compare_full
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def g():
+    from paper_2607_22866_amd import gmagnus
+
+    gmagnus.load()
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    return gmagnus
+
+
+def _product(g, A, B, it=torch.int32, vt=torch.float64, **opts):
+    dA, dB = (g.DeviceCSR.from_host(m, index_dtype=it, value_dtype=vt) for m in (A, B))
+    with g.Plan(dA, dB, **opts) as p:
+        rp, _ = p.symbolic()
+        col, val = p.numeric()
+        info = p.info()
+    torch.cuda.synchronize()
+    assert info.check_flags == 0 and info.n_heavy_rows > 0
+    return rp.cpu().numpy(), col.cpu().numpy(), val.cpu().numpy()
+
+
+# (A rows, inner size, columns, A entries per row, B entries per row)
+SIZES = [
+    (9, 300, 16383, 40, 200),     # one chunk, not full
+    (9, 300, 16384, 40, 200),     # exactly one chunk
+    (9, 300, 16385, 40, 200),     # one column in a second chunk
+    (5, 40, 300, 30, 290),        # fewer columns than a wave's words
+    (6, 300, 3 * 16384 + 5, 250, 40),      # regions of about 3300 products
+    (4, 400, 40000, 200, 900),    # dense: over 7168 distinct columns a chunk
+    (3, 300, 32768, 280, 1000),   # more long parts than the shared list holds
+    (3, 50, 70000, 6, 20000),     # B rows copied in pieces, parts of thousands
+    (8, 4000, 16 * 16384, 300, 20),        # one whole group of 16 chunks
+    (8, 4000, 16 * 16384 + 1, 300, 20),    # and one column past it
+    (8, 4000, 37 * 16384 - 3, 300, 40),    # several groups, merged regions
+    (12, 500, 17 * 16384, 60, 100),        # about 350 products a region group
+]
+
+
+@pytest.mark.parametrize("m,k,n,a_d,b_d", SIZES)
+def test_sizes(g, m, k, n, a_d, b_d):
+    A, B = wl.erdos_renyi(m, k, a_d, 11), wl.erdos_renyi(k, n, b_d, 12)
+    ref = oracle.spgemm(A, B)
+    rp, col, val = _product(g, A, B)
+    compare_full(rp, col, val, ref)
+    rp2, col2, _ = _product(g, A, B, flags=g.FLAG_LEVEL_BY_LEVEL)
+    assert np.array_equal(rp, rp2) and np.array_equal(col, col2)
+
+
+@pytest.mark.parametrize("it,vt", [(torch.int32, torch.float32), (torch.int64, torch.float64),
+                                   (torch.int64, torch.float32)])
+@pytest.mark.parametrize("m,k,n,a_d,b_d", [SIZES[5], SIZES[6], SIZES[10]])
+def test_types(g, it, vt, m, k, n, a_d, b_d):
+    if it == torch.int32 and vt == torch.float32:
+        n = min(n, 1 << 18)  # (fp32 values with int32 columns: one multisplit level at most)
+    A, B = wl.erdos_renyi(m, k, a_d, 21), wl.erdos_renyi(k, n, b_d, 22)
+    f32 = vt == torch.float32
+    if f32:
+        A, B = (x.with_values(x.val.astype(np.float32).astype(np.float64)) for x in (A, B))
+    compare_full(*_product(g, A, B, it, vt), oracle.spgemm(A, B), f32=f32)
+
+
+@pytest.mark.parametrize("seed,skew", [(5, (0.57, 0.19, 0.19)), (6, (0.7, 0.12, 0.12))])
+def test_rmat_panel_and_new_values(g, seed, skew):
+    # R-MAT rows (a few entries hold most products) over 8 chunks, empty B
+    # rows among them; a row panel, then new values on the kept pattern
+    A = wl.rmat(17, 2, *skew, seed)
+    ip = oracle.row_products(A, A)
+    r1 = int(np.searchsorted(np.cumsum(ip), 3_000_000)) + 1
+    dA = g.DeviceCSR.from_host(A)
+    rng = np.random.default_rng(seed)
+    A2 = A.with_values(rng.uniform(-1.0, 1.0, A.nnz))
+    with g.Plan(dA, dA, row_end=r1, flags=g.FLAG_KEEP_PATTERN | g.FLAG_CONCURRENT_STREAMS) as p:
+        rp, _ = p.symbolic()
+        for X in (A, A2):
+            if X is A2:
+                p.update_values(torch.from_numpy(A2.val).cuda())
+            col, val = p.numeric()
+            assert p.info().check_flags == 0 and p.info().n_heavy_rows > 0
+            compare_full(rp.cpu().numpy(), col.cpu().numpy(), val.cpu().numpy(),
+                         oracle.spgemm(X, X, rows=np.arange(r1)))
