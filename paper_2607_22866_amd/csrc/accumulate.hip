@@ -1,8 +1,8 @@
 // Accumulation (Section III-E): symbolic (distinct-column counts) and
 // numeric (sorted rows of C) for
 //   * light rows of C -- Gustavson (Section II-B, Algorithm 1) with an LDS
-//     hash map (modulo hashing, linear probing, load factor <= 1/2) or, when
-//     the row's column span is small, an LDS dense window;
+//     dense window when the row's column span is small, else summed by rank
+//     (rank.hpp; small rows are counted with an LDS hash table);
 //   * final chunks of the heavy rows ("leaves" of the multisplit) -- the
 //     chunk's (column, value) pairs are accumulated with the hash map when the
 //     chunk is light and with an LDS dense accumulator plus bitmap when it is
@@ -14,6 +14,7 @@
 // Work is binned by size (OpSparse-style, Section III-E): one work group per
 // row or chunk, with the work-group size and LDS table chosen per bin.
 #include "host.hpp"
+#include "rank.hpp"
 
 namespace gm {
 
@@ -325,26 +326,23 @@ GM_DEV int hash_bin_sym(int64_t n) {
 GM_DEV int hash_bin_num(int64_t nnz) {
     return nnz <= HN_CAP[0] ? 0 : nnz <= HN_CAP[1] ? 1 : nnz <= HN_CAP[2] ? 2 : 3;
 }
-// Numeric light rows: few distinct columns hash (table of HN_CAP[0]); rows of
-// at most SORT_SMALL[1] products sort them in one wave (with LDS sized for
-// SORT_SMALL[0] or SORT_SMALL[1] products, so the smaller rows fit more work
-// groups per CU); then hashing for rows with at most HN_CAP[1] distinct
-// columns; larger rows sort all products (by product count, SORT_CAP).
-// Sorting a few hundred products in LDS (one or three 8-bit passes) costs far
-// less LDS traffic than the bitonic sort of the hash table's occupied slots.
-constexpr int SORT_SMALL[2] = {256, 512};
-// (the middle cap keeps two 256-thread work groups per CU; the largest
-// needs almost all of a CU's LDS)
-constexpr int SORT_CAP[3] = {2048, 3456, 6912};
-GM_DEV int light_bin_num(int64_t nnz, int64_t ip) {
-    return nnz <= HN_CAP[0]        ? 0
-           : ip <= SORT_SMALL[0]   ? 1
-           : ip <= SORT_SMALL[1]   ? 2
-           : nnz <= HN_CAP[1]      ? 3
-           : ip <= SORT_CAP[0]     ? 4
-           : ip <= SORT_CAP[1]     ? 5
-                                   : 6;
-}
+constexpr int TAU_MAX = 6912;    // products of a light chunk at most
+constexpr int LIGHT_MAX = 3456;  // products of a light row at most
+
+// Bins of the light rows outside a window, by products: one wave (4 or 8
+// products a lane) up to 512, then work groups of 4 products a thread. The
+// numeric phase sums by rank (rank.hpp), the symbolic phase counts by rank
+// above 512 products and with a hash table up to there. Against the LSD radix
+// sort, the hash table with a bitonic sort and the hash counts that these rows
+// took before (ms, one MI355X): 16 x 16 products a row over 2^22 columns
+// numeric 10.4 -> 8.9; 40 x 40 over 250007 columns (64-bit) numeric 7.8 -> 3.8,
+// symbolic 1.55 -> 1.20; 27-point stencil numeric 4.2 -> 2.9, symbolic 2.0 ->
+// 1.8; 6 x 9 products a row numeric 0.63 -> 0.26. Counting by rank up to 512
+// products lost to the hash table: 5.8 against 3.5 for 256 products over 2^22
+// columns (three levels of words), 0.19 against 0.17 for 54.
+constexpr int RB_CAP[5] = {256, 512, 1024, 2048, 3584};
+static_assert(RB_CAP[4] >= LIGHT_MAX, "the largest bin holds every light row");
+GM_DEV int rank_bin(int64_t p) { return p <= RB_CAP[0] ? 0 : p <= RB_CAP[1] ? 1 : p <= RB_CAP[2] ? 2 : p <= RB_CAP[3] ? 3 : 4; }
 
 // Window choice for a light row: span = max column - min column + 1.
 GM_DEV int window_bin(int64_t ip, int64_t span, bool window) {
@@ -361,8 +359,8 @@ GM_DEV int window_bin(int64_t ip, int64_t span, bool window) {
 // cannot be keyed by 32-bit column offsets: it goes to the heavy path,
 // whose chunks are at most 2^31 columns wide.
 template <typename CI>
-__global__ void k_light_classes(const int64_t *ip, const int64_t *row_nnz, const CI *minc, const CI *maxc, int64_t n,
-                                int64_t tau, int window, uint8_t *cls) {
+__global__ void k_light_classes(const int64_t *ip, const CI *minc, const CI *maxc, int64_t n, int64_t tau, int window,
+                                uint8_t *cls) {
     for (int64_t r = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; r < n; r += (int64_t)gridDim.x * blockDim.x) {
         const int64_t p = ip[r];
         uint8_t c;
@@ -375,7 +373,7 @@ __global__ void k_light_classes(const int64_t *ip, const int64_t *row_nnz, const
             if (wb >= 0)
                 c = (uint8_t)(LIGHT_W0 + wb);
             else
-                c = (uint8_t)(LIGHT_H0 + (row_nnz ? light_bin_num(row_nnz[r], p) : hash_bin_sym(p)));
+                c = (uint8_t)(LIGHT_R0 + rank_bin(p));
         }
         cls[r] = c;
     }
@@ -442,46 +440,126 @@ GM_DEV CI light_base(const CI *minc, int64_t r) {
     return sizeof(CI) == 8 ? minc[r] : (CI)0;
 }
 
-template <int BLOCK, int TS, typename CI>
-__global__ __launch_bounds__(BLOCK) void k_light_hash_sym(CsrV<CI, NoV> A, CsrV<CI, NoV> B, int64_t r0,
-                                                          const int64_t *items, const CI *minc, int64_t *row_nnz) {
-    __shared__ int32_t keys[TS];
-    __shared__ GusLds<BLOCK, NoV> G;
+// Counts the distinct columns of a small row, one wave per row: the table
+// takes the smallest power of two of at least four slots a product (16 x 16
+// products a row over 2^22 columns: 3.5 ms with four slots, 4.7 with two).
+template <int TS, typename CI>
+__global__ __launch_bounds__(GM_WAVE) void k_light_hash_sym(CsrV<CI, NoV> A, CsrV<CI, NoV> B, int64_t r0,
+                                                            const int64_t *items, const int64_t *ip, const CI *minc,
+                                                            int64_t *row_nnz) {
+    __shared__ __align__(16) int32_t keys[TS];
+    __shared__ GusLds<GM_WAVE, NoV> G;
     __shared__ int32_t counter;
     const int64_t r = items[blockIdx.x];
-    hash_clear<BLOCK, TS, double>(keys, nullptr);
+    const int p = (int)ip[r];
+    const int lg = 32 - __clz(4 * p - 1) > 6 ? 32 - __clz(4 * p - 1) : 6;
+    const int shift = 32 - (1 << lg <= TS ? lg : __builtin_ctz(TS)), mask = (1 << (32 - shift)) - 1;
+    for (int i = threadIdx.x * 4; i <= mask; i += GM_WAVE * 4) *(int4 *)&keys[i] = make_int4(-1, -1, -1, -1);
     if (threadIdx.x == 0) counter = 0;
     __syncthreads();
-    gustavson_row<BLOCK, false>(A, B, A.rp[r0 + r], A.rp[r0 + r + 1], light_base(minc, r), G,
-                                [&](int32_t c, NoV) { hash_insert_key<TS>(keys, c, &counter); });
+    gustavson_row<GM_WAVE, false>(A, B, A.rp[r0 + r], A.rp[r0 + r + 1], light_base(minc, r), G, [&](int32_t c, NoV) {
+        uint32_t h = ((uint32_t)c * 0x9E3779B1u) >> shift;
+        for (int probe = 0; probe <= mask; ++probe) {  // (as hash_insert_key)
+            int32_t old = ((volatile int32_t *)keys)[h];
+            if (old == -1) {
+                old = atomicCAS(&keys[h], -1, c);
+                if (old == -1) {
+                    atomicAdd(&counter, 1);
+                    return;
+                }
+            }
+            if (old == c) return;
+            h = (h + 1) & mask;
+        }
+    });
     if (threadIdx.x == 0) row_nnz[r] = counter;
 }
 
-template <int BLOCK, int TS, typename CI, typename V>
-__global__ __launch_bounds__(BLOCK) void k_light_hash_num(CsrV<CI, V> A, CsrV<CI, V> B, int64_t r0,
-                                                          const int64_t *items, const CI *minc,
-                                                          const int64_t *c_row_ptr, CI *c_col, V *c_val,
-                                                          int32_t *err) {
-    __shared__ int32_t keys[TS];
-    __shared__ V vals[TS];
-    __shared__ GusLds<BLOCK, V> G;
-    const int64_t r = items[blockIdx.x];
-    const CI base = light_base(minc, r);
-    hash_clear<BLOCK, TS>(keys, vals);
-    __syncthreads();
-    gustavson_row<BLOCK, true>(A, B, A.rp[r0 + r], A.rp[r0 + r + 1], base, G,
-                               [&](int32_t c, V v) { hash_insert_add<TS>(keys, vals, c, v); });
-    const int64_t dst = c_row_ptr[r];
-    hash_emit_sorted<BLOCK, TS>(keys, vals, c_row_ptr[r + 1] - dst, base, c_col + dst, c_val + dst, G.scan, err);
+// ---------------------------------------------------- light rows by rank
+// The parts of a light row are its A entries' B rows; columns are taken
+// relative to the row's smallest one.
+template <typename CI, typename V>
+struct RowParts {
+    typedef int64_t Pos;
+    typedef CI Col;
+    const CsrV<CI, V> &A, &B;
+    int64_t j0, j1;
+    CI base;
+    GM_DEV int64_t np() const { return j1 - j0; }
+    GM_DEV uint32_t part(int64_t q, int64_t *st, uint32_t *) const {
+        const int64_t k = (int64_t)A.ci[j0 + q];
+        *st = B.rp[k];
+        return (uint32_t)(B.rp[k + 1] - *st);
+    }
+    GM_DEV V scale(int64_t q) const { return A.v[j0 + q]; }
+    GM_DEV RankWord pack(int64_t st, uint32_t off, uint32_t) const {
+        const uint64_t p = (uint64_t)(st - off);
+        return RankWord{(uint32_t)p, (uint32_t)(p >> 32)};
+    }
+    GM_DEV Pos at(const RankWord &p, uint32_t x, uint32_t *col) const {
+        *col = 0;
+        return (int64_t)((uint64_t)p.bits | (uint64_t)p.rank << 32) + x;
+    }
+    GM_DEV Col col(Pos p) const { return B.ci[p]; }
+    GM_DEV V val(Pos p) const { return B.v[p]; }
+    GM_DEV uint32_t local(Col c) const { return (uint32_t)(c - base); }
+};
+
+template <int BLOCK, int CAP, int REGS, typename CI>
+__global__ __launch_bounds__(BLOCK *REGS) void k_light_rank_sym(CsrV<CI, NoV> A, CsrV<CI, NoV> B, int64_t r0,
+                                                                const int64_t *items, int64_t n, const CI *minc,
+                                                                const CI *maxc, int64_t *row_nnz) {
+    static_assert(REGS == 1 || BLOCK == GM_WAVE, "several rows per work group are one wave each");
+    __shared__ __align__(16) RankLds<BLOCK, CAP, false, float> L[REGS];
+    const int reg = REGS > 1 ? threadIdx.x / GM_WAVE : 0, tid = REGS > 1 ? threadIdx.x & (GM_WAVE - 1) : threadIdx.x;
+    const int64_t i = blockIdx.x * (int64_t)REGS + reg;
+    if (i >= n) return;  // the whole wave (one row: the whole work group)
+    const int64_t r = items[i];
+    const CI base = minc[r];
+    const RowParts<CI, NoV> src{A, B, A.rp[r0 + r], A.rp[r0 + r + 1], base};
+    const uint32_t cnt = rank_region<BLOCK, CAP, false, float>(src, (uint32_t)(maxc[r] - base) + 1u, L[reg], tid,
+                                                               [](uint32_t, uint32_t) {});
+    if (tid == 0) row_nnz[r] = cnt;
 }
 
-// ------------------------------------------------ sort-based light rows
-// Light rows with many distinct columns (their products barely repeat a
-// column): every product is placed in LDS as (column - row minimum, value),
-// the columns are sorted with a stable LSD radix sort carrying the product
-// index, and runs of equal columns are summed into the row. This replaces a
-// hash table plus a bitonic sort of the whole table, whose many
-// barrier-separated stages dominated these rows.
+template <int BLOCK, int CAP, int REGS, typename CI, typename V>
+__global__ __launch_bounds__(BLOCK *REGS) void k_light_rank_num(CsrV<CI, V> A, CsrV<CI, V> B, int64_t r0,
+                                                                const int64_t *items, int64_t n, const CI *minc,
+                                                                const CI *maxc, const int64_t *c_row_ptr, CI *c_col,
+                                                                V *c_val, int32_t *err) {
+    static_assert(REGS == 1 || BLOCK == GM_WAVE, "several rows per work group are one wave each");
+    __shared__ __align__(16) RankLds<BLOCK, CAP, true, V> L_all[REGS];
+    const int reg = REGS > 1 ? threadIdx.x / GM_WAVE : 0, tid = REGS > 1 ? threadIdx.x & (GM_WAVE - 1) : threadIdx.x;
+    const int64_t i = blockIdx.x * (int64_t)REGS + reg;
+    if (i >= n) return;  // the whole wave (one row: the whole work group)
+    RankLds<BLOCK, CAP, true, V> &L = L_all[reg];
+    const int64_t r = items[i];
+    const CI base = minc[r];
+    const RowParts<CI, V> src{A, B, A.rp[r0 + r], A.rp[r0 + r + 1], base};
+    const int64_t dst = c_row_ptr[r], want = c_row_ptr[r + 1] - dst;
+    const uint32_t cnt = rank_region<BLOCK, CAP, true, V>(src, (uint32_t)(maxc[r] - base) + 1u, L, tid,
+                                                          [&](uint32_t rk, uint32_t c) {
+                                                              if (rk < want) c_col[dst + rk] = base + (CI)c;
+                                                          });
+    if (tid == 0 && cnt != want) atomicOr(err, 1);
+    const int64_t m = cnt < want ? cnt : want;
+    for (int q = tid; q < m; q += BLOCK) c_val[dst + q] = L.vals[q];
+}
+
+template <class K, class... Args>
+void launch_rank(K kernel, int block, int regs, int64_t n, hipStream_t s, Args... args) {
+    if (n <= 0) return;
+    const int64_t groups = (n + regs - 1) / regs;
+    GM_REQUIRE(groups < (int64_t)1 << 31, GMAGNUS_ERROR_UNSUPPORTED, "too many work items for one launch");
+    hipLaunchKernelGGL(kernel, dim3((unsigned)groups), dim3(block * regs), 0, s, args...);
+    GM_CHECK_LAUNCH();
+}
+
+// -------------------------------------------------- sort-based small chunks
+// Small wide chunks: every element is placed in LDS as (column, value), the
+// columns are sorted with a stable LSD radix sort carrying the element index,
+// and runs of equal columns are summed. This replaces a hash table plus a
+// bitonic sort of the whole table with its many barrier-separated stages.
 
 // Stable LSD radix sort of n <= CAP keys in LDS, 8-bit digits over the low
 // `bits` bits, with a 16-bit payload. Wave w ranks the contiguous range
@@ -683,13 +761,8 @@ struct SortLds {
     V vals[CAP];
     uint16_t idx[2][CAP];
     int32_t hist[(BLOCK / GM_WAVE) * 256];
-    int32_t off[BLOCK + 1];
-    int64_t bst[BLOCK];
-    V av[BLOCK];
     int32_t scan[BLOCK / GM_WAVE];
 };
-
-constexpr int SORT_ILP = 4;
 
 // Writes the sums of the runs of equal keys of a sorted (keys, idx) array in
 // key order: heads counted per thread over a contiguous range, their output
@@ -731,80 +804,6 @@ GM_DEV void sorted_runs_emit(const uint32_t *keys, const uint16_t *idx, uint16_t
             }
         }
     }
-}
-
-template <int BLOCK, int CAP, typename CI, typename V>
-__global__ __launch_bounds__(BLOCK) void k_light_sort_num(CsrV<CI, V> A, CsrV<CI, V> B, int64_t r0,
-                                                          const int64_t *items, const CI *minc, const CI *maxc,
-                                                          const int64_t *c_row_ptr, CI *c_col, V *c_val,
-                                                          int32_t *err) {
-    static_assert(CAP < 65536, "16-bit product indices");
-    __shared__ SortLds<BLOCK, CAP, V> L;
-    const int tid = threadIdx.x;
-    const int64_t r = items[blockIdx.x];
-    const CI base_col = minc[r];
-    const uint32_t span = (uint32_t)(maxc[r] - base_col);
-    const int64_t j0 = A.rp[r0 + r], j1 = A.rp[r0 + r + 1];
-    const int64_t dst = c_row_ptr[r], nnz = c_row_ptr[r + 1] - dst;
-    // gather every product of the row: A entries in batches of BLOCK
-    int n = 0;
-    for (int64_t jb = j0; jb < j1; jb += BLOCK) {
-        const int nb = (int)(j1 - jb < BLOCK ? j1 - jb : BLOCK);
-        int32_t len = 0;
-        if (tid < nb) {
-            const int64_t k = (int64_t)A.ci[jb + tid];
-            const int64_t bs = B.rp[k];
-            len = (int32_t)(B.rp[k + 1] - bs);
-            L.bst[tid] = bs;
-            L.av[tid] = A.v[jb + tid];
-        }
-        int32_t tot;
-        const int32_t ex = block_excl_scan<BLOCK>(len, L.scan, &tot);
-        L.off[tid] = tid < nb ? ex : INT32_MAX;
-        __syncthreads();
-        if (n + tot > CAP) {  // cannot happen for a light row of this bin (ip <= CAP)
-            if (tid == 0) atomicOr(err, 8);
-            return;
-        }
-        // as in gustavson_row: searches, then every load, with no branch between them
-        for (int tb = tid; tb < tot; tb += BLOCK * SORT_ILP) {
-            int q[SORT_ILP];
-            int64_t src[SORT_ILP];
-#pragma unroll
-            for (int u = 0; u < SORT_ILP; ++u) {
-                const int t = tb + u * BLOCK < tot ? tb + u * BLOCK : tot - 1;
-                q[u] = entry_of<BLOCK>(L.off, t);
-                src[u] = L.bst[q[u]] + (t - L.off[q[u]]);
-            }
-            CI c[SORT_ILP];
-            V v[SORT_ILP];
-#pragma unroll
-            for (int u = 0; u < SORT_ILP; ++u) {
-                c[u] = B.ci[src[u]];
-                v[u] = B.v[src[u]];
-            }
-#pragma unroll
-            for (int u = 0; u < SORT_ILP; ++u) v[u] *= L.av[q[u]];
-#pragma unroll
-            for (int u = 0; u < SORT_ILP; ++u) {
-                const int t = tb + u * BLOCK;
-                if (t < tot) {
-                    L.keys[0][n + t] = (uint32_t)(c[u] - base_col);
-                    L.vals[n + t] = v[u];
-                    L.idx[0][n + t] = (uint16_t)(n + t);
-                }
-            }
-        }
-        n += tot;
-        __syncthreads();
-    }
-    const int bits = span == 0 ? 0 : 32 - __clz((int)span);
-    uint32_t *keys = L.keys[0], *keys_alt = L.keys[1];
-    uint16_t *idx = L.idx[0], *idx_alt = L.idx[1];
-    if (CAP > 512 || !msd_sort_lds<BLOCK, CAP>(keys, idx, keys_alt, idx_alt, n, bits, L.hist, L.scan))
-        radix_sort_lds<BLOCK, CAP>(keys, idx, keys_alt, idx_alt, n, bits, L.hist, L.scan);
-    sorted_runs_emit<BLOCK, CAP>(keys, idx, idx_alt, (const V *)L.vals, n, nnz, base_col, c_col + dst, c_val + dst,
-                                 err, 1, L.scan);
 }
 
 // Dense window of a light row: one presence byte per column, set with a
@@ -1183,8 +1182,8 @@ constexpr int RANK_L2BLOCK = 512, RANK_L2EPT = 14;  // the same in 8 waves: twic
 constexpr int RANK_X2BLOCK = 1024, RANK_X2EPT = 8;  // 16 waves for the shapes whose LDS allows two groups per CU
 constexpr int RANK_LBLOCK = 256, RANK_LWEPT = 27;  // wide symbolic at 2^17 columns: 4 waves and 16 KB of
                                                    // LDS, so eight work groups share a CU
-static_assert(RANK_LBLOCK * RANK_LWEPT >= SORT_CAP[2] && RANK_BLOCK * RANK_EPT >= SORT_CAP[2] &&
-                  RANK_L2BLOCK * RANK_L2EPT >= SORT_CAP[2] && RANK_X2BLOCK * RANK_X2EPT >= SORT_CAP[2],
+static_assert(RANK_LBLOCK * RANK_LWEPT >= TAU_MAX && RANK_BLOCK * RANK_EPT >= TAU_MAX &&
+                  RANK_L2BLOCK * RANK_L2EPT >= TAU_MAX && RANK_X2BLOCK * RANK_X2EPT >= TAU_MAX,
               "the wide shapes hold a light chunk of up to the largest tau");
 static_assert(RANK_WBLOCK * RANK_WEPT >= RANK_WIDE_SMALL, "the small wide shape holds its chunks");
 constexpr int RANK_SBLOCK = 256, RANK_SWORDS = 256, RANK_SCAP = 512, RANK_SEPT = 2, RANK_LEPT = 8;
@@ -1507,17 +1506,12 @@ void launch_items(K kernel, int block, int64_t n, hipStream_t s, Args... args) {
 
 }  // namespace
 
-void light_classes_sym(const int64_t *ip, const void *minc, const void *maxc, bool ci64, int64_t n, int64_t tau,
-                       bool window, uint8_t *cls, hipStream_t s) {
-    light_classes_num(ip, nullptr, minc, maxc, ci64, n, tau, window, cls, s);
-}
-
-void light_classes_num(const int64_t *ip, const int64_t *row_nnz, const void *minc, const void *maxc, bool ci64,
-                       int64_t n, int64_t tau, bool window, uint8_t *cls, hipStream_t s) {
+void light_classes(const int64_t *ip, const void *minc, const void *maxc, bool ci64, int64_t n, int64_t tau, bool window,
+                   uint8_t *cls, hipStream_t s) {
     if (n <= 0) return;
     with_index_type(ci64, [&](auto ci) {
         using CI = decltype(ci);
-        hipLaunchKernelGGL(k_light_classes<CI>, dim3(grid_for(n, 256, 65536)), dim3(256), 0, s, ip, row_nnz,
+        hipLaunchKernelGGL(k_light_classes<CI>, dim3(grid_for(n, 256, 65536)), dim3(256), 0, s, ip,
                            static_cast<const CI *>(minc), static_cast<const CI *>(maxc), n, tau, (int)window, cls);
         GM_CHECK_LAUNCH();
     });
@@ -1559,7 +1553,7 @@ void light_symbolic_narrow(const Csr &A, const Csr &B, int64_t r0, const int64_t
 }
 
 void light_symbolic(const Csr &A, const Csr &B, int64_t r0, int bin, const int64_t *items, int64_t n,
-                    const void *minc_v, const void *maxc_v, int64_t *row_nnz, hipStream_t s) {
+                    const int64_t *ip, const void *minc_v, const void *maxc_v, int64_t *row_nnz, hipStream_t s) {
     with_index_type(B.ci64, [&](auto ci) {
         using CI = decltype(ci);
         const auto a = typed<CI, NoV>(A);
@@ -1575,17 +1569,20 @@ void light_symbolic(const Csr &A, const Csr &B, int64_t r0, int bin, const int64
         case LIGHT_W2:
             launch_items(k_light_win_sym<512, WIN2, CI>, 512, n, s, a, b, r0, items, minc, maxc, row_nnz);
             break;
-        case LIGHT_H0:
-            launch_items(k_light_hash_sym<64, 2 * HS_CAP[0], CI>, 64, n, s, a, b, r0, items, minc, row_nnz);
+        case LIGHT_R0:
+            launch_items(k_light_hash_sym<4 * RB_CAP[0], CI>, 64, n, s, a, b, r0, items, ip, minc, row_nnz);
             break;
-        case LIGHT_H1:
-            launch_items(k_light_hash_sym<64, 2 * HS_CAP[1], CI>, 64, n, s, a, b, r0, items, minc, row_nnz);
+        case LIGHT_R1:
+            launch_items(k_light_hash_sym<4 * RB_CAP[1], CI>, 64, n, s, a, b, r0, items, ip, minc, row_nnz);
             break;
-        case LIGHT_H2:
-            launch_items(k_light_hash_sym<256, 2 * HS_CAP[2], CI>, 256, n, s, a, b, r0, items, minc, row_nnz);
+        case LIGHT_R2:
+            launch_rank(k_light_rank_sym<256, RB_CAP[2], 1, CI>, 256, 1, n, s, a, b, r0, items, n, minc, maxc, row_nnz);
             break;
-        case LIGHT_H3:
-            launch_items(k_light_hash_sym<512, 2 * HS_CAP[3], CI>, 512, n, s, a, b, r0, items, minc, row_nnz);
+        case LIGHT_R3:
+            launch_rank(k_light_rank_sym<512, RB_CAP[3], 1, CI>, 512, 1, n, s, a, b, r0, items, n, minc, maxc, row_nnz);
+            break;
+        case LIGHT_R4:
+            launch_rank(k_light_rank_sym<896, RB_CAP[4], 1, CI>, 896, 1, n, s, a, b, r0, items, n, minc, maxc, row_nnz);
             break;
         default: break;
         }
@@ -1616,33 +1613,25 @@ void light_numeric(const Csr &A, const Csr &B, int64_t r0, int bin, const int64_
             launch_items(k_light_win_num<512, WIN2, CI, V>, 512, n, s, a, b, r0, items, minc, maxc, c_row_ptr, c_col,
                          c_val, err);
             break;
-        case LIGHT_H0:
-            launch_items(k_light_hash_num<64, 256, CI, V>, 64, n, s, a, b, r0, items, minc, c_row_ptr, c_col, c_val,
-                         err);
+        case LIGHT_R0:
+            launch_rank(k_light_rank_num<64, RB_CAP[0], 4, CI, V>, 64, 4, n, s, a, b, r0, items, n, minc, maxc, c_row_ptr,
+                        c_col, c_val, err);
             break;
-        case LIGHT_H1:
-            launch_items(k_light_sort_num<64, SORT_SMALL[0], CI, V>, 64, n, s, a, b, r0, items, minc, maxc, c_row_ptr,
-                         c_col, c_val, err);
+        case LIGHT_R1:
+            launch_rank(k_light_rank_num<64, RB_CAP[1], 4, CI, V>, 64, 4, n, s, a, b, r0, items, n, minc, maxc, c_row_ptr,
+                        c_col, c_val, err);
             break;
-        case LIGHT_H2:
-            launch_items(k_light_sort_num<64, SORT_SMALL[1], CI, V>, 64, n, s, a, b, r0, items, minc, maxc, c_row_ptr,
-                         c_col, c_val, err);
+        case LIGHT_R2:
+            launch_rank(k_light_rank_num<256, RB_CAP[2], 1, CI, V>, 256, 1, n, s, a, b, r0, items, n, minc, maxc, c_row_ptr,
+                        c_col, c_val, err);
             break;
-        case LIGHT_H3:
-            launch_items(k_light_hash_num<64, 1024, CI, V>, 64, n, s, a, b, r0, items, minc, c_row_ptr, c_col, c_val,
-                         err);
+        case LIGHT_R3:
+            launch_rank(k_light_rank_num<512, RB_CAP[3], 1, CI, V>, 512, 1, n, s, a, b, r0, items, n, minc, maxc, c_row_ptr,
+                        c_col, c_val, err);
             break;
-        case LIGHT_H4:
-            launch_items(k_light_sort_num<256, SORT_CAP[0], CI, V>, 256, n, s, a, b, r0, items, minc, maxc, c_row_ptr,
-                         c_col, c_val, err);
-            break;
-        case LIGHT_H5:
-            launch_items(k_light_sort_num<256, SORT_CAP[1], CI, V>, 256, n, s, a, b, r0, items, minc, maxc, c_row_ptr,
-                         c_col, c_val, err);
-            break;
-        case LIGHT_H6:
-            launch_items(k_light_sort_num<512, SORT_CAP[2], CI, V>, 512, n, s, a, b, r0, items, minc, maxc, c_row_ptr,
-                         c_col, c_val, err);
+        case LIGHT_R4:
+            launch_rank(k_light_rank_num<896, RB_CAP[4], 1, CI, V>, 896, 1, n, s, a, b, r0, items, n, minc, maxc, c_row_ptr,
+                        c_col, c_val, err);
             break;
         default: break;
         }
@@ -1824,12 +1813,10 @@ void slot_scan(int64_t *slot, int64_t n_heavy, int64_t n_slots, const int64_t *h
 
 int64_t tau_limit() {
     int64_t t = HN_CAP[3] < RANK_NNZ_MAX ? HN_CAP[3] : RANK_NNZ_MAX;
-    return t < SORT_CAP[2] ? t : SORT_CAP[2];
+    return t < TAU_MAX ? t : TAU_MAX;
 }
 
-// Rows of more products take the heavy path even when they are below tau:
-// one 512-thread group per CU sorting up to 6912 products in LDS is slower
-// than expanding and splitting them.
-int64_t light_row_limit() { return SORT_CAP[1]; }
+// Rows of more products take the heavy path even when they are below tau.
+int64_t light_row_limit() { return LIGHT_MAX; }
 
 }  // namespace gm

@@ -289,7 +289,7 @@ enum LeafBin : uint8_t {
     LEAF_RANK_T, LEAF_NBINS
 };
 enum LightBin : uint8_t {
-    LIGHT_EMPTY = 0, LIGHT_HEAVY, LIGHT_W0, LIGHT_W1, LIGHT_W2, LIGHT_H0, LIGHT_H1, LIGHT_H2, LIGHT_H3, LIGHT_H4, LIGHT_H5, LIGHT_H6, LIGHT_NBINS
+    LIGHT_EMPTY = 0, LIGHT_HEAVY, LIGHT_W0, LIGHT_W1, LIGHT_W2, LIGHT_R0, LIGHT_R1, LIGHT_R2, LIGHT_R3, LIGHT_R4, LIGHT_NBINS
 };
 // Largest tau the light accumulators can hold.
 int64_t tau_limit();
@@ -297,10 +297,8 @@ int64_t tau_limit();
 int64_t light_row_limit();
 // (minc / maxc of B's column type: int64 when ci64; a row whose column span
 // does not fit 31 bits is sent to the heavy path)
-void light_classes_sym(const int64_t *ip, const void *minc, const void *maxc, bool ci64, int64_t n, int64_t tau,
-                       bool window, uint8_t *cls, hipStream_t s);
-void light_classes_num(const int64_t *ip, const int64_t *row_nnz, const void *minc, const void *maxc, bool ci64,
-                       int64_t n, int64_t tau, bool window, uint8_t *cls, hipStream_t s);
+void light_classes(const int64_t *ip, const void *minc, const void *maxc, bool ci64, int64_t n, int64_t tau, bool window,
+                   uint8_t *cls, hipStream_t s);
 void leaf_classes_sym(const LeafSet &L, int64_t tau, int64_t width, uint8_t *cls, hipStream_t s);
 void leaf_classes_num(const LeafSet &L, const int64_t *leaf_nnz, int64_t tau, int64_t width, uint8_t *cls,
                       hipStream_t s);
@@ -337,7 +335,7 @@ int64_t brow_mask_bytes(const Csr &B);
 void light_symbolic_narrow(const Csr &A, const Csr &B, int64_t r0, const int64_t *items, int64_t n,
                            const void *minc, void *masks, int64_t *row_nnz, hipStream_t s);
 void light_symbolic(const Csr &A, const Csr &B, int64_t r0, int bin, const int64_t *items, int64_t n,
-                    const void *minc, const void *maxc, int64_t *row_nnz, hipStream_t s);
+                    const int64_t *ip, const void *minc, const void *maxc, int64_t *row_nnz, hipStream_t s);
 void light_numeric(const Csr &A, const Csr &B, int64_t r0, int bin, const int64_t *items, int64_t n,
                    const void *minc, const void *maxc, const int64_t *c_row_ptr, void *c_col, void *c_val,
                    int32_t *err, hipStream_t s);

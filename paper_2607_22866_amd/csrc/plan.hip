@@ -282,10 +282,8 @@ struct gmagnus_plan_s {
     int64_t *ip = nullptr;
     void *minc = nullptr, *maxc = nullptr;  // B's column type
     int64_t vsize = 8, csize = 4;          // bytes of a value and of a column index
-    int64_t *perm = nullptr;          // rows grouped by symbolic light bin (heavy class included)
+    int64_t *perm = nullptr;          // rows grouped by light bin (heavy class included)
     int64_t bins_sym[LIGHT_NBINS + 1] = {0};
-    int64_t *perm_num = nullptr;      // rows grouped by numeric bin
-    int64_t bins_num[LIGHT_NBINS + 1] = {0};
     int64_t n_heavy = 0;
     const int64_t *heavy_rows = nullptr;
     int64_t *chat_ptr = nullptr;      // n_heavy + 1
@@ -734,7 +732,7 @@ void do_plan(gmagnus_plan_s *p, const gmagnus_matrix_t *A, const gmagnus_matrix_
     }
     const bool window = (o.flags & GMAGNUS_FLAG_NO_WINDOW) == 0;
     uint8_t *cls = ws.alloc<uint8_t>(n);
-    light_classes_sym(p->ip, p->minc, p->maxc, p->B.ci64, n, p->info.row_tau, window, cls, stream);
+    light_classes(p->ip, p->minc, p->maxc, p->B.ci64, n, p->info.row_tau, window, cls, stream);
     p->perm = ws.alloc<int64_t>(n);
     int64_t *bins = ws.alloc<int64_t>(LIGHT_NBINS + 1);
     int64_t *scratch = ws.alloc<int64_t>(std::max(partition_scratch_elems(n, LIGHT_NBINS), scan_scratch_elems(n)));
@@ -1517,7 +1515,7 @@ void light_symbolic_all(gmagnus_plan_s *p, void **keep) {
             light_symbolic_narrow(p->A, p->B, p->r0, p->perm + p->bins_sym[b], cnt, p->minc, masks, p->row_nnz, s);
             *keep = masks;
         } else {
-            light_symbolic(p->A, p->B, p->r0, b, p->perm + p->bins_sym[b], cnt, p->minc, p->maxc, p->row_nnz, s);
+            light_symbolic(p->A, p->B, p->r0, b, p->perm + p->bins_sym[b], cnt, p->ip, p->minc, p->maxc, p->row_nnz, s);
         }
         if (cnt) p->info.kernel_launches[GMAGNUS_K_LIGHT_SYM] += 1;
     }
@@ -1563,8 +1561,7 @@ void do_symbolic(gmagnus_plan_s *p, int64_t *c_row_ptr, int64_t *c_nnz) {
     GM_HIP(hipStreamWaitEvent(p->stream, jl, 0));
     GM_HIP(hipStreamWaitEvent(p->stream, jh, 0));
     ws.free(light_keep);
-    // C's row pointers, then the light rows' numeric bins; nnz(C) and the
-    // bins come back in one host round trip
+    // C's row pointers and nnz(C)
     int64_t *hs = nullptr, *sc = nullptr;
     {
         Timed t(p, GMAGNUS_K_ROWPTR, p->stream);
@@ -1576,29 +1573,14 @@ void do_symbolic(gmagnus_plan_s *p, int64_t *c_row_ptr, int64_t *c_nnz) {
         }
         add_bytes(p, GMAGNUS_K_ROWPTR, 16.0 * n);
     }
-    uint8_t *cls = ws.alloc<uint8_t>(n);
-    int64_t *bins = ws.alloc<int64_t>(LIGHT_NBINS + 1);
-    int64_t *psc = ws.alloc<int64_t>(partition_scratch_elems(n, LIGHT_NBINS));
-    {
-        Timed t(p, GMAGNUS_K_SETUP, p->stream);
-        const bool window = (p->opts.flags & GMAGNUS_FLAG_NO_WINDOW) == 0;
-        p->perm_num = ws.alloc<int64_t>(n);
-        light_classes_num(p->ip, p->row_nnz, p->minc, p->maxc, p->B.ci64, n, p->info.row_tau, window, cls,
-                          p->stream);
-        partition_u8(cls, n, LIGHT_NBINS, p->perm_num, nullptr, bins, psc, p->stream);
-    }
     {
         HostReads r(p->stream);
         r.add(c_row_ptr + n, 1, &p->c_nnz);
         if (hs) r.add(hs + p->n_heavy, 1, &p->info.c_nnz_heavy);
-        r.add(bins, LIGHT_NBINS + 1, p->bins_num);
         r.wait();
     }
     ws.free(hs);
     ws.free(sc);
-    ws.free(cls);
-    ws.free(bins);
-    ws.free(psc);
     *c_nnz = p->c_nnz;
     p->info.c_nnz = p->c_nnz;
     p->symbolic_done = true;
@@ -1658,8 +1640,8 @@ void do_numeric(gmagnus_plan_s *p, const int64_t *c_row_ptr, void *c_col, void *
         const hipStream_t s = p->s_light;
         Timed t(p, GMAGNUS_K_LIGHT_NUM, s);
         for (int b = LIGHT_W0; b < LIGHT_NBINS; ++b) {
-            const int64_t cnt = p->bins_num[b + 1] - p->bins_num[b];
-            light_numeric(p->A, p->B, p->r0, b, p->perm_num + p->bins_num[b], cnt, p->minc, p->maxc, c_row_ptr, c_col,
+            const int64_t cnt = p->bins_sym[b + 1] - p->bins_sym[b];
+            light_numeric(p->A, p->B, p->r0, b, p->perm + p->bins_sym[b], cnt, p->minc, p->maxc, c_row_ptr, c_col,
                           c_val, p->err, s);
             if (cnt) p->info.kernel_launches[GMAGNUS_K_LIGHT_NUM] += 1;
         }

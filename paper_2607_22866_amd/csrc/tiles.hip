@@ -23,6 +23,7 @@
 #include <type_traits>
 
 #include "host.hpp"
+#include "rank.hpp"
 
 namespace gm {
 
@@ -651,195 +652,44 @@ GM_DEV void bit_or(uint32_t *bits, uint32_t c) {
     __hip_atomic_fetch_or(&bits[c >> 5], 1u << (c & 31), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
-// The bitmap with every word's rank beside it (the present columns, or words, before it).
-struct RankWord {
-    uint32_t bits, rank;
+// Regions of at most TILE_MERGE products (rank.hpp): the parts come from the
+// lists, their columns relative to the region's first chunk.
+template <typename V>
+struct TileParts {
+    typedef uint32_t Pos;
+    typedef uint32_t Col;
+    const TileArgs<V> &t;
+    const Region &g;
+    GM_DEV int64_t np() const { return g.q1 - g.q0; }
+    GM_DEV uint32_t part(int64_t q, int64_t *st, uint32_t *aux) const {
+        const uint2 sg = t.seg[g.q0 + q];
+        *st = sg.x;
+        *aux = ((sg.y >> 16) - g.sub0) << TILE_LOG2;
+        return sg.y & 0xffffu;
+    }
+    GM_DEV V scale(int64_t q) const { return t.ea[t.seg_e[g.q0 + q]]; }
+    GM_DEV RankWord pack(int64_t st, uint32_t off, uint32_t aux) const { return RankWord{(uint32_t)st - off, aux}; }
+    GM_DEV Pos at(const RankWord &p, uint32_t x, uint32_t *col) const {
+        *col = p.rank;
+        return p.bits + x;
+    }
+    GM_DEV Col col(Pos p) const { return t.col[p]; }
+    GM_DEV V val(Pos p) const { return t.val[p]; }
+    GM_DEV uint32_t local(Col c) const { return c; }
 };
-GM_DEV uint32_t rank_of(const RankWord &x, uint32_t bit) { return x.rank + (uint32_t)__popc(x.bits & ((1u << bit) - 1u)); }
-
-// Regions of at most TILE_MERGE products, up to 2^18 columns wide, one
-// thread of a work group (or lane of a wave: BLOCK = 64, several regions per
-// work group, no barrier between them) holding EPT = CAP / BLOCK products in
-// registers. The region's parts are laid out in product order (their last
-// products marked in a bitmap, which gives a product its part), so every
-// thread's loads go out at once. The 32-column words that hold columns are
-// marked in a bitmap of words; a scan numbers them, the columns are marked in
-// those words only, and a second scan gives every column its rank: the work
-// follows the products and not the columns.
-constexpr int TTOP = (16 * TILE_COLS) / 32 / 32;
-
-template <int BLOCK>
-GM_DEV void region_sync() {
-    if (BLOCK == GM_WAVE)
-        wave_lds_fence();
-    else
-        __syncthreads();
-}
-
-// Exclusive scan over the threads of a region (one wave or the work group).
-template <int BLOCK>
-GM_DEV int32_t region_scan(int32_t x, int32_t *sm, int32_t *total) {
-    if constexpr (BLOCK == GM_WAVE) {
-        const int32_t inc = wave_incl_scan<int32_t>(x);
-        *total = __builtin_amdgcn_readlane(inc, GM_WAVE - 1);
-        return inc - x;
-    } else {
-        return block_excl_scan<BLOCK>(x, sm, total);
-    }
-}
-
-template <int BLOCK, int CAP, bool NUM, typename V>
-struct SmallLds {
-    RankWord top[TTOP];
-    RankWord words[CAP];       // first the parts: (start - first product, column offset)
-    V vals[NUM ? CAP : 1];     // first the parts' scales
-    RankWord ends[CAP / 32];   // last products of the parts; rank: parts that end before the word
-    int32_t scan[BLOCK / GM_WAVE];
-};
-
-// The region's distinct columns (returned). With NUM their sums are left in
-// L.vals in order, and put(rank, column) is called once per distinct column.
-template <int BLOCK, int CAP, bool NUM, typename V, class Put>
-GM_DEV int small_region(const TileArgs<V> &t, const Region &g, SmallLds<BLOCK, CAP, NUM, V> &L, int tid, Put &&put) {
-    constexpr int EPT = CAP / BLOCK, TPT = (TTOP + BLOCK - 1) / BLOCK;
-    const int ntop = g.chunks * (TTOP / 16);
-    for (int q = tid; q < ntop; q += BLOCK) L.top[q].bits = 0u;
-    for (int q = tid; q < CAP / 32; q += BLOCK) L.ends[q].bits = 0u;
-    region_sync<BLOCK>();
-    const uint32_t np = g.q1 - g.q0 < (uint32_t)CAP ? g.q1 - g.q0 : (uint32_t)CAP;  // (parts are not empty)
-    uint32_t n = 0;  // products
-    for (uint32_t j = 0; j < np; j += BLOCK) {
-        const uint32_t q = j + tid;
-        uint32_t len = 0;
-        uint2 sg = make_uint2(0u, 0u);
-        if (q < np) {
-            sg = t.seg[g.q0 + q];
-            len = sg.y & 0xffffu;
-            if (NUM) L.vals[q] = t.ea[t.seg_e[g.q0 + q]];
-        }
-        int32_t tot;
-        const uint32_t off = n + (uint32_t)region_scan<BLOCK>((int32_t)len, L.scan, &tot);
-        if (q < np && off + len <= (uint32_t)CAP) {  // (always: a region of the bin holds at most CAP products)
-            L.words[q] = RankWord{sg.x - off, ((sg.y >> 16) - g.sub0) << TILE_LOG2};
-            __hip_atomic_fetch_or(&L.ends[(off + len - 1) >> 5].bits, 1u << ((off + len - 1) & 31), __ATOMIC_RELAXED,
-                                  __HIP_MEMORY_SCOPE_WORKGROUP);
-        }
-        n += (uint32_t)tot;
-    }
-    n = n < (uint32_t)CAP ? n : (uint32_t)CAP;
-    region_sync<BLOCK>();
-    if (tid < GM_WAVE) {  // parts that end before each word of products
-        constexpr int NE = CAP / 32, PER = (NE + GM_WAVE - 1) / GM_WAVE;
-        int32_t cnt = 0;
-        uint32_t b[PER];
-#pragma unroll
-        for (int q = 0; q < PER; ++q) {
-            b[q] = tid * PER + q < NE ? L.ends[tid * PER + q].bits : 0u;
-            cnt += __popc(b[q]);
-        }
-        uint32_t run = (uint32_t)(wave_incl_scan<int32_t>(cnt) - cnt);
-#pragma unroll
-        for (int q = 0; q < PER; ++q) {
-            if (tid * PER + q < NE) L.ends[tid * PER + q].rank = run;
-            run += (uint32_t)__popc(b[q]);
-        }
-    }
-    region_sync<BLOCK>();
-    uint32_t col[EPT], pos[EPT], own[EPT];
-    V val[EPT];
-#pragma unroll
-    for (int k = 0; k < EPT; ++k) {
-        const uint32_t x = tid + k * BLOCK < n ? tid + k * BLOCK : n - 1;
-        own[k] = rank_of(L.ends[x >> 5], x & 31);
-        const RankWord pt = L.words[own[k]];
-        pos[k] = pt.bits + x;
-        col[k] = pt.rank;
-    }
-    uint32_t lc[EPT];
-#pragma unroll
-    for (int k = 0; k < EPT; ++k) {
-        lc[k] = t.col[pos[k]];
-        if (NUM) val[k] = t.val[pos[k]];
-    }
-#pragma unroll
-    for (int k = 0; k < EPT; ++k) {
-        if (NUM) val[k] *= L.vals[own[k]];
-        col[k] += lc[k];
-        if (tid + k * BLOCK < n)
-            __hip_atomic_fetch_or(&L.top[col[k] >> 10].bits, 1u << ((col[k] >> 5) & 31), __ATOMIC_RELAXED,
-                                  __HIP_MEMORY_SCOPE_WORKGROUP);
-    }
-    region_sync<BLOCK>();  // (the parts are read)
-    int32_t nwords;
-    {
-        int32_t cnt = 0;
-        uint32_t b[TPT];
-#pragma unroll
-        for (int q = 0; q < TPT; ++q) {
-            b[q] = tid * TPT + q < ntop ? L.top[tid * TPT + q].bits : 0u;
-            cnt += __popc(b[q]);
-        }
-        uint32_t run = (uint32_t)region_scan<BLOCK>(cnt, L.scan, &nwords);
-#pragma unroll
-        for (int q = 0; q < TPT; ++q) {
-            if (tid * TPT + q < ntop) L.top[tid * TPT + q].rank = run;
-            run += (uint32_t)__popc(b[q]);
-        }
-    }
-    for (int q = tid; q < nwords; q += BLOCK) L.words[q].bits = 0u;
-    region_sync<BLOCK>();
-    uint32_t wd[EPT], fresh = 0;
-#pragma unroll
-    for (int k = 0; k < EPT; ++k)
-        if (tid + k * BLOCK < n) {
-            wd[k] = rank_of(L.top[col[k] >> 10], (col[k] >> 5) & 31);
-            const uint32_t bit = 1u << (col[k] & 31);
-            const uint32_t old = __hip_atomic_fetch_or(&L.words[wd[k]].bits, bit, __ATOMIC_RELAXED,
-                                                       __HIP_MEMORY_SCOPE_WORKGROUP);
-            if (!(old & bit)) fresh |= 1u << k;
-        }
-    int32_t total;
-    if constexpr (!NUM) {
-        region_scan<BLOCK>(__popc(fresh), L.scan, &total);
-        return total;
-    }
-    region_sync<BLOCK>();
-    {
-        const int per = (nwords + BLOCK - 1) / BLOCK;  // words per thread (uniform)
-        int32_t cnt = 0;
-        for (int q = 0; q < per; ++q)
-            if (tid * per + q < nwords) cnt += __popc(L.words[tid * per + q].bits);
-        uint32_t run = (uint32_t)region_scan<BLOCK>(cnt, L.scan, &total);
-        for (int q = 0; q < per; ++q)
-            if (tid * per + q < nwords) {
-                L.words[tid * per + q].rank = run;
-                run += (uint32_t)__popc(L.words[tid * per + q].bits);
-            }
-    }
-    for (int q = tid; q < total; q += BLOCK) L.vals[q] = (V)0;
-    region_sync<BLOCK>();
-#pragma unroll
-    for (int k = 0; k < EPT; ++k)
-        if (tid + k * BLOCK < n) {
-            const uint32_t rk = rank_of(L.words[wd[k]], col[k] & 31);
-            __hip_atomic_fetch_add(&L.vals[rk], val[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            if ((fresh >> k) & 1u) put(rk, col[k]);
-        }
-    region_sync<BLOCK>();
-    return total;
-}
 
 // Symbolic of small regions.
 template <int BLOCK, int CAP, int REGS>
 __global__ __launch_bounds__(BLOCK * REGS) void k_tile_sym_small(TileArgs<float> t, uint32_t *nnz, int64_t ncp,
                                                                  int64_t *slot) {
     static_assert(REGS == 1 || BLOCK == GM_WAVE, "several regions per work group are one wave each");
-    __shared__ __align__(16) SmallLds<BLOCK, CAP, false, float> L[REGS];
+    __shared__ __align__(16) RankLds<BLOCK, CAP, false, float> L[REGS];
     const int reg = REGS > 1 ? threadIdx.x / GM_WAVE : 0, tid = REGS > 1 ? threadIdx.x & (GM_WAVE - 1) : threadIdx.x;
     const int64_t i = blockIdx.x * (int64_t)REGS + reg;
     if (i >= t.n_items) return;  // the whole wave (one region: the whole work group)
     const Region g = region_at(t, i);
-    const int n = small_region<BLOCK, CAP, false, float>(t, g, L[reg], tid, [](uint32_t, uint32_t) {});
+    const uint32_t n = rank_region<BLOCK, CAP, false, float>(TileParts<float>{t, g}, (uint32_t)g.chunks << TILE_LOG2, L[reg],
+                                                             tid, [](uint32_t, uint32_t) {});
     if (tid == 0) {
         nnz[g.c * t.nh + g.h] = (uint32_t)n;
         slot[g.h * ncp + g.c] = n;
@@ -897,18 +747,19 @@ struct TileOut {
 template <int BLOCK, int CAP, int REGS, typename CI, typename V>
 __global__ __launch_bounds__(BLOCK * REGS) void k_tile_num_small(TileArgs<V> t, TileOut<CI, V> o) {
     static_assert(REGS == 1 || BLOCK == GM_WAVE, "several regions per work group are one wave each");
-    __shared__ __align__(16) SmallLds<BLOCK, CAP, true, V> L_all[REGS];
+    __shared__ __align__(16) RankLds<BLOCK, CAP, true, V> L_all[REGS];
     const int reg = REGS > 1 ? threadIdx.x / GM_WAVE : 0, tid = REGS > 1 ? threadIdx.x & (GM_WAVE - 1) : threadIdx.x;
     const int64_t i = blockIdx.x * (int64_t)REGS + reg;
     if (i >= t.n_items) return;  // the whole wave (one region: the whole work group)
     const Region g = region_at(t, i);
-    SmallLds<BLOCK, CAP, true, V> &L = L_all[reg];
+    RankLds<BLOCK, CAP, true, V> &L = L_all[reg];
     const int want = o.want(g, t.nh);
     const int64_t dst = o.dst(g);
     const CI cb = o.base(g);
-    const int total = small_region<BLOCK, CAP, true, V>(t, g, L, tid, [&](uint32_t rk, uint32_t c) {
-        if ((int)rk < want) o.c_col[dst + rk] = cb + (CI)c;
-    });
+    const int total = (int)rank_region<BLOCK, CAP, true, V>(TileParts<V>{t, g}, (uint32_t)g.chunks << TILE_LOG2, L, tid,
+                                                            [&](uint32_t rk, uint32_t c) {
+                                                                if ((int)rk < want) o.c_col[dst + rk] = cb + (CI)c;
+                                                            });
     if (tid == 0 && total != want) atomicOr(o.err, 4);
     const int m = total < want ? total : want;
     for (int q = tid; q < m; q += BLOCK) o.c_val[dst + q] = L.vals[q];
