@@ -10,30 +10,44 @@ namespace {
 constexpr int FLAT_BLOCK = 256;
 constexpr int FLAT_ITEMS = 8;  // consecutive entries per thread
 
-// InterOffsets for rows [r0, r1): every thread walks FLAT_ITEMS consecutive
-// nonzeros of A, adding nnz(B[k,:]) to its current row and tracking the
-// smallest first column and largest last column of the B rows it touches
-// (the row's column span, used to pick a dense window for light rows).
-// A row split across threads is merged with atomics. Without SPAN only the
-// counts are taken (one B.rp pair per entry, no reads of B's columns).
-// The rows of the work group's entries are found once (two searches of
-// A.rp), their row pointers staged in LDS when they are few, and each thread
-// issues all its loads of one kind together (entries, then B.rp pairs, then
-// the first and last columns) instead of one dependent chain per entry.
-constexpr int RP_ROWS = 1024;  // row pointers a work group stages in LDS
+// InterOffsets for rows [r0, r1): a work group takes FLAT_BLOCK * FLAT_ITEMS
+// consecutive nonzeros of A, every thread adding nnz(B[k,:]) of FLAT_ITEMS of
+// them to its current row and tracking the smallest first column and largest
+// last column of the B rows it touches (the row's column span, used to pick a
+// dense window for light rows). Without SPAN only the counts are taken (one
+// B.rp pair per entry, no reads of B's columns).
+// The rows of the work group's entries are found once (two searches of A.rp).
+// When they are few, their row pointers and sums are kept in LDS: a row that
+// lies inside the group is stored once, and only the group's first and last
+// row are merged with atomics on memory (every thread's partial sums merged
+// there: 0.40 ms for 27 entries x 2^20 rows, three atomics per 8 entries; 0.13 so).
+// Each thread issues all its loads of one kind together instead of one
+// dependent chain per entry.
+constexpr int RP_ROWS = 1024;  // rows a work group keeps in LDS
 
 // Per-B-row summary (length, first and last column) in one 16-byte record
 // (int32 columns), so that an A entry's B-row facts come from one random read
 // instead of the row pointer pair plus two column reads; built when the
 // panel has many more A entries than B has rows.
+//
+// One byte per row beside it: the length of a wide row (its columns span at
+// least a quarter of all, so no row of C that meets it fits a dense window) of
+// at most 254 elements, else 255. Where most rows are wide, an entry's facts
+// then come from a table that the L2s hold (4 MB for 2^22 rows) and a wide
+// row counts as spanning all columns: 1.36 -> 0.55 ms for 16 entries x 2^22
+// rows, whose 16-byte records (67 MB) came 128 bytes a read from behind the L2s.
 template <typename CI>
 struct BRowInfo {
     int64_t len;
     CI first, last;
 };
+constexpr int64_t WIDE_MIN_COLS = 65536;  // a quarter of fewer columns could fit a dense window
 
 template <typename CI>
-__global__ void k_brow_info(CsrV<CI, NoV> B, BRowInfo<CI> *info) {
+__global__ __launch_bounds__(256) void k_brow_info(CsrV<CI, NoV> B, BRowInfo<CI> *info, uint8_t *code, int bytes,
+                                                   unsigned long long *n_wide) {
+    __shared__ int32_t sm[256 / GM_WAVE];
+    int32_t wide = 0;
     for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < B.n_rows;
          k += (int64_t)gridDim.x * blockDim.x) {
         const int64_t b0 = B.rp[k], b1 = B.rp[k + 1];
@@ -42,15 +56,27 @@ __global__ void k_brow_info(CsrV<CI, NoV> B, BRowInfo<CI> *info) {
         r.first = b1 > b0 ? B.ci[b0] : (CI)0;
         r.last = b1 > b0 ? B.ci[b1 - 1] : (CI)0;
         info[k] = r;
+        if (bytes) {
+            const bool w = r.len < 255 && (r.len == 0 || (int64_t)(r.last - r.first) >= B.n_cols / 4);
+            code[k] = w ? (uint8_t)r.len : (uint8_t)255;
+            wide += w;
+        }
+    }
+    if (bytes) {
+        wide = block_reduce_sum<256>(wide, sm);
+        if (threadIdx.x == 0 && wide) atomicAdd(n_wide, (unsigned long long)wide);
     }
 }
 
 template <bool SPAN, bool INFO, typename CI>
 __global__ __launch_bounds__(FLAT_BLOCK) void k_row_products(CsrV<CI, NoV> A, CsrV<CI, NoV> B,
-                                                             const BRowInfo<CI> *binfo, int64_t r0, int64_t r1,
+                                                             const BRowInfo<CI> *binfo, const uint8_t *code,
+                                                             const unsigned long long *n_wide, int64_t r0, int64_t r1,
                                                              int64_t *ip, CI *minc, CI *maxc) {
     constexpr CI CI_MAX = sizeof(CI) == 8 ? (CI)INT64_MAX : (CI)INT32_MAX;
     __shared__ int64_t rp_s[RP_ROWS + 1];
+    __shared__ unsigned long long s_ip[RP_ROWS];
+    __shared__ CI s_lo[SPAN ? RP_ROWS : 1], s_hi[SPAN ? RP_ROWS : 1];
     __shared__ int64_t rows[2];
     const int64_t e_begin = A.rp[r0], e_end = A.rp[r1];
     const int64_t blk0 = e_begin + blockIdx.x * (int64_t)FLAT_BLOCK * FLAT_ITEMS;
@@ -61,72 +87,119 @@ __global__ __launch_bounds__(FLAT_BLOCK) void k_row_products(CsrV<CI, NoV> A, Cs
     const int64_t ra = rows[0], rb = rows[1];  // rows of the group's first and last entry
     const int64_t nr = rb - ra + 1;
     const bool staged = nr <= RP_ROWS;
-    if (staged)
+    if (staged) {
         for (int64_t q = threadIdx.x; q <= nr; q += FLAT_BLOCK) rp_s[q] = A.rp[ra + q];
-    __syncthreads();
-    const int64_t e0 = blk0 + (int64_t)threadIdx.x * FLAT_ITEMS;
-    if (e0 >= blk1) return;
-    const int64_t e1 = e0 + FLAT_ITEMS < blk1 ? e0 + FLAT_ITEMS : blk1;
-    const int ne = (int)(e1 - e0);
-    int64_t kk[FLAT_ITEMS], b0[FLAT_ITEMS], b1[FLAT_ITEMS];
-    CI f[FLAT_ITEMS], l[FLAT_ITEMS];
-#pragma unroll
-    for (int i = 0; i < FLAT_ITEMS; ++i) kk[i] = (int64_t)A.ci[i < ne ? e0 + i : e0];
-    if (INFO) {
-#pragma unroll
-        for (int i = 0; i < FLAT_ITEMS; ++i) {
-            const BRowInfo<CI> r = binfo[kk[i]];
-            b0[i] = 0;
-            b1[i] = r.len;
-            f[i] = r.first;
-            l[i] = r.last;
-        }
-    } else {
-#pragma unroll
-        for (int i = 0; i < FLAT_ITEMS; ++i) {
-            b0[i] = B.rp[kk[i]];
-            b1[i] = B.rp[kk[i] + 1];
-        }
-        if (SPAN) {
-#pragma unroll
-            for (int i = 0; i < FLAT_ITEMS; ++i) {
-                const bool nonempty = b1[i] > b0[i];  // (an empty B may have no column array)
-                f[i] = nonempty ? B.ci[b0[i]] : (CI)0;
-                l[i] = nonempty ? B.ci[b1[i] - 1] : (CI)0;
+        for (int64_t q = threadIdx.x; q < nr; q += FLAT_BLOCK) {
+            s_ip[q] = 0;
+            if (SPAN) {
+                s_lo[q] = CI_MAX;
+                s_hi[q] = -1;
             }
         }
     }
-    int64_t row = staged ? ra + find_row(rp_s, 0, nr + 1, e0) : find_row(A.rp, ra, rb + 1, e0);
-    int64_t row_end = staged ? rp_s[row - ra + 1] : A.rp[row + 1];
-    int64_t acc = 0;
-    CI lo = CI_MAX, hi = -1;
+    __syncthreads();
+    const int64_t e0 = blk0 + (int64_t)threadIdx.x * FLAT_ITEMS;
+    if (e0 < blk1) {
+        const int64_t e1 = e0 + FLAT_ITEMS < blk1 ? e0 + FLAT_ITEMS : blk1;
+        const int ne = (int)(e1 - e0);
+        int64_t kk[FLAT_ITEMS], b0[FLAT_ITEMS], b1[FLAT_ITEMS];
+        CI f[FLAT_ITEMS], l[FLAT_ITEMS];
 #pragma unroll
-    for (int i = 0; i < FLAT_ITEMS; ++i) {
-        if (i >= ne) break;
-        while (e0 + i >= row_end) {  // flush and move to the next nonempty row
-            if (acc) atomicAdd((unsigned long long *)&ip[row - r0], (unsigned long long)acc);
-            if (SPAN && hi >= 0) {
-                __hip_atomic_fetch_min(&minc[row - r0], lo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                __hip_atomic_fetch_max(&maxc[row - r0], hi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        for (int i = 0; i < FLAT_ITEMS; ++i) kk[i] = (int64_t)A.ci[i < ne ? e0 + i : e0];
+        if (INFO) {
+            const bool bytes = code && *n_wide * 4 >= (unsigned long long)B.n_rows * 3;  // uniform
+            int cd[FLAT_ITEMS];
+#pragma unroll
+            for (int i = 0; i < FLAT_ITEMS; ++i) cd[i] = bytes ? code[kk[i]] : 255;
+#pragma unroll
+            for (int i = 0; i < FLAT_ITEMS; ++i) {
+                b0[i] = 0;
+                if (cd[i] == 255) {
+                    const BRowInfo<CI> r = binfo[kk[i]];
+                    b1[i] = r.len;
+                    f[i] = r.first;
+                    l[i] = r.last;
+                } else {
+                    b1[i] = cd[i];
+                    f[i] = 0;
+                    l[i] = (CI)(B.n_cols - 1);
+                }
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < FLAT_ITEMS; ++i) {
+                b0[i] = B.rp[kk[i]];
+                b1[i] = B.rp[kk[i] + 1];
+            }
+            if (SPAN) {
+#pragma unroll
+                for (int i = 0; i < FLAT_ITEMS; ++i) {
+                    const bool nonempty = b1[i] > b0[i];  // (an empty B may have no column array)
+                    f[i] = nonempty ? B.ci[b0[i]] : (CI)0;
+                    l[i] = nonempty ? B.ci[b1[i] - 1] : (CI)0;
+                }
+            }
+        }
+        int64_t row = staged ? ra + find_row(rp_s, 0, nr + 1, e0) : find_row(A.rp, ra, rb + 1, e0);
+        int64_t row_end = staged ? rp_s[row - ra + 1] : A.rp[row + 1];
+        int64_t acc = 0;
+        CI lo = CI_MAX, hi = -1;
+        auto flush = [&]() {
+            if (acc) {
+                if (staged) {
+                    atomicAdd(&s_ip[row - ra], (unsigned long long)acc);
+                    if (SPAN) {
+                        __hip_atomic_fetch_min(&s_lo[row - ra], lo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                        __hip_atomic_fetch_max(&s_hi[row - ra], hi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                    }
+                } else {
+                    atomicAdd((unsigned long long *)&ip[row - r0], (unsigned long long)acc);
+                    if (SPAN) {
+                        __hip_atomic_fetch_min(&minc[row - r0], lo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        __hip_atomic_fetch_max(&maxc[row - r0], hi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    }
+                }
             }
             acc = 0;
             lo = CI_MAX;
             hi = -1;
-            ++row;
-            row_end = staged ? rp_s[row - ra + 1] : A.rp[row + 1];
-        }
-        if (b1[i] > b0[i]) {
-            acc += b1[i] - b0[i];
-            if (SPAN) {
-                lo = f[i] < lo ? f[i] : lo;
-                hi = l[i] > hi ? l[i] : hi;
+        };
+#pragma unroll
+        for (int i = 0; i < FLAT_ITEMS; ++i) {
+            if (i >= ne) break;
+            while (e0 + i >= row_end) {  // flush and move to the next nonempty row
+                flush();
+                ++row;
+                row_end = staged ? rp_s[row - ra + 1] : A.rp[row + 1];
+            }
+            if (b1[i] > b0[i]) {
+                acc += b1[i] - b0[i];
+                if (SPAN) {
+                    lo = f[i] < lo ? f[i] : lo;
+                    hi = l[i] > hi ? l[i] : hi;
+                }
             }
         }
+        flush();
     }
-    if (acc) atomicAdd((unsigned long long *)&ip[row - r0], (unsigned long long)acc);
-    if (SPAN && hi >= 0) {
-        __hip_atomic_fetch_min(&minc[row - r0], lo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_fetch_max(&maxc[row - r0], hi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (!staged) return;  // uniform
+    __syncthreads();
+    for (int64_t q = threadIdx.x; q < nr; q += FLAT_BLOCK) {
+        if (s_ip[q] == 0) continue;  // (the arrays start with the values of an empty row)
+        const int64_t o = ra + q - r0;
+        if (rp_s[q] >= blk0 && rp_s[q + 1] <= blk1) {  // all of the row's entries are this group's
+            ip[o] = (int64_t)s_ip[q];
+            if (SPAN) {
+                minc[o] = s_lo[q];
+                maxc[o] = s_hi[q];
+            }
+        } else {
+            atomicAdd((unsigned long long *)&ip[o], s_ip[q]);
+            if (SPAN) {
+                __hip_atomic_fetch_min(&minc[o], s_lo[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_fetch_max(&maxc[o], s_hi[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+        }
     }
 }
 
@@ -365,7 +438,7 @@ unsigned flat_grid(int64_t total) {
 
 }  // namespace
 
-int64_t brow_info_bytes(const Csr &B) { return B.n_rows * (B.ci64 ? 24 : 16); }
+int64_t brow_info_bytes(const Csr &B) { return 8 + B.n_rows * ((B.ci64 ? 24 : 16) + 1); }
 
 void row_products(const Csr &A, const Csr &B, int64_t r0, int64_t r1, int64_t panel_nnz, int64_t *ip, void *minc,
                   void *maxc, hipStream_t s, void *binfo) {
@@ -380,19 +453,25 @@ void row_products(const Csr &A, const Csr &B, int64_t r0, int64_t r1, int64_t pa
             fill<CI>(mx, (CI)-1, n, s);
         }
         if (panel_nnz <= 0) return;
-        BRowInfo<CI> *bi = static_cast<BRowInfo<CI> *>(binfo);
+        // (the counter, the records, the bytes)
+        unsigned long long *n_wide = static_cast<unsigned long long *>(binfo);
+        BRowInfo<CI> *bi = binfo ? reinterpret_cast<BRowInfo<CI> *>(n_wide + 1) : nullptr;
+        // bytes only where a wide row rules a window out and all columns can be keyed in 31 bits
+        const bool bytes = bi && B.n_cols >= WIDE_MIN_COLS && B.n_cols < ((int64_t)1 << 31) - 1;
+        uint8_t *code = bytes ? reinterpret_cast<uint8_t *>(bi + B.n_rows) : nullptr;
         if (mn && bi) {
-            hipLaunchKernelGGL(k_brow_info<CI>, dim3(grid_for(B.n_rows, 256, 65536)), dim3(256), 0, s,
-                               typed<CI, NoV>(B), bi);
+            if (bytes) fill<unsigned long long>(n_wide, 0ull, 1, s);
+            hipLaunchKernelGGL(k_brow_info<CI>, dim3(grid_for(B.n_rows, 256, 2048)), dim3(256), 0, s, typed<CI, NoV>(B), bi,
+                               code, (int)bytes, n_wide);
             GM_CHECK_LAUNCH();
             hipLaunchKernelGGL((k_row_products<true, true, CI>), dim3(flat_grid(panel_nnz)), dim3(FLAT_BLOCK), 0, s,
-                               typed<CI, NoV>(A), typed<CI, NoV>(B), bi, r0, r1, ip, mn, mx);
+                               typed<CI, NoV>(A), typed<CI, NoV>(B), bi, code, n_wide, r0, r1, ip, mn, mx);
         } else if (mn) {
             hipLaunchKernelGGL((k_row_products<true, false, CI>), dim3(flat_grid(panel_nnz)), dim3(FLAT_BLOCK), 0, s,
-                               typed<CI, NoV>(A), typed<CI, NoV>(B), bi, r0, r1, ip, mn, mx);
+                               typed<CI, NoV>(A), typed<CI, NoV>(B), bi, code, n_wide, r0, r1, ip, mn, mx);
         } else {
             hipLaunchKernelGGL((k_row_products<false, false, CI>), dim3(flat_grid(panel_nnz)), dim3(FLAT_BLOCK), 0, s,
-                               typed<CI, NoV>(A), typed<CI, NoV>(B), bi, r0, r1, ip, mn, mx);
+                               typed<CI, NoV>(A), typed<CI, NoV>(B), bi, code, n_wide, r0, r1, ip, mn, mx);
         }
         GM_CHECK_LAUNCH();
     });
