@@ -1639,7 +1639,7 @@ void light_numeric(const Csr &A, const Csr &B, int64_t r0, int bin, const int64_
                         c_col, c_val, err);
             break;
         case LIGHT_R4:
-            launch_rank(k_light_rank_num<896, RB_CAP[4], 1, CI, V>, 896, 1, n, s, a, b, r0, items, n, minc, maxc, c_row_ptr,
+            launch_rank(k_light_rank_num<448, RB_CAP[4], 1, CI, V>, 448, 1, n, s, a, b, r0, items, n, minc, maxc, c_row_ptr,
                         c_col, c_val, err);
             break;
         default: break;

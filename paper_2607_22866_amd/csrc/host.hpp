@@ -348,7 +348,18 @@ constexpr int TILE_MAX_CHUNKS = 1024;
 enum TileBin : uint8_t { TILE_EMPTY = 0, TILE_D_BIG, TILE_D, TILE_M, TILE_L, TILE_S, TILE_T, TILE_NBINS };
 constexpr int TILE_T_MAX = 256, TILE_S_MAX = 1024, TILE_M_MAX = 4096, TILE_D_MAX = 65536;
 constexpr int TILE_MERGE = 2048;  // most products of a region of several chunks
-constexpr int TILE_RANK_MAX = 7168;  // distinct columns of a large region summed by rank (two work groups per CU)
+// distinct columns of the large regions summed by rank, by launch (two 16-wave, four 8-wave, seven 4-wave groups per CU)
+constexpr int TILE_RANK_MAX = 7168, TILE_RANK_MID = 4096, TILE_RANK_MIN = 2048;
+// Launch record of a region.
+struct TileTask {
+    int64_t id;            // c * nh + h
+    int64_t out;           // symbolic: its slot; numeric: its first entry in C
+    uint32_t q0, q1;       // its parts
+    int32_t c;             // first chunk
+    uint32_t want;         // distinct columns (numeric)
+    uint32_t at;           // its place in the symbolic order (bitmap)
+    uint16_t sub0, chunks; // first chunk within its S chunks, number of chunks
+};
 struct TileHeavy {
     int nc = 0;                      // column chunks
     int slog = 0;                    // log2 of the chunks of a row whose lists are adjacent
@@ -370,21 +381,36 @@ struct TileHeavy {
     uint2 *seg = nullptr;                  // non-empty parts by list: start in col / val, length | chunk << 16
     uint32_t *seg_e = nullptr;             // ... and the A entry
     uint32_t *bitmap = nullptr;            // present columns of the regions of more than TILE_MERGE products
+    TileTask *tasks = nullptr;             // the non-empty regions' records (symbolic), by bin
+    int64_t *large_perm = nullptr;         // the regions of more than TILE_MERGE products by numeric bin
     int64_t bins[TILE_NBINS + 1] = {0};
 };
+int64_t tile_items(const TileHeavy &t);  // non-empty regions
+int64_t tile_large(const TileHeavy &t);  // regions of more than TILE_MERGE products
 int tile_chunks(int64_t c_m);
 int64_t tile_scan_words(int64_t n);
 // t.cnt and t.part of the slices (cm: ns * nc + 1 words of scratch)
 void tile_parts(const Csr &B, const int32_t *slice_k, const TileHeavy &t, uint32_t *cm, hipStream_t s);
 void tile_fill(const Csr &B, const int32_t *slice_k, const TileHeavy &t, int32_t *long_list, hipStream_t s);
+// cls[k] = 0 for the non-empty B rows that the heavy rows meet, else 1; then
+// (perm: those rows) their numbers, lengths and places
+void tile_mark(const Csr &A, const Csr &B, const int64_t *heavy_rows, int64_t n_heavy, int64_t r0,
+               const int64_t *a_heavy_ptr, int64_t total, uint8_t *cls, hipStream_t s);
+void tile_slices(const Csr &B, const int64_t *perm, int64_t ns, int32_t *slice_k, int64_t *len, int32_t *k_to_slice,
+                 hipStream_t s);
+// (*n_kept += entries with a non-empty B row)
 void tile_entries(const Csr &A, const int64_t *heavy_rows, int64_t r0, const int32_t *k_to_slice, const TileHeavy &t,
-                  hipStream_t s);
+                  unsigned long long *n_kept, hipStream_t s);
 // region sizes, bins (cls) and part counts (scanned into t.seg_end); *n_seg: all parts
 void tile_regions(const TileHeavy &t, unsigned long long *size, uint8_t *cls, int64_t *n_seg, hipStream_t s);
 void tile_segments(const TileHeavy &t, hipStream_t s);
 void tile_symbolic(const TileHeavy &t, int bin, int64_t *slot, hipStream_t s);
-void tile_numeric(const TileHeavy &t, int bin, const int64_t *heavy_rows, const int64_t *c_row_ptr,
-                  const int64_t *slot, bool ci64, bool v32, void *c_col, void *c_val, int32_t *err, hipStream_t s);
+void tile_tasks(const TileHeavy &t, hipStream_t s);
+void tile_large_bins(const TileHeavy &t, uint8_t *cls, int64_t *scratch, int64_t *large_bins, hipStream_t s);
+// (tasks: tile_items(t) records of scratch; returns the launches)
+int tile_numeric(const TileHeavy &t, const int64_t *large_bins, TileTask *tasks, const int64_t *heavy_rows,
+                 const int64_t *c_row_ptr, const int64_t *slot, bool ci64, bool v32, void *c_col, void *c_val,
+                 int32_t *err, hipStream_t s);
 
 // Per heavy row h: in-place exclusive scan of slot[h*n_slots .. +n_slots),
 // row total into row_nnz[heavy_rows[h]].

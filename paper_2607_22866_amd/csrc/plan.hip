@@ -295,6 +295,8 @@ struct gmagnus_plan_s {
     int n_slots_log2 = 0, slot_width_log2 = 0;
     int64_t *slot = nullptr;
     std::vector<LeafLevel> leaves;
+    int64_t large_bins[5] = {0};      // numeric bins of the tiled path's large regions
+    int64_t *large_bins_dev = nullptr;
     TileHeavy tile;                   // heavy rows accumulated from chunk-major B (tile.nh > 0), instead of leaves
     // value-producing launches of the heavy path in their order, recorded
     // under GMAGNUS_FLAG_KEEP_PATTERN and replayed by gmagnus_update_values
@@ -803,7 +805,7 @@ namespace {
 // Whether the heavy rows are accumulated straight from a chunk-major copy of
 // the B rows they use (tiles.hip) instead of being expanded and split in
 // memory. A caller that forces a hierarchy or an order gets it.
-bool use_tiles(const gmagnus_plan_s *p, int64_t n_slices, int64_t blen_total) {
+bool tiles_possible(const gmagnus_plan_s *p) {
     const gmagnus_options_t &o = p->opts;
     const uint32_t ordered = GMAGNUS_FLAG_PAPER_HISTOGRAM | GMAGNUS_FLAG_PAPER_EXPANSION | GMAGNUS_FLAG_SLICE_SPLIT |
                              GMAGNUS_FLAG_LEVEL_BY_LEVEL;
@@ -812,19 +814,26 @@ bool use_tiles(const gmagnus_plan_s *p, int64_t n_slices, int64_t blen_total) {
     if (p->params.n_levels > 0 && p->params.v_chunks[0] >= GM_WAVE) return false;
     const int64_t H = p->products_heavy, nc = tile_chunks(std::max<int64_t>(p->B.n_cols, 1));
     // part positions and region ids in 31 bits, products of a region in 32
-    if (nc > TILE_MAX_CHUNKS || H >= ((int64_t)1 << 32) || blen_total >= ((int64_t)1 << 31) ||
-        p->n_heavy * nc >= ((int64_t)1 << 31) || p->nnz_heavy * nc >= ((int64_t)1 << 40))
+    if (nc > TILE_MAX_CHUNKS || H >= ((int64_t)1 << 32) || p->n_heavy * nc >= ((int64_t)1 << 31) ||
+        p->nnz_heavy * nc >= ((int64_t)1 << 40))
         return false;
-    if (H < p->nnz_heavy * nc) return false;
+    return H >= p->nnz_heavy * nc;
+}
+
+// ... and whether it fits, with the slices known.
+bool use_tiles(const gmagnus_plan_s *p, int64_t n_slices, int64_t blen_total) {
+    const int64_t H = p->products_heavy, nc = tile_chunks(std::max<int64_t>(p->B.n_cols, 1));
+    if (blen_total >= ((int64_t)1 << 31)) return false;
     const int64_t bytes = n_slices * nc * 10 + blen_total * (2 + p->vsize) + p->nnz_heavy * (8 + p->vsize) +
-                          p->n_heavy * nc * 34 + p->nnz_heavy * nc * 12 + 2 * H;
+                          p->n_heavy * nc * 74 + p->nnz_heavy * nc * 12 + 2 * H;
     return bytes <= H * (4 + p->vsize);
 }
 
 // The tiled heavy path from the slices on: chunk-major B, region sizes and
 // bins, symbolic of every region, fragment offsets.
 template <class ValuesStep>
-void tiled_symbolic(gmagnus_plan_s *p, const SliceArrays &sl, int64_t blen_total, ValuesStep &&values_step) {
+void tiled_symbolic(gmagnus_plan_s *p, const SliceArrays &sl, int64_t blen_total, const int64_t *n_kept,
+                    ValuesStep &&values_step) {
     Workspace &ws = *p->ws;
     const hipStream_t s = p->s_heavy;
     TileHeavy &t = p->tile;
@@ -835,6 +844,7 @@ void tiled_symbolic(gmagnus_plan_s *p, const SliceArrays &sl, int64_t blen_total
     const int64_t regions = t.nh * t.ncp;
     p->n_slots = t.ncp;
     int32_t *long_list;
+    int64_t n_seg;
     {
         Timed tm(p, GMAGNUS_K_HISTOGRAM, s);
         t.cnt = ws.alloc<uint16_t>(t.ns * t.nc);
@@ -873,9 +883,14 @@ void tiled_symbolic(gmagnus_plan_s *p, const SliceArrays &sl, int64_t blen_total
         partition_u8(cls, regions, TILE_NBINS, t.items, nullptr, bins, sc, s);
         fill<int64_t>(p->slot, 0, regions, s);
         int64_t got[TILE_NBINS + 2];
-        read_bins(bins, TILE_NBINS + 1, got, s);
+        {
+            HostReads r(s);
+            r.add(bins, TILE_NBINS + 2, got);
+            r.add(n_kept, 1, &p->info.nnz_a_heavy);
+            r.wait();
+        }
         std::copy(got, got + TILE_NBINS + 1, t.bins);
-        const int64_t n_seg = got[TILE_NBINS + 1];
+        n_seg = got[TILE_NBINS + 1];
         ws.free(size);
         ws.free(cls);
         ws.free(bins);
@@ -886,6 +901,8 @@ void tiled_symbolic(gmagnus_plan_s *p, const SliceArrays &sl, int64_t blen_total
         tile_segments(t, s);
         ws.free(t.cnt);
         t.bitmap = ws.alloc<uint32_t>((t.bins[TILE_M + 1] - t.bins[TILE_D_BIG]) * (TILE_COLS / 32));
+        t.tasks = ws.alloc<TileTask>(tile_items(t));
+        tile_tasks(t, s);
     }
     {
         Timed tm(p, GMAGNUS_K_CHUNK_SYM, s);
@@ -895,7 +912,18 @@ void tiled_symbolic(gmagnus_plan_s *p, const SliceArrays &sl, int64_t blen_total
             if (n) p->info.kernel_launches[GMAGNUS_K_CHUNK_SYM] += 1;
             (b <= TILE_D ? p->info.n_leaves_dense : p->info.n_leaves_rank) += n;
         }
-        add_bytes(p, GMAGNUS_K_CHUNK_SYM, 2.0 * p->products_heavy + 12.0 * (double)t.n_ent * t.nc);
+        add_bytes(p, GMAGNUS_K_CHUNK_SYM, 2.0 * p->products_heavy + 8.0 * (double)n_seg);
+    }
+    {
+        Timed tm(p, GMAGNUS_K_SETUP, s);
+        const int64_t n = tile_large(t);
+        t.large_perm = ws.alloc<int64_t>(n);
+        p->large_bins_dev = ws.alloc<int64_t>(5);
+        uint8_t *cls = ws.alloc<uint8_t>(n);
+        int64_t *sc = ws.alloc<int64_t>(partition_scratch_elems(n, 4));
+        tile_large_bins(t, cls, sc, p->large_bins_dev, s);
+        ws.free(cls);
+        ws.free(sc);
     }
     {
         Timed tm(p, GMAGNUS_K_ROWPTR, s);
@@ -963,6 +991,7 @@ void heavy_symbolic(gmagnus_plan_s *p) {
     int64_t *row_len, *a_heavy_ptr, *scratch;
     int64_t nnz_heavy_all = 0, blen_total = 0;
     bool tiled = false;
+    int64_t *n_kept = nullptr;  // tiled: heavy entries with a non-empty B row
     {
         Timed t(p, GMAGNUS_K_CSC, s);
         row_len = ws.alloc<int64_t>(nh);
@@ -973,6 +1002,68 @@ void heavy_symbolic(gmagnus_plan_s *p) {
         gather_row_len(p->A.rp, p->heavy_rows, nh, p->r0, row_len, s);
         scan_i64(row_len, nh, a_heavy_ptr, scratch, s);
         nnz_heavy_all = p->nnz_heavy;  // summed over the same rows at plan time (checked below)
+        if (tiles_possible(p)) {
+            ws.hold(false);  // (what the other paths do not need goes back when they are taken)
+            uint8_t *kcls = ws.alloc<uint8_t>(n_k);
+            int64_t *kperm = ws.alloc<int64_t>(n_k);
+            int64_t *kb = ws.alloc<int64_t>(3);
+            tile_mark(p->A, p->B, heavy_rows, nh, r0, a_heavy_ptr, nnz_heavy_all, kcls, s);
+            partition_u8(kcls, n_k, 2, kperm, nullptr, kb, scratch, s);
+            int64_t kbh[3];
+            read_bins(kb, 2, kbh, s);
+            sl.n_slices = kbh[1];
+            sl.slice_k = ws.alloc<int32_t>(sl.n_slices);
+            int64_t *len = ws.alloc<int64_t>(sl.n_slices), *len_scan = ws.alloc<int64_t>(sl.n_slices + 1);
+            int64_t *sc2 = ws.alloc<int64_t>(scan_scratch_elems(sl.n_slices));
+            int32_t *k_to_slice = ws.alloc<int32_t>(p->B.n_rows);
+            tile_slices(p->B, kperm, sl.n_slices, sl.slice_k, len, k_to_slice, s);
+            scan_i64(len, sl.n_slices, len_scan, sc2, s);
+            int64_t a_end = 0;
+            {
+                HostReads r(s);
+                r.add(len_scan + sl.n_slices, 1, &blen_total);
+                r.add(a_heavy_ptr + nh, 1, &a_end);
+                r.wait();
+            }
+            GM_REQUIRE(a_end == nnz_heavy_all, GMAGNUS_ERROR_HIP, "heavy rows' entries disagree with the plan's count");
+            ws.free(kcls);
+            ws.free(kperm);
+            ws.free(kb);
+            ws.free(len);
+            ws.free(len_scan);
+            ws.free(sc2);
+            tiled = use_tiles(p, sl.n_slices, blen_total);
+            if (!tiled) {
+                ws.free(sl.slice_k);
+                ws.free(k_to_slice);
+                sl = SliceArrays{};
+            }
+            ws.hold(keep);
+            if (tiled) {
+                TileHeavy &t = p->tile;
+                t.nc = tile_chunks(p->B.n_cols);
+                t.ns = sl.n_slices;
+                t.nh = nh;
+                t.n_ent = nnz_heavy_all;
+                t.n_elems = blen_total;
+                t.a_ptr = a_heavy_ptr;
+                t.es = ws.alloc<int32_t>(nnz_heavy_all);
+                t.eh = ws.alloc<int32_t>(nnz_heavy_all);
+                t.ea = ws.alloc_bytes(VS * nnz_heavy_all);
+                n_kept = ws.alloc<int64_t>(1);
+                fill<int64_t>(n_kept, 0, 1, s);
+                const TileHeavy tv = t;
+                int64_t *kept = n_kept;
+                values_step([=](const Csr &A, const Csr &, hipStream_t st) {
+                    tile_entries(A, heavy_rows, r0, k_to_slice, tv, (unsigned long long *)kept, st);
+                });
+                ws.free(k_to_slice);
+                ws.free(row_len);
+                ws.free(scratch);
+                add_bytes(p, GMAGNUS_K_CSC, (CS + VS) * nnz_heavy_all + (8.0 + VS) * nnz_heavy_all + 8.0 * (n_k + sl.n_slices));
+            }
+        }
+        if (!tiled) {
         int64_t *colcnt = ws.alloc<int64_t>(n_k);
         csc_count(p->A, p->B, p->heavy_rows, nh, p->r0, a_heavy_ptr, nnz_heavy_all, colcnt, s);
         uint8_t *kcls = ws.alloc<uint8_t>(n_k);
@@ -1012,23 +1103,7 @@ void heavy_symbolic(gmagnus_plan_s *p) {
         GM_REQUIRE(tot[1] == H, GMAGNUS_ERROR_HIP, "slice products disagree with the row products");
         GM_REQUIRE(tot[3] == nnz_heavy_all, GMAGNUS_ERROR_HIP, "heavy rows' entries disagree with the plan's count");
         int64_t *cursor = nullptr;
-        tiled = use_tiles(p, sl.n_slices, blen_total);
-        if (tiled) {
-            TileHeavy &t = p->tile;
-            t.nc = tile_chunks(p->B.n_cols);
-            t.ns = sl.n_slices;
-            t.nh = nh;
-            t.n_ent = nnz_heavy_all;
-            t.n_elems = blen_total;
-            t.a_ptr = a_heavy_ptr;
-            t.es = ws.alloc<int32_t>(nnz_heavy_all);
-            t.eh = ws.alloc<int32_t>(nnz_heavy_all);
-            t.ea = ws.alloc_bytes(VS * nnz_heavy_all);
-            const TileHeavy tv = t;
-            values_step([=](const Csr &A, const Csr &, hipStream_t st) {
-                tile_entries(A, heavy_rows, r0, k_to_slice, tv, st);
-            });
-        } else if (!rows_order) {
+        if (!rows_order) {
             cursor = ws.alloc<int64_t>(std::max<int64_t>(sl.n_slices, 1));
             sl.row_h = ws.alloc<int32_t>(sl.nnz);
             sl.a_val = ws.alloc_bytes(VS * sl.nnz);
@@ -1047,7 +1122,7 @@ void heavy_symbolic(gmagnus_plan_s *p) {
                 heavy_entries(A, B, heavy_rows, nh, r0, a_heavy_ptr, nnz_heavy_all, k_to_slice, ent, st);
             });
         }
-        if (P.n_levels > 0 && !paper_hist && !tiled) {
+        if (P.n_levels > 0 && !paper_hist) {
             // level-0 (row, chunk) counts from the structure of A~ and B
             Timed t2(p, GMAGNUS_K_HISTOGRAM, s);
             const int nc0 = P.v_chunks[0];
@@ -1087,17 +1162,18 @@ void heavy_symbolic(gmagnus_plan_s *p) {
         ws.free(k_to_slice);
         ws.free(sc2);
         ws.free(row_len);
-        if (rows_order || tiled)
+        if (rows_order)
             a_heavy_keep = a_heavy_ptr;  // region records need the row pointers of A~
         else
             ws.free(a_heavy_ptr);
         ws.free(scratch);
         add_bytes(p, GMAGNUS_K_CSC, (CS + VS) * nnz_heavy_all + (4.0 + VS) * sl.nnz + 8.0 * (p->A.n_cols + sl.n_slices));
+        }
     }
     p->info.n_slices = sl.n_slices;
     p->info.nnz_a_heavy = sl.nnz;
     if (tiled) {
-        tiled_symbolic(p, sl, blen_total, values_step);
+        tiled_symbolic(p, sl, blen_total, n_kept, values_step);
         return;
     }
 
@@ -1577,6 +1653,7 @@ void do_symbolic(gmagnus_plan_s *p, int64_t *c_row_ptr, int64_t *c_nnz) {
         HostReads r(p->stream);
         r.add(c_row_ptr + n, 1, &p->c_nnz);
         if (hs) r.add(hs + p->n_heavy, 1, &p->info.c_nnz_heavy);
+        if (p->large_bins_dev) r.add(p->large_bins_dev, 5, p->large_bins);
         r.wait();
     }
     ws.free(hs);
@@ -1610,10 +1687,11 @@ void do_numeric(gmagnus_plan_s *p, const int64_t *c_row_ptr, void *c_col, void *
         const hipStream_t s = p->s_heavy;
         Timed t(p, GMAGNUS_K_CHUNK_NUM, s);
         if (p->tile.nh > 0) {
-            for (int b = TILE_D_BIG; b < TILE_NBINS; ++b) {
-                tile_numeric(p->tile, b, p->heavy_rows, c_row_ptr, p->slot, p->B.ci64, p->B.v32, c_col, c_val, p->err, s);
-                if (p->tile.bins[b + 1] > p->tile.bins[b]) p->info.kernel_launches[GMAGNUS_K_CHUNK_NUM] += 1;
-            }
+            TileTask *tasks = p->ws->alloc<TileTask>(tile_items(p->tile));
+            p->info.kernel_launches[GMAGNUS_K_CHUNK_NUM] +=
+                tile_numeric(p->tile, p->large_bins, tasks, p->heavy_rows, c_row_ptr, p->slot, p->B.ci64, p->B.v32, c_col,
+                             c_val, p->err, s);
+            p->ws->free(tasks);
             add_bytes(p, GMAGNUS_K_CHUNK_NUM, (2.0 + p->vsize) * p->products_heavy);
         }
         for (auto &lv : p->leaves) {

@@ -135,7 +135,11 @@ GM_DEV uint32_t rank_region(const Src &src, uint32_t width, RankLds<BLOCK, CAP, 
         const int64_t q = j + tid;
         uint32_t len = 0, aux = 0;
         int64_t st = 0;
-        if (q < np) len = src.part(q, &st, &aux);
+        V scale = (V)0;
+        if (q < np) {
+            len = src.part(q, &st, &aux);
+            if (NUM) scale = src.scale(q);  // (in flight with the part)
+        }
         uint32_t tot;
         // products in the low, non-empty parts in the high 16 bits (at most CAP of each)
         const uint32_t ex = region_scan<BLOCK>(len ? (len | 0x10000u) : 0u, L.scan[par], &tot);
@@ -143,7 +147,7 @@ GM_DEV uint32_t rank_region(const Src &src, uint32_t width, RankLds<BLOCK, CAP, 
         const uint32_t off = n + (ex & 0xffffu), p = nparts + (ex >> 16);
         if (len > 0 && off + len <= (uint32_t)CAP) {
             L.x[p] = src.pack(st, off, aux);
-            if (NUM) L.vals[p] = src.scale(q);
+            if (NUM) L.vals[p] = scale;
             __hip_atomic_fetch_or(&L.ends[(off + len - 1) >> 5].bits, 1u << ((off + len - 1) & 31), __ATOMIC_RELAXED,
                                   __HIP_MEMORY_SCOPE_WORKGROUP);
         }

@@ -251,6 +251,8 @@ constexpr int TF_WAVES = 4;
 constexpr int64_t TF_LONG = 2048;  // longer rows are copied in pieces of this many elements by many waves
 
 // Rows of at most TF_LONG elements, one wave each; longer ones are listed.
+// (A work group per 64 consecutive slices, whose parts share lines in every
+// chunk: 0.79 instead of 0.64 ms, the rows' lengths being too uneven.)
 template <typename CI, typename V>
 __global__ __launch_bounds__(TF_WAVES * GM_WAVE) void k_tile_fill(CsrV<CI, V> B, const int32_t *slice_k, int64_t ns,
                                                                   int nc, const uint32_t *part, int64_t n_elems,
@@ -305,14 +307,58 @@ __global__ __launch_bounds__(TF_WAVES * GM_WAVE) void k_tile_fill_long(CsrV<CI, 
 template <typename CI, typename V>
 __global__ void k_tile_entries(CsrV<CI, V> A, const int64_t *heavy_rows, int64_t n_heavy, int64_t r0,
                                const int64_t *a_heavy_ptr, int64_t total, const int32_t *k_to_slice, int32_t *es,
-                               int32_t *eh, V *ea) {
+                               int32_t *eh, V *ea, unsigned long long *n_kept) {
+    __shared__ int32_t sm[256 / GM_WAVE];
+    int32_t kept = 0;
     for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < total;
          e += (int64_t)gridDim.x * blockDim.x) {
         const int64_t h = find_row(a_heavy_ptr, 0, n_heavy + 1, e);
         const int64_t j = A.rp[r0 + heavy_rows[h]] + (e - a_heavy_ptr[h]);
-        es[e] = k_to_slice[(int64_t)A.ci[j]];
+        const int32_t sl = k_to_slice[(int64_t)A.ci[j]];
+        es[e] = sl;
         eh[e] = (int32_t)h;
         ea[e] = A.v[j];
+        kept += sl >= 0;
+    }
+    kept = block_reduce_sum<256>(kept, sm);
+    if (threadIdx.x == 0 && kept) atomicAdd(n_kept, (unsigned long long)kept);
+}
+
+// cls[k] = 0 for the B rows that the heavy rows' entries meet and that are not
+// empty (the slices), by plain stores of one value (counting each slice's
+// entries with atomics, as the slice order needs, takes 0.43 ms for 2e6 entries
+// of R-MAT scale 17, whose hub columns stand in most rows).
+template <typename CI>
+__global__ void k_tile_mark(CsrV<CI, NoV> A, const int64_t *b_rp, const int64_t *heavy_rows, int64_t n_heavy, int64_t r0,
+                            const int64_t *a_heavy_ptr, int64_t total, uint8_t *cls) {
+    constexpr int U = 8;
+    const int64_t e0 = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) * U;
+    if (e0 >= total) return;
+    int64_t h = find_row(a_heavy_ptr, 0, n_heavy + 1, e0), h_end = a_heavy_ptr[h + 1];
+    int64_t base = A.rp[r0 + heavy_rows[h]] - a_heavy_ptr[h];
+    int64_t k[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int64_t e = e0 + u < total ? e0 + u : total - 1;
+        while (e >= h_end) {
+            ++h;
+            h_end = a_heavy_ptr[h + 1];
+            base = A.rp[r0 + heavy_rows[h]] - a_heavy_ptr[h];
+        }
+        k[u] = (int64_t)A.ci[base + e];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+        if (cls[k[u]] && b_rp[k[u] + 1] > b_rp[k[u]]) cls[k[u]] = 0;
+}
+
+__global__ void k_tile_slices(const int64_t *b_rp, const int64_t *perm, int64_t ns, int32_t *slice_k, int64_t *len,
+                              int32_t *k_to_slice) {
+    for (int64_t s = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; s < ns; s += (int64_t)gridDim.x * blockDim.x) {
+        const int64_t k = perm[s];
+        slice_k[s] = (int32_t)k;
+        len[s] = b_rp[k + 1] - b_rp[k];
+        k_to_slice[k] = (int32_t)s;
     }
 }
 
@@ -379,7 +425,7 @@ __global__ __launch_bounds__(TE_BLOCK) void k_tile_sizes(const int32_t *es, cons
 // chunk at a time with an entry per lane, so that a row's parts go out as one
 // contiguous store (writing them a thread per chunk, 8 bytes at a time into
 // as many lists as threads, took 3.1 ms instead of 1.9 for 1e8 parts).
-constexpr int TL_BLOCK = 256, TL_C = 128, TL_U = 8;
+constexpr int TL_BLOCK = 256, TL_C = 64, TL_U = 8;
 __global__ __launch_bounds__(TL_BLOCK) void k_tile_lists(const int32_t *es, const int32_t *eh, int64_t n_ent,
                                                          const uint16_t *cnt, const uint32_t *part, int nc, int64_t nh,
                                                          int slog, uint32_t *cursor, uint2 *seg, uint32_t *seg_e) {
@@ -498,41 +544,63 @@ __global__ void k_tile_classes(const unsigned long long *size, int64_t nh, int64
 __global__ void k_tile_total(const uint32_t *v, int64_t *out) { *out = (int64_t)*v; }
 
 // ------------------------------------------------------------- accumulation
-// What a region's kernel reads.
+// What a region's kernel reads. The regions' records are built in launch
+// order beforehand, so that a region starts from one load instead of a chain
+// (id -> chunks -> list ends -> parts); with the scales loaded beside the parts
+// the small regions' numeric kernels went from 1.92 to 1.70 ms for a panel of
+// 2e9 R-MAT 22 products and from 6.9 to 6.0 for 1.5e9 of R-MAT 23.
 template <typename V>
 struct TileArgs {
     const uint16_t *col;
     const V *val;
     const uint2 *seg;          // the regions' parts: start, length | chunk within its S chunks << 16
     const uint32_t *seg_e;     // A entry of a part
-    const uint32_t *seg_end;   // one past list l's last part (list l starts at seg_end[l - 1])
     const V *ea;
-    int64_t nh;
-    int slog;                  // log2 S
-    const uint8_t *grp;        // chunks of a region
-    const int64_t *items;      // region ids c * nh + h of the bin
-    int64_t n_items;
-    uint32_t *bitmap;          // TWORDS words per item (bins of more than TILE_MERGE products), or null
+    const TileTask *tasks;     // the bin's regions
+    int64_t n;
+    uint32_t *bitmap;          // TWORDS words per region of more than TILE_MERGE products
 };
 
-struct Region {
-    int64_t c, h;       // first chunk, heavy row
-    uint32_t q0, q1;    // parts
-    int chunks;
-    uint32_t sub0;      // first chunk within its S chunks
-};
-template <typename V>
-GM_DEV Region region_at(const TileArgs<V> &t, int64_t i) {
-    Region g;
-    const int64_t id = t.items[i];
-    g.c = id / t.nh;
-    g.h = id - g.c * t.nh;
-    g.chunks = t.grp[id];
-    g.sub0 = (uint32_t)(g.c & ((1 << t.slog) - 1));
-    const int64_t l = list_of(g.c, g.h, t.nh, t.slog);
-    g.q0 = l > 0 ? t.seg_end[l - 1] : 0u;
-    g.q1 = t.seg_end[l + g.chunks - 1];
-    return g;
+// Records of the regions items[0 .. n) (ids c * nh + h): symbolic.
+__global__ void k_tile_tasks_sym(const int64_t *items, int64_t n, const uint8_t *grp, const uint32_t *seg_end,
+                                 int64_t nh, int64_t ncp, int slog, TileTask *tasks) {
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+        const int64_t id = items[i], c = id / nh, h = id - c * nh;
+        const int64_t l = list_of(c, h, nh, slog);
+        TileTask t;
+        t.id = id;
+        t.out = h * ncp + c;
+        t.q0 = l > 0 ? seg_end[l - 1] : 0u;
+        t.q1 = seg_end[l + grp[id] - 1];
+        t.c = (int32_t)c;
+        t.want = 0;
+        t.at = (uint32_t)i;
+        t.sub0 = (uint16_t)(c & ((1 << slog) - 1));
+        t.chunks = grp[id];
+        tasks[i] = t;
+    }
+}
+
+// ... numeric: the place in C and the distinct columns, the first n_large
+// regions in the order of `perm` (by distinct columns).
+__global__ void k_tile_tasks_num(const TileTask *sym, int64_t n, const int64_t *perm, int64_t n_large, int64_t nh,
+                                 const uint32_t *nnz, const int64_t *slot, const int64_t *heavy_rows,
+                                 const int64_t *c_row_ptr, TileTask *tasks) {
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+        TileTask t = sym[i < n_large ? perm[i] : i];
+        const int64_t h = t.id - (int64_t)t.c * nh;
+        t.want = nnz[t.id];
+        t.out = c_row_ptr[heavy_rows[h]] + slot[t.out];
+        tasks[i] = t;
+    }
+}
+
+// Numeric bin of the large regions by distinct columns.
+__global__ void k_tile_large_classes(const TileTask *sym, int64_t n, const uint32_t *nnz, uint8_t *cls) {
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+        const uint32_t z = nnz[sym[i].id];
+        cls[i] = z > TILE_RANK_MAX ? 0 : z > TILE_RANK_MID ? 1 : z > TILE_RANK_MIN ? 2 : 3;
+    }
 }
 
 // Calls f(column, product) for the parts held one per lane (start
@@ -599,7 +667,7 @@ struct LongParts {
 // by every thread; the list must be empty (n = 0) and a barrier behind it;
 // ends without a barrier.
 template <int NW, bool NUM, typename V, class F>
-GM_DEV void tile_products(const TileArgs<V> &t, const Region &g, uint32_t *ends, LongParts<V> *lp, F &&f) {
+GM_DEV void tile_products(const TileArgs<V> &t, const TileTask &g, uint32_t *ends, LongParts<V> *lp, F &&f) {
     const int lane = threadIdx.x & (GM_WAVE - 1);
     const uint32_t w = threadIdx.x / GM_WAVE;
     for (uint32_t jb = g.q0 + w; jb < g.q1; jb += GM_WAVE * NW) {
@@ -659,12 +727,12 @@ struct TileParts {
     typedef uint32_t Pos;
     typedef uint32_t Col;
     const TileArgs<V> &t;
-    const Region &g;
+    const TileTask &g;
     GM_DEV int64_t np() const { return g.q1 - g.q0; }
     GM_DEV uint32_t part(int64_t q, int64_t *st, uint32_t *aux) const {
         const uint2 sg = t.seg[g.q0 + q];
         *st = sg.x;
-        *aux = ((sg.y >> 16) - g.sub0) << TILE_LOG2;
+        *aux = ((sg.y >> 16) - (uint32_t)g.sub0) << TILE_LOG2;
         return sg.y & 0xffffu;
     }
     GM_DEV V scale(int64_t q) const { return t.ea[t.seg_e[g.q0 + q]]; }
@@ -680,25 +748,25 @@ struct TileParts {
 
 // Symbolic of small regions.
 template <int BLOCK, int CAP, int REGS>
-__global__ __launch_bounds__(BLOCK * REGS) void k_tile_sym_small(TileArgs<float> t, uint32_t *nnz, int64_t ncp,
+__global__ __launch_bounds__(BLOCK * REGS) void k_tile_sym_small(TileArgs<float> t, uint32_t *nnz,
                                                                  int64_t *slot) {
     static_assert(REGS == 1 || BLOCK == GM_WAVE, "several regions per work group are one wave each");
     __shared__ __align__(16) RankLds<BLOCK, CAP, false, float> L[REGS];
     const int reg = REGS > 1 ? threadIdx.x / GM_WAVE : 0, tid = REGS > 1 ? threadIdx.x & (GM_WAVE - 1) : threadIdx.x;
     const int64_t i = blockIdx.x * (int64_t)REGS + reg;
-    if (i >= t.n_items) return;  // the whole wave (one region: the whole work group)
-    const Region g = region_at(t, i);
+    if (i >= t.n) return;  // the whole wave (one region: the whole work group)
+    const TileTask g = t.tasks[i];
     const uint32_t n = rank_region<BLOCK, CAP, false, float>(TileParts<float>{t, g}, (uint32_t)g.chunks << TILE_LOG2, L[reg],
                                                              tid, [](uint32_t, uint32_t) {});
     if (tid == 0) {
-        nnz[g.c * t.nh + g.h] = (uint32_t)n;
-        slot[g.h * ncp + g.c] = n;
+        nnz[g.id] = (uint32_t)n;
+        slot[g.out] = n;
     }
 }
 
 // Symbolic, one work group per region; the bitmap is kept for the numeric phase.
 template <int BLOCK>
-__global__ __launch_bounds__(BLOCK) void k_tile_sym(TileArgs<float> t, uint32_t *nnz, int64_t ncp, int64_t *slot) {
+__global__ __launch_bounds__(BLOCK) void k_tile_sym(TileArgs<float> t, uint32_t *nnz, int64_t *slot) {
     constexpr int NW = BLOCK / GM_WAVE;
     __shared__ __align__(16) uint32_t bits[TWORDS];
     __shared__ __align__(16) uint32_t ends[NW][TENDS];
@@ -706,7 +774,7 @@ __global__ __launch_bounds__(BLOCK) void k_tile_sym(TileArgs<float> t, uint32_t 
     __shared__ int32_t scan[NW];
     for (int q = threadIdx.x; q < TWORDS; q += BLOCK) bits[q] = 0;
     if (threadIdx.x == 0) lp.n = 0;
-    const Region g = region_at(t, blockIdx.x);
+    const TileTask g = t.tasks[blockIdx.x];
     __syncthreads();
     tile_products<NW, false, float>(t, g, ends[threadIdx.x / GM_WAVE], &lp,
                                     [&](uint32_t c, float) {
@@ -716,7 +784,7 @@ __global__ __launch_bounds__(BLOCK) void k_tile_sym(TileArgs<float> t, uint32_t 
                                     });
     __syncthreads();
     int32_t n = 0;
-    uint32_t *bm = t.bitmap + blockIdx.x * (int64_t)TWORDS;
+    uint32_t *bm = t.bitmap + g.at * (int64_t)TWORDS;
     for (int q = threadIdx.x; q < TWORDS; q += BLOCK) {
         const uint32_t x = bits[q];
         bm[q] = x;
@@ -724,23 +792,18 @@ __global__ __launch_bounds__(BLOCK) void k_tile_sym(TileArgs<float> t, uint32_t 
     }
     n = block_reduce_sum<BLOCK>(n, scan);
     if (threadIdx.x == 0) {
-        nnz[g.c * t.nh + g.h] = (uint32_t)n;
-        slot[g.h * ncp + g.c] = n;
+        nnz[g.id] = (uint32_t)n;
+        slot[g.out] = n;
     }
 }
 
-// Where a region's entries of C go.
+// C's arrays.
 template <typename CI, typename V>
 struct TileOut {
-    const int64_t *heavy_rows, *c_row_ptr, *slot;  // slot: exclusive offsets within the row
-    const uint32_t *nnz;
-    int64_t ncp;
     CI *c_col;
     V *c_val;
     int32_t *err;
-    GM_DEV int want(const Region &g, int64_t nh) const { return (int)nnz[g.c * nh + g.h]; }
-    GM_DEV int64_t dst(const Region &g) const { return c_row_ptr[heavy_rows[g.h]] + slot[g.h * ncp + g.c]; }
-    GM_DEV CI base(const Region &g) const { return (CI)g.c << TILE_LOG2; }
+    GM_DEV CI base(const TileTask &g) const { return (CI)g.c << TILE_LOG2; }
 };
 
 // Numeric of small regions.
@@ -750,11 +813,11 @@ __global__ __launch_bounds__(BLOCK * REGS) void k_tile_num_small(TileArgs<V> t, 
     __shared__ __align__(16) RankLds<BLOCK, CAP, true, V> L_all[REGS];
     const int reg = REGS > 1 ? threadIdx.x / GM_WAVE : 0, tid = REGS > 1 ? threadIdx.x & (GM_WAVE - 1) : threadIdx.x;
     const int64_t i = blockIdx.x * (int64_t)REGS + reg;
-    if (i >= t.n_items) return;  // the whole wave (one region: the whole work group)
-    const Region g = region_at(t, i);
+    if (i >= t.n) return;  // the whole wave (one region: the whole work group)
+    const TileTask g = t.tasks[i];
     RankLds<BLOCK, CAP, true, V> &L = L_all[reg];
-    const int want = o.want(g, t.nh);
-    const int64_t dst = o.dst(g);
+    const int want = (int)g.want;
+    const int64_t dst = g.out;
     const CI cb = o.base(g);
     const int total = (int)rank_region<BLOCK, CAP, true, V>(TileParts<V>{t, g}, (uint32_t)g.chunks << TILE_LOG2, L, tid,
                                                             [&](uint32_t rk, uint32_t c) {
@@ -787,27 +850,42 @@ GM_DEV void rank_columns(const RankWord *words, uint16_t *cols, int w0, int n) {
 }
 
 // Numeric of larger regions of at most CAP distinct columns: the ranks come
-// from the bitmap the symbolic phase kept, so the products are read once.
-// (Regions of more columns than CAP are left to the dense kernel.)
+// from the bitmap the symbolic phase kept, so the products are read once. One
+// launch per size of the value array, so that a small one leaves room for
+// more work groups on a CU. (Panel of 2e9 R-MAT 22 products, these launches
+// and the dense one: 6.65 ms with 1024 threads for all regions of more than
+// 4096 products, each kernel leaving the other's regions at once; 5.58 ms with
+// the regions sorted into the four launches.)
 template <int BLOCK, int CAP, typename CI, typename V>
 __global__ __launch_bounds__(BLOCK) void k_tile_num_rank(TileArgs<V> t, TileOut<CI, V> o) {
-    constexpr int NW = BLOCK / GM_WAVE;
+    constexpr int NW = BLOCK / GM_WAVE, WPT = TWORDS > BLOCK ? TWORDS / BLOCK : 1;
+    static_assert(WPT == 1 || WPT * BLOCK == TWORDS, "bitmap words per thread");
     __shared__ __align__(16) RankWord words[TWORDS];
     __shared__ __align__(16) V vals[CAP];
     __shared__ __align__(16) uint32_t ends[NW][TENDS];
     __shared__ LongParts<V> lp;
     __shared__ int32_t scan[NW];
-    const int tid = threadIdx.x;
-    const Region g = region_at(t, blockIdx.x);
-    const int want = o.want(g, t.nh);
-    if (want > CAP) return;  // uniform
-    const uint32_t bw = tid < TWORDS ? t.bitmap[blockIdx.x * (int64_t)TWORDS + tid] : 0u;
+    const int tid = threadIdx.x, w0 = tid * WPT;
+    const TileTask g = t.tasks[blockIdx.x];
+    const int want = (int)g.want;
+    if (want > CAP) return;  // (uniform; such regions are in another bin)
+    uint32_t bw[WPT];
+    int32_t cnt = 0;
+#pragma unroll
+    for (int q = 0; q < WPT; ++q) {
+        bw[q] = w0 + q < TWORDS ? t.bitmap[g.at * (int64_t)TWORDS + w0 + q] : 0u;
+        cnt += __popc(bw[q]);
+    }
     for (int q = tid; q < want; q += BLOCK) vals[q] = (V)0;
     if (tid == 0) lp.n = 0;
-    static_assert(BLOCK >= TWORDS, "one bitmap word per thread");
     int32_t total;
-    const int32_t rank = block_excl_scan<BLOCK>((int32_t)__popc(bw), scan, &total);
-    if (tid < TWORDS) words[tid] = RankWord{bw, (uint32_t)rank};
+    uint32_t rank = (uint32_t)block_excl_scan<BLOCK>(cnt, scan, &total);
+#pragma unroll
+    for (int q = 0; q < WPT; ++q)
+        if (w0 + q < TWORDS) {
+            words[w0 + q] = RankWord{bw[q], rank};
+            rank += (uint32_t)__popc(bw[q]);
+        }
     __syncthreads();
     tile_products<NW, true, V>(t, g, ends[tid / GM_WAVE], &lp,
                                [&](uint32_t c, V v) { rank_add<CAP>(words, vals, c, v); });
@@ -815,18 +893,18 @@ __global__ __launch_bounds__(BLOCK) void k_tile_num_rank(TileArgs<V> t, TileOut<
     if (tid == 0 && total != want) atomicOr(o.err, 4);
     const int m = total < want ? total : want;
     const CI cb = o.base(g);
-    const int64_t dst = o.dst(g);
+    const int64_t dst = g.out;
     for (int q = tid; q < m; q += BLOCK) o.c_val[dst + q] = vals[q];
     __syncthreads();  // the values' place is reused for the columns
     uint16_t *cols = (uint16_t *)vals;
-    if (tid < TWORDS) rank_columns<CAP>(words, cols, tid, 1);
+    if (w0 < TWORDS) rank_columns<CAP>(words, cols, w0, WPT);
     __syncthreads();
     for (int q = tid; q < m; q += BLOCK) o.c_col[dst + q] = cb + (CI)cols[q];
 }
 
-// Numeric of regions of more than MIN distinct columns: one value per column
-// of the chunk.
-template <int BLOCK, int MIN, typename CI, typename V>
+// Numeric of regions of more than TILE_RANK_MAX distinct columns: one value per
+// column of the chunk.
+template <int BLOCK, typename CI, typename V>
 __global__ __launch_bounds__(BLOCK) void k_tile_num_dense(TileArgs<V> t, TileOut<CI, V> o) {
     constexpr int NW = BLOCK / GM_WAVE;
     constexpr int SPAN = TILE_COLS / NW;  // columns a wave writes out
@@ -836,11 +914,10 @@ __global__ __launch_bounds__(BLOCK) void k_tile_num_dense(TileArgs<V> t, TileOut
     __shared__ LongParts<V> lp;
     __shared__ int32_t scan[NW];
     const int tid = threadIdx.x, lane = tid & (GM_WAVE - 1), w = tid / GM_WAVE;
-    const Region g = region_at(t, blockIdx.x);
-    const int want = o.want(g, t.nh);
-    if (want <= MIN) return;  // uniform
+    const TileTask g = t.tasks[blockIdx.x];
+    const int want = (int)g.want;
     static_assert(BLOCK >= TWORDS, "one bitmap word per thread");
-    if (tid < TWORDS) bits[tid] = t.bitmap[blockIdx.x * (int64_t)TWORDS + tid];
+    if (tid < TWORDS) bits[tid] = t.bitmap[g.at * (int64_t)TWORDS + tid];
     for (int q = tid; q < TILE_COLS; q += BLOCK) vals[q] = (V)0;
     if (tid == 0) lp.n = 0;
     __syncthreads();
@@ -857,7 +934,7 @@ __global__ __launch_bounds__(BLOCK) void k_tile_num_dense(TileArgs<V> t, TileOut
     at = __builtin_amdgcn_readfirstlane(at);
     if (tid == 0 && total != want) atomicOr(o.err, 2);
     const CI cb = o.base(g);
-    const int64_t dst = o.dst(g);
+    const int64_t dst = g.out;
     for (int x0 = 0; x0 < SPAN; x0 += GM_WAVE) {
         const int x = w * SPAN + x0 + lane;
         const bool p = (bits[x >> 5] >> (x & 31)) & 1u;
@@ -880,12 +957,9 @@ void launch_regions(K kernel, int block, int64_t groups, hipStream_t s, Args... 
 }
 
 template <typename V>
-TileArgs<V> tile_args(const TileHeavy &t, int bin, int64_t *n) {
-    const int64_t b0 = t.bins[bin];
-    *n = t.bins[bin + 1] - b0;
-    uint32_t *bm = bin <= TILE_M ? t.bitmap + (b0 - t.bins[TILE_D_BIG]) * TWORDS : nullptr;
-    return TileArgs<V>{t.col, static_cast<const V *>(t.val), t.seg, t.seg_e, t.seg_end, static_cast<const V *>(t.ea),
-                       t.nh, t.slog, t.grp, t.items + b0, *n, bm};
+TileArgs<V> tile_args(const TileHeavy &t, const TileTask *tasks, int64_t b0, int64_t b1) {
+    return TileArgs<V>{t.col,       static_cast<const V *>(t.val), t.seg,  t.seg_e, static_cast<const V *>(t.ea),
+                       tasks + b0, b1 - b0,                        t.bitmap};
 }
 
 void scan_u32(uint32_t *a, int64_t n, uint32_t *scratch, hipStream_t s) {
@@ -939,16 +1013,37 @@ void tile_fill(const Csr &B, const int32_t *slice_k, const TileHeavy &t, int32_t
 }
 
 void tile_entries(const Csr &A, const int64_t *heavy_rows, int64_t r0, const int32_t *k_to_slice, const TileHeavy &t,
-                  hipStream_t s) {
+                  unsigned long long *n_kept, hipStream_t s) {
     if (t.n_ent <= 0) return;
     with_types(A, [&](auto ci, auto v) {
         using CI = decltype(ci);
         using V = decltype(v);
         hipLaunchKernelGGL((k_tile_entries<CI, V>), dim3(grid_for(t.n_ent, 256, 65536)), dim3(256), 0, s,
                            typed<CI, V>(A), heavy_rows, t.nh, r0, t.a_ptr, t.n_ent, k_to_slice, t.es, t.eh,
-                           static_cast<V *>(t.ea));
+                           static_cast<V *>(t.ea), n_kept);
         GM_CHECK_LAUNCH();
     });
+}
+
+void tile_mark(const Csr &A, const Csr &B, const int64_t *heavy_rows, int64_t n_heavy, int64_t r0,
+               const int64_t *a_heavy_ptr, int64_t total, uint8_t *cls, hipStream_t s) {
+    fill<uint8_t>(cls, 1, A.n_cols, s);
+    if (total <= 0) return;
+    with_index_type(A.ci64, [&](auto ci) {
+        using CI = decltype(ci);
+        hipLaunchKernelGGL(k_tile_mark<CI>, dim3(grid_for((total + 7) / 8, 256, (int64_t)1 << 30)), dim3(256), 0, s,
+                           typed<CI, NoV>(A), B.rp, heavy_rows, n_heavy, r0, a_heavy_ptr, total, cls);
+        GM_CHECK_LAUNCH();
+    });
+}
+
+void tile_slices(const Csr &B, const int64_t *perm, int64_t ns, int32_t *slice_k, int64_t *len, int32_t *k_to_slice,
+                 hipStream_t s) {
+    fill<int32_t>(k_to_slice, -1, B.n_rows, s);
+    if (ns <= 0) return;
+    hipLaunchKernelGGL(k_tile_slices, dim3(grid_for(ns, 256, 16384)), dim3(256), 0, s, B.rp, perm, ns, slice_k, len,
+                       k_to_slice);
+    GM_CHECK_LAUNCH();
 }
 
 void tile_regions(const TileHeavy &t, unsigned long long *size, uint8_t *cls, int64_t *n_seg, hipStream_t s) {
@@ -982,48 +1077,74 @@ void tile_segments(const TileHeavy &t, hipStream_t s) {
     GM_CHECK_LAUNCH();
 }
 
+void tile_tasks(const TileHeavy &t, hipStream_t s) {
+    const int64_t n = tile_items(t);
+    if (n <= 0) return;
+    hipLaunchKernelGGL(k_tile_tasks_sym, dim3(grid_for(n, 256, 65536)), dim3(256), 0, s, t.items + t.bins[TILE_EMPTY + 1], n,
+                       t.grp, t.seg_end, t.nh, t.ncp, t.slog, t.tasks);
+    GM_CHECK_LAUNCH();
+}
+
+// (the tasks hold the bins after TILE_EMPTY)
 void tile_symbolic(const TileHeavy &t, int bin, int64_t *slot, hipStream_t s) {
-    int64_t n;
-    const TileArgs<float> a = tile_args<float>(t, bin, &n);
+    const int64_t first = t.bins[TILE_EMPTY + 1];
+    const TileArgs<float> a = tile_args<float>(t, t.tasks, t.bins[bin] - first, t.bins[bin + 1] - first);
+    const int64_t n = a.n;
     if (n <= 0) return;
     switch (bin) {
-    case TILE_T:
-        launch_regions(k_tile_sym_small<64, TILE_T_MAX, 4>, 256, (n + 3) / 4, s, a, t.nnz, t.ncp, slot);
-        break;
-    case TILE_S: launch_regions(k_tile_sym_small<256, TILE_S_MAX, 1>, 256, n, s, a, t.nnz, t.ncp, slot); break;
-    case TILE_L: launch_regions(k_tile_sym_small<512, TILE_MERGE, 1>, 512, n, s, a, t.nnz, t.ncp, slot); break;
-    case TILE_M: launch_regions(k_tile_sym<256>, 256, n, s, a, t.nnz, t.ncp, slot); break;
-    case TILE_D: launch_regions(k_tile_sym<512>, 512, n, s, a, t.nnz, t.ncp, slot); break;
-    case TILE_D_BIG: launch_regions(k_tile_sym<1024>, 1024, n, s, a, t.nnz, t.ncp, slot); break;
+    case TILE_T: launch_regions(k_tile_sym_small<64, TILE_T_MAX, 4>, 256, (n + 3) / 4, s, a, t.nnz, slot); break;
+    case TILE_S: launch_regions(k_tile_sym_small<256, TILE_S_MAX, 1>, 256, n, s, a, t.nnz, slot); break;
+    case TILE_L: launch_regions(k_tile_sym_small<512, TILE_MERGE, 1>, 512, n, s, a, t.nnz, slot); break;
+    case TILE_M: launch_regions(k_tile_sym<256>, 256, n, s, a, t.nnz, slot); break;
+    case TILE_D: launch_regions(k_tile_sym<512>, 512, n, s, a, t.nnz, slot); break;
+    case TILE_D_BIG: launch_regions(k_tile_sym<1024>, 1024, n, s, a, t.nnz, slot); break;
     default: break;
     }
 }
 
-void tile_numeric(const TileHeavy &t, int bin, const int64_t *heavy_rows, const int64_t *c_row_ptr,
-                  const int64_t *slot, bool ci64, bool v32, void *c_col, void *c_val, int32_t *err, hipStream_t s) {
+// Orders the regions of more than TILE_MERGE products by numeric bin:
+// large_bins (device) gets the bounds of the dense, large, middle and small
+// rank regions, which t.large_perm lists.
+void tile_large_bins(const TileHeavy &t, uint8_t *cls, int64_t *scratch, int64_t *large_bins, hipStream_t s) {
+    const int64_t n = tile_large(t);
+    if (n > 0) {
+        hipLaunchKernelGGL(k_tile_large_classes, dim3(grid_for(n, 256, 65536)), dim3(256), 0, s, t.tasks, n, t.nnz, cls);
+        GM_CHECK_LAUNCH();
+    }
+    partition_u8(cls, n, 4, t.large_perm, nullptr, large_bins, scratch, s);
+}
+
+int64_t tile_items(const TileHeavy &t) { return t.bins[TILE_NBINS] - t.bins[TILE_EMPTY + 1]; }
+int64_t tile_large(const TileHeavy &t) { return t.bins[TILE_M + 1] - t.bins[TILE_D_BIG]; }
+
+int tile_numeric(const TileHeavy &t, const int64_t *large_bins, TileTask *tasks, const int64_t *heavy_rows,
+                 const int64_t *c_row_ptr, const int64_t *slot, bool ci64, bool v32, void *c_col, void *c_val,
+                 int32_t *err, hipStream_t s) {
+    const int64_t n_all = tile_items(t);
+    if (n_all <= 0) return 0;
+    hipLaunchKernelGGL(k_tile_tasks_num, dim3(grid_for(n_all, 256, 65536)), dim3(256), 0, s, t.tasks, n_all, t.large_perm,
+                       tile_large(t), t.nh, t.nnz, slot, heavy_rows, c_row_ptr, tasks);
+    GM_CHECK_LAUNCH();
+    int launches = 0;
     with_types(ci64, v32, [&](auto ci, auto v) {
         using CI = decltype(ci);
         using V = decltype(v);
-        int64_t n;
-        const TileArgs<V> a = tile_args<V>(t, bin, &n);
-        if (n <= 0) return;
-        const TileOut<CI, V> o{heavy_rows, c_row_ptr, slot, t.nnz, t.ncp, static_cast<CI *>(c_col),
-                               static_cast<V *>(c_val), err};
-        switch (bin) {
-        case TILE_T:
-            launch_regions(k_tile_num_small<64, TILE_T_MAX, 4, CI, V>, 256, (n + 3) / 4, s, a, o);
-            break;
-        case TILE_S: launch_regions(k_tile_num_small<256, TILE_S_MAX, 1, CI, V>, 256, n, s, a, o); break;
-        case TILE_L: launch_regions(k_tile_num_small<512, TILE_MERGE, 1, CI, V>, 512, n, s, a, o); break;
-        case TILE_M: launch_regions(k_tile_num_rank<512, TILE_M_MAX, CI, V>, 512, n, s, a, o); break;
-        case TILE_D:
-        case TILE_D_BIG:
-            launch_regions(k_tile_num_dense<1024, TILE_RANK_MAX, CI, V>, 1024, n, s, a, o);
-            launch_regions(k_tile_num_rank<1024, TILE_RANK_MAX, CI, V>, 1024, n, s, a, o);
-            break;
-        default: break;
-        }
+        const TileOut<CI, V> o{static_cast<CI *>(c_col), static_cast<V *>(c_val), err};
+        const int64_t first = t.bins[TILE_EMPTY + 1];
+        auto bin = [&](int64_t b0, int64_t b1, int per_group, int block, auto kernel) {
+            if (b1 <= b0) return;
+            launch_regions(kernel, block, (b1 - b0 + per_group - 1) / per_group, s, tile_args<V>(t, tasks, b0, b1), o);
+            ++launches;
+        };
+        bin(large_bins[0], large_bins[1], 1, 1024, k_tile_num_dense<1024, CI, V>);
+        bin(large_bins[1], large_bins[2], 1, 1024, k_tile_num_rank<1024, TILE_RANK_MAX, CI, V>);
+        bin(large_bins[2], large_bins[3], 1, 512, k_tile_num_rank<512, TILE_RANK_MID, CI, V>);
+        bin(large_bins[3], large_bins[4], 1, 256, k_tile_num_rank<256, TILE_RANK_MIN, CI, V>);
+        bin(t.bins[TILE_L] - first, t.bins[TILE_L + 1] - first, 1, 512, k_tile_num_small<512, TILE_MERGE, 1, CI, V>);
+        bin(t.bins[TILE_S] - first, t.bins[TILE_S + 1] - first, 1, 256, k_tile_num_small<256, TILE_S_MAX, 1, CI, V>);
+        bin(t.bins[TILE_T] - first, t.bins[TILE_T + 1] - first, 4, 256, k_tile_num_small<64, TILE_T_MAX, 4, CI, V>);
     });
+    return launches;
 }
 
 }  // namespace gm
