@@ -84,27 +84,49 @@ GM_DEV bool rank_mark(RankWord *w, uint32_t bit) {
     return !(__hip_atomic_fetch_or(&w->bits, m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) & m);
 }
 
-// Numbers the set bits of words [0, n); returns their count to every thread.
-template <int BLOCK>
+// Numbers the set bits of words [0, n), at most PER a thread; returns their
+// count to every thread. A wave takes consecutive words, 64 at a time (a thread
+// taking consecutive words itself meets eight-way bank conflicts: with 256
+// words a wave and three levels, two thirds of the LDS cycles).
+template <int BLOCK, int PER>
 GM_DEV uint32_t rank_number(RankWord *words, int n, uint32_t *sm, int tid) {
-    const int per = (n + BLOCK - 1) / BLOCK;  // words per thread (uniform)
-    uint32_t cnt = 0;
-    if (per == 1) {
+    const int per = (n + BLOCK - 1) / BLOCK;  // (uniform)
+    if (BLOCK > GM_WAVE && per == 1) {
         const uint32_t b = tid < n ? words[tid].bits : 0u;
         uint32_t total;
         const uint32_t run = region_scan<BLOCK>((uint32_t)__popc(b), sm, &total);
         if (tid < n) words[tid].rank = run;
         return total;
     }
-    for (int q = 0; q < per; ++q)
-        if (tid * per + q < n) cnt += (uint32_t)__popc(words[tid * per + q].bits);
-    uint32_t total;
-    uint32_t run = region_scan<BLOCK>(cnt, sm, &total);
-    for (int q = 0; q < per; ++q)
-        if (tid * per + q < n) {
-            words[tid * per + q].rank = run;
-            run += (uint32_t)__popc(words[tid * per + q].bits);
+    const int w = BLOCK == GM_WAVE ? 0 : tid / GM_WAVE, i0 = w * per * GM_WAVE + (tid & (GM_WAVE - 1));
+    uint32_t before[PER], carry = 0;
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        if (q >= per) break;
+        const int i = i0 + q * GM_WAVE;
+        const int32_t c = i < n ? __popc(words[i].bits) : 0;
+        const int32_t inc = wave_incl_scan<int32_t>(c);
+        before[q] = carry + (uint32_t)(inc - c);
+        carry += (uint32_t)__builtin_amdgcn_readlane(inc, GM_WAVE - 1);
+    }
+    uint32_t base = 0, total = carry;
+    if constexpr (BLOCK > GM_WAVE) {
+        if ((tid & (GM_WAVE - 1)) == 0) sm[w] = carry;
+        __syncthreads();
+        total = 0;
+#pragma unroll
+        for (int q = 0; q < BLOCK / GM_WAVE; ++q) {
+            const uint32_t v = sm[q];
+            base += q < w ? v : 0u;
+            total += v;
         }
+    }
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        if (q >= per) break;
+        const int i = i0 + q * GM_WAVE;
+        if (i < n) words[i].rank = base + before[q];
+    }
     return total;
 }
 
@@ -203,7 +225,7 @@ GM_DEV uint32_t rank_region(const Src &src, uint32_t width, RankLds<BLOCK, CAP, 
         if ((uint32_t)(tid + k * BLOCK) < n) rank_mark(&L.top[at[k]], (col[k] >> (5 * depth)) & 31);
     }
     region_sync<BLOCK>();  // (the parts are read)
-    uint32_t count = rank_number<BLOCK>(L.top, ntop, L.scan[par], tid);
+    uint32_t count = rank_number<BLOCK, (TOPW + BLOCK - 1) / BLOCK>(L.top, ntop, L.scan[par], tid);
     par ^= 1;
     RankWord *above = L.top;
     uint32_t fresh = 0;
@@ -224,7 +246,7 @@ GM_DEV uint32_t rank_region(const Src &src, uint32_t width, RankLds<BLOCK, CAP, 
             return count;
         }
         region_sync<BLOCK>();
-        count = rank_number<BLOCK>(cur, m, L.scan[par], tid);
+        count = rank_number<BLOCK, EPT>(cur, m, L.scan[par], tid);
         par ^= 1;
         above = cur;
     }
