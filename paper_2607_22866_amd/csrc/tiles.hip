@@ -278,6 +278,7 @@ __global__ __launch_bounds__(TF_WAVES * GM_WAVE) void k_tile_fill_long(CsrV<CI, 
                                                                        int64_t n_elems, uint16_t *out_col, V *out_val,
                                                                        const int32_t *n_long,
                                                                        const int32_t *long_list) {
+    const int lane = threadIdx.x & (GM_WAVE - 1);
     const int n = *n_long;
     for (int i = blockIdx.y; i < n; i += gridDim.y) {
         const int64_t s = long_list[i];
@@ -286,15 +287,21 @@ __global__ __launch_bounds__(TF_WAVES * GM_WAVE) void k_tile_fill_long(CsrV<CI, 
         const CI *row = B.ci + b0;
         const int64_t step = (int64_t)gridDim.x * TF_WAVES * TF_LONG;
         for (int64_t p0 = (blockIdx.x * (int64_t)TF_WAVES + threadIdx.x / GM_WAVE) * TF_LONG; p0 < len; p0 += step) {
-            // chunk open at p0 and where it starts in the row
+            // chunk open at p0 and where it starts in the row: 64 bounds a step
+            // (a chain of binary search steps took longer than the copy)
             const int64_t f64 = (int64_t)row[p0] >> TILE_LOG2;
-            int64_t lo = 0, hi = p0;
-            while (lo < hi) {
-                const int64_t mid = (lo + hi) >> 1;
-                if (((int64_t)row[mid] >> TILE_LOG2) < f64)
-                    lo = mid + 1;
-                else
-                    hi = mid;
+            int64_t lo = 0, hi = p0;  // the answer is in [lo, hi]
+            while (hi > lo) {
+                const int64_t span = hi - lo, x = lo + span * lane / GM_WAVE;
+                const uint64_t below = ballot(((int64_t)row[x] >> TILE_LOG2) < f64);
+                const int c = __popcll(below);  // (a prefix: the row is sorted)
+                if (c == 0) {
+                    hi = lo;
+                    break;
+                }
+                const int64_t nlo = lo + span * (c - 1) / GM_WAVE + 1;
+                if (c < GM_WAVE) hi = lo + span * c / GM_WAVE;
+                lo = nlo;
             }
             const int64_t p1 = p0 + TF_LONG < len ? p0 + TF_LONG : len;
             tile_copy_row<CI, V>(row, B.v + b0, p0, p1, nc, part + s * nc, n_elems, (int)(f64 < nc ? f64 : nc - 1), lo,
@@ -304,23 +311,66 @@ __global__ __launch_bounds__(TF_WAVES * GM_WAVE) void k_tile_fill_long(CsrV<CI, 
 }
 
 // ------------------------------------------------------ entries and regions
+// The heavy rows' entries in row order. The rows of a work group's entries are
+// found once and their starts kept in LDS, so that an entry's row takes no
+// search in memory.
+constexpr int EN_BLOCK = 256, EN_ITEMS = 8, EN_ROWS = 512;
 template <typename CI, typename V>
-__global__ void k_tile_entries(CsrV<CI, V> A, const int64_t *heavy_rows, int64_t n_heavy, int64_t r0,
-                               const int64_t *a_heavy_ptr, int64_t total, const int32_t *k_to_slice, int32_t *es,
-                               int32_t *eh, V *ea, unsigned long long *n_kept) {
-    __shared__ int32_t sm[256 / GM_WAVE];
-    int32_t kept = 0;
-    for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < total;
-         e += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t h = find_row(a_heavy_ptr, 0, n_heavy + 1, e);
-        const int64_t j = A.rp[r0 + heavy_rows[h]] + (e - a_heavy_ptr[h]);
-        const int32_t sl = k_to_slice[(int64_t)A.ci[j]];
-        es[e] = sl;
-        eh[e] = (int32_t)h;
-        ea[e] = A.v[j];
-        kept += sl >= 0;
+__global__ __launch_bounds__(EN_BLOCK) void k_tile_entries(CsrV<CI, V> A, const int64_t *heavy_rows, int64_t n_heavy,
+                                                           int64_t r0, const int64_t *a_heavy_ptr, int64_t total,
+                                                           const int32_t *k_to_slice, int32_t *es, int32_t *eh, V *ea,
+                                                           unsigned long long *n_kept) {
+    __shared__ int64_t s_ptr[EN_ROWS + 1], s_at[EN_ROWS];
+    __shared__ int64_t rows[2];
+    __shared__ int32_t sm[EN_BLOCK / GM_WAVE];
+    const int64_t e0 = blockIdx.x * (int64_t)(EN_BLOCK * EN_ITEMS);
+    const int64_t e1 = e0 + EN_BLOCK * EN_ITEMS < total ? e0 + EN_BLOCK * EN_ITEMS : total;
+    if (threadIdx.x == 0) rows[0] = find_row(a_heavy_ptr, 0, n_heavy + 1, e0);
+    if (threadIdx.x == GM_WAVE) rows[1] = find_row(a_heavy_ptr, 0, n_heavy + 1, e1 - 1);
+    __syncthreads();
+    const int64_t ha = rows[0], nr = rows[1] - ha + 1;
+    const bool staged = nr <= EN_ROWS;  // uniform
+    if (staged) {
+        for (int64_t q = threadIdx.x; q <= nr; q += EN_BLOCK) s_ptr[q] = a_heavy_ptr[ha + q];
+        for (int64_t q = threadIdx.x; q < nr; q += EN_BLOCK) s_at[q] = A.rp[r0 + heavy_rows[ha + q]];
     }
-    kept = block_reduce_sum<256>(kept, sm);
+    __syncthreads();
+    int64_t j[EN_ITEMS];
+    int32_t h[EN_ITEMS], sl[EN_ITEMS];
+    int32_t kept = 0;
+#pragma unroll
+    for (int u = 0; u < EN_ITEMS; ++u) {
+        const int64_t e = e0 + u * EN_BLOCK + threadIdx.x < e1 ? e0 + u * EN_BLOCK + threadIdx.x : e1 - 1;
+        if (staged) {
+            const int64_t q = find_row(s_ptr, 0, nr + 1, e);
+            h[u] = (int32_t)(ha + q);
+            j[u] = s_at[q] + (e - s_ptr[q]);
+        } else {
+            const int64_t hh = find_row(a_heavy_ptr, ha, ha + nr + 1, e);
+            h[u] = (int32_t)hh;
+            j[u] = A.rp[r0 + heavy_rows[hh]] + (e - a_heavy_ptr[hh]);
+        }
+    }
+    CI k[EN_ITEMS];
+    V v[EN_ITEMS];
+#pragma unroll
+    for (int u = 0; u < EN_ITEMS; ++u) {
+        k[u] = A.ci[j[u]];
+        v[u] = A.v[j[u]];
+    }
+#pragma unroll
+    for (int u = 0; u < EN_ITEMS; ++u) sl[u] = k_to_slice[(int64_t)k[u]];
+#pragma unroll
+    for (int u = 0; u < EN_ITEMS; ++u) {
+        const int64_t e = e0 + u * EN_BLOCK + threadIdx.x;
+        if (e < e1) {
+            es[e] = sl[u];
+            eh[e] = h[u];
+            ea[e] = v[u];
+            kept += sl[u] >= 0;
+        }
+    }
+    kept = block_reduce_sum<EN_BLOCK>(kept, sm);
     if (threadIdx.x == 0 && kept) atomicAdd(n_kept, (unsigned long long)kept);
 }
 
@@ -374,7 +424,7 @@ GM_DEV int64_t list_of(int64_t c, int64_t h, int64_t nh, int slog) {
 // A work group takes TE_BLOCK consecutive entries, a thread one chunk of a
 // contiguous group of them, so the chunk sizes of a slice are read coalesced;
 // one atomic per (row, chunk) and group.
-constexpr int TE_BLOCK = 256, TE_U = 8;
+constexpr int TE_BLOCK = 256, TE_U = 8, TE_PER = 16;
 __global__ __launch_bounds__(TE_BLOCK) void k_tile_sizes(const int32_t *es, const int32_t *eh, int64_t n_ent,
                                                          const uint16_t *cnt, int nc, int ncb, int64_t nh, int slog,
                                                          unsigned long long *size) {
@@ -387,7 +437,9 @@ __global__ __launch_bounds__(TE_BLOCK) void k_tile_sizes(const int32_t *es, cons
         s_h[tid] = eh[e0 + tid];
     }
     __syncthreads();
-    const int i0 = (tid / ncb) * ncb, i1 = i0 + ncb < ne ? i0 + ncb : ne;
+    // (few chunks: TE_PER entries a thread all the same, for fewer atomics)
+    const int per = ncb > TE_PER ? ncb : TE_PER;
+    const int i0 = (tid / ncb) * per, i1 = i0 + per < ne ? i0 + per : ne;
     const int c = blockIdx.y * ncb + tid % ncb;
     if (i0 >= i1 || c >= nc) return;
     int cur = s_h[i0];
@@ -1006,7 +1058,7 @@ void tile_fill(const Csr &B, const int32_t *slice_k, const TileHeavy &t, int32_t
         hipLaunchKernelGGL((k_tile_fill<CI, V>), dim3(grid_for(t.ns, TF_WAVES, 65536)), dim3(TF_WAVES * GM_WAVE), 0, s,
                            typed<CI, V>(B), slice_k, t.ns, t.nc, t.part, t.n_elems, t.col, ov, long_list, long_list + 1);
         GM_CHECK_LAUNCH();
-        hipLaunchKernelGGL((k_tile_fill_long<CI, V>), dim3(8, 512), dim3(TF_WAVES * GM_WAVE), 0, s, typed<CI, V>(B),
+        hipLaunchKernelGGL((k_tile_fill_long<CI, V>), dim3(8, 2048), dim3(TF_WAVES * GM_WAVE), 0, s, typed<CI, V>(B),
                            slice_k, t.ns, t.nc, t.part, t.n_elems, t.col, ov, long_list, long_list + 1);
         GM_CHECK_LAUNCH();
     });
@@ -1018,9 +1070,9 @@ void tile_entries(const Csr &A, const int64_t *heavy_rows, int64_t r0, const int
     with_types(A, [&](auto ci, auto v) {
         using CI = decltype(ci);
         using V = decltype(v);
-        hipLaunchKernelGGL((k_tile_entries<CI, V>), dim3(grid_for(t.n_ent, 256, 65536)), dim3(256), 0, s,
-                           typed<CI, V>(A), heavy_rows, t.nh, r0, t.a_ptr, t.n_ent, k_to_slice, t.es, t.eh,
-                           static_cast<V *>(t.ea), n_kept);
+        hipLaunchKernelGGL((k_tile_entries<CI, V>), dim3(grid_for(t.n_ent, EN_BLOCK * EN_ITEMS, INT32_MAX)),
+                           dim3(EN_BLOCK), 0, s, typed<CI, V>(A), heavy_rows, t.nh, r0, t.a_ptr, t.n_ent, k_to_slice,
+                           t.es, t.eh, static_cast<V *>(t.ea), n_kept);
         GM_CHECK_LAUNCH();
     });
 }
