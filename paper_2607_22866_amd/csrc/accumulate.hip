@@ -450,7 +450,7 @@ __global__ __launch_bounds__(GM_WAVE) void k_light_hash_sym(CsrV<CI, NoV> A, Csr
     __shared__ __align__(16) int32_t keys[TS];
     __shared__ GusLds<GM_WAVE, NoV> G;
     __shared__ int32_t counter;
-    const int64_t r = items[blockIdx.x];
+    const int64_t r = items[xcd_run()];
     const int p = (int)ip[r];
     const int lg = 32 - __clz(4 * p - 1) > 6 ? 32 - __clz(4 * p - 1) : 6;
     const int shift = 32 - (1 << lg <= TS ? lg : __builtin_ctz(TS)), mask = (1 << (32 - shift)) - 1;
@@ -512,7 +512,7 @@ __global__ __launch_bounds__(BLOCK *REGS) void k_light_rank_sym(CsrV<CI, NoV> A,
     static_assert(REGS == 1 || BLOCK == GM_WAVE, "several rows per work group are one wave each");
     __shared__ __align__(16) RankLds<BLOCK, CAP, false, float> L[REGS];
     const int reg = REGS > 1 ? threadIdx.x / GM_WAVE : 0, tid = REGS > 1 ? threadIdx.x & (GM_WAVE - 1) : threadIdx.x;
-    const int64_t i = blockIdx.x * (int64_t)REGS + reg;
+    const int64_t i = xcd_run() * (int64_t)REGS + reg;
     if (i >= n) return;  // the whole wave (one row: the whole work group)
     const int64_t r = items[i];
     const CI base = minc[r];
@@ -530,7 +530,7 @@ __global__ __launch_bounds__(BLOCK *REGS) void k_light_rank_num(CsrV<CI, V> A, C
     static_assert(REGS == 1 || BLOCK == GM_WAVE, "several rows per work group are one wave each");
     __shared__ __align__(16) RankLds<BLOCK, CAP, true, V> L_all[REGS];
     const int reg = REGS > 1 ? threadIdx.x / GM_WAVE : 0, tid = REGS > 1 ? threadIdx.x & (GM_WAVE - 1) : threadIdx.x;
-    const int64_t i = blockIdx.x * (int64_t)REGS + reg;
+    const int64_t i = xcd_run() * (int64_t)REGS + reg;
     if (i >= n) return;  // the whole wave (one row: the whole work group)
     RankLds<BLOCK, CAP, true, V> &L = L_all[reg];
     const int64_t r = items[i];
@@ -869,7 +869,7 @@ __global__ __launch_bounds__(BLOCK) void k_light_win_sym(CsrV<CI, NoV> A, CsrV<C
                                                          int64_t *row_nnz) {
     __shared__ WinLds<BLOCK, WMAX, false> D;
     __shared__ GusLds<BLOCK, NoV> G;
-    const int64_t r = items[blockIdx.x];
+    const int64_t r = items[xcd_run()];
     const CI base = minc[r];
     const int width = (int)(maxc[r] - base + 1);
     win_clear(D, width);
@@ -888,7 +888,7 @@ __global__ __launch_bounds__(BLOCK) void k_light_win_num(CsrV<CI, V> A, CsrV<CI,
                                                          int32_t *err) {
     __shared__ WinLds<BLOCK, WMAX, true, V> D;
     __shared__ GusLds<BLOCK, V> G;
-    const int64_t r = items[blockIdx.x];
+    const int64_t r = items[xcd_run()];
     const CI base = minc[r];
     const int width = (int)(maxc[r] - base + 1);
     win_clear(D, width);
