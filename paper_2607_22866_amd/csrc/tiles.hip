@@ -472,39 +472,45 @@ __global__ __launch_bounds__(TE_BLOCK) void k_tile_sizes(const int32_t *es, cons
 
 // The lists: seg = (start of the part in the chunk-major B, its length | its
 // chunk within the S chunks << 16), seg_e = A entry; cursor[l] starts at list
-// l's first place and ends one past its last. Tiles of 64 entries x TL_C
+// l's first place and ends one past its last. Tiles of 64 entries x C
 // chunks pass through LDS: read a slice at a time (coalesced), written a
 // chunk at a time with an entry per lane, so that a row's parts go out as one
 // contiguous store (writing them a thread per chunk, 8 bytes at a time into
 // as many lists as threads, took 3.1 ms instead of 1.9 for 1e8 parts).
-constexpr int TL_BLOCK = 256, TL_C = 64, TL_U = 8;
+// C chunks a work group: the smallest of 8, 16, 32, 64 that holds them all, for
+// the LDS and the idle lanes that more would take (8 chunks, R-MAT 17 panels:
+// 103 -> 76 us a panel in tiles of 8 instead of 64; 256 and 512 chunks: 64 and 32
+// measure the same).
+constexpr int TL_BLOCK = 256, TL_U = 8;
+template <int C>
 __global__ __launch_bounds__(TL_BLOCK) void k_tile_lists(const int32_t *es, const int32_t *eh, int64_t n_ent,
                                                          const uint16_t *cnt, const uint32_t *part, int nc, int64_t nh,
                                                          int slog, uint32_t *cursor, uint2 *seg, uint32_t *seg_e) {
-    __shared__ uint32_t t_st[GM_WAVE][TL_C + 1];
-    __shared__ uint16_t t_len[GM_WAVE][TL_C + 2];
+    __shared__ uint32_t t_st[GM_WAVE][C + 1];
+    __shared__ uint16_t t_len[GM_WAVE][C + 2];
     __shared__ int32_t s_s[GM_WAVE];
     const int tid = threadIdx.x, lane = tid & (GM_WAVE - 1), w = tid / GM_WAVE;
     const int64_t e0 = blockIdx.x * (int64_t)GM_WAVE;
-    const int c0 = blockIdx.y * TL_C, ncc = nc - c0 < TL_C ? nc - c0 : TL_C;
+    const int c0 = blockIdx.y * C, ncc = nc - c0 < C ? nc - c0 : C;
     const int64_t e = e0 + lane;
     const int32_t h = e < n_ent ? eh[e] : -1;
     if (w == 0) s_s[lane] = e < n_ent ? es[e] : -1;
     __syncthreads();
     {
-        constexpr int RPB = TL_BLOCK / TL_C;  // slices read at a time
-        const int c = tid & (TL_C - 1);
-        for (int i0 = tid / TL_C; i0 < GM_WAVE; i0 += RPB * TL_U) {
-            uint32_t len[TL_U], st[TL_U];
+        constexpr int RPB = TL_BLOCK / C;  // slices read at a time, RU times
+        constexpr int RU = GM_WAVE / RPB < TL_U ? GM_WAVE / RPB : TL_U;
+        const int c = tid & (C - 1);
+        for (int i0 = tid / C; i0 < GM_WAVE; i0 += RPB * RU) {
+            uint32_t len[RU], st[RU];
 #pragma unroll
-            for (int u = 0; u < TL_U; ++u) {
+            for (int u = 0; u < RU; ++u) {
                 const int32_t s = s_s[i0 + u * RPB];
                 const bool ok = s >= 0 && c < ncc;
                 len[u] = ok ? cnt[(int64_t)s * nc + c0 + c] : 0u;
                 st[u] = ok ? part[(int64_t)s * nc + c0 + c] : 0u;
             }
 #pragma unroll
-            for (int u = 0; u < TL_U; ++u) {
+            for (int u = 0; u < RU; ++u) {
                 t_len[i0 + u * RPB][c] = (uint16_t)len[u];
                 t_st[i0 + u * RPB][c] = st[u];
             }
@@ -518,13 +524,14 @@ __global__ __launch_bounds__(TL_BLOCK) void k_tile_lists(const int32_t *es, cons
     const uint64_t above = heads & ~le_mask;
     const int end = above ? __ffsll((long long)above) - 1 : GM_WAVE;  // lane after the run
     const uint64_t run = (end == GM_WAVE ? ~0ull : (uint64_t(1) << end) - 1) & ~((uint64_t(1) << first) - 1);
-    // TL_U chunks at a time: their reservations are in flight together
-    for (int cb = w; cb < ncc; cb += TL_U * (TL_BLOCK / GM_WAVE)) {
-        uint32_t len[TL_U], at[TL_U];
-        uint64_t full[TL_U];
+    constexpr int NW = TL_BLOCK / GM_WAVE, CU = C / NW < TL_U ? C / NW : TL_U;
+    // CU chunks at a time: their reservations are in flight together
+    for (int cb = w; cb < ncc; cb += CU * NW) {
+        uint32_t len[CU], at[CU];
+        uint64_t full[CU];
 #pragma unroll
-        for (int u = 0; u < TL_U; ++u) {
-            const int c = cb + u * (TL_BLOCK / GM_WAVE);
+        for (int u = 0; u < CU; ++u) {
+            const int c = cb + u * NW;
             len[u] = c < ncc ? t_len[lane][c] : 0u;
             full[u] = ballot(len[u] > 0) & run;
             at[u] = 0;
@@ -532,8 +539,8 @@ __global__ __launch_bounds__(TL_BLOCK) void k_tile_lists(const int32_t *es, cons
                 at[u] = atomicAdd(&cursor[list_of(c0 + c, h, nh, slog)], (uint32_t)__popcll(full[u]));
         }
 #pragma unroll
-        for (int u = 0; u < TL_U; ++u) {
-            const int c = cb + u * (TL_BLOCK / GM_WAVE);
+        for (int u = 0; u < CU; ++u) {
+            const int c = cb + u * NW;
             const uint32_t q = (uint32_t)__shfl((int32_t)at[u], first, GM_WAVE) +
                                (uint32_t)__popcll(full[u] & lanemask_lt());
             if (len[u] > 0) {
@@ -1123,9 +1130,19 @@ void tile_regions(const TileHeavy &t, unsigned long long *size, uint8_t *cls, in
 }
 
 void tile_segments(const TileHeavy &t, hipStream_t s) {
-    hipLaunchKernelGGL(k_tile_lists, dim3((unsigned)((t.n_ent + GM_WAVE - 1) / GM_WAVE), (unsigned)((t.nc + TL_C - 1) / TL_C)),
-                       dim3(TL_BLOCK), 0, s, t.es, t.eh, t.n_ent, t.cnt, t.part, t.nc, t.nh, t.slog, t.seg_end, t.seg,
-                       t.seg_e);
+    auto launch = [&](auto kernel, int c) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)((t.n_ent + GM_WAVE - 1) / GM_WAVE), (unsigned)((t.nc + c - 1) / c)),
+                           dim3(TL_BLOCK), 0, s, t.es, t.eh, t.n_ent, t.cnt, t.part, t.nc, t.nh, t.slog, t.seg_end,
+                           t.seg, t.seg_e);
+    };
+    if (t.nc <= 8)
+        launch(k_tile_lists<8>, 8);
+    else if (t.nc <= 16)
+        launch(k_tile_lists<16>, 16);
+    else if (t.nc <= 32)
+        launch(k_tile_lists<32>, 32);
+    else
+        launch(k_tile_lists<64>, 64);
     GM_CHECK_LAUNCH();
 }
 
