@@ -44,11 +44,14 @@ PAIR_WORKLOADS = {
                       "fp64 U(0,1), C=A*B",
 }
 HEAVY_KERNELS = ["expand", "histogram", "multisplit", "chunk_symbolic", "chunk_numeric"]
-# Timing classes that are exactly one kernel launch per panel: the roofline is
-# reported for the one of these with the largest device time.
-SINGLE_KERNEL_CLASSES = {"expand": "k_expand_rows2", "multisplit": "k_multisplit"}
+# Timing classes of one kernel per panel: the roofline is reported for the one
+# of these with the largest device time. ("expand" is by default the chunk-major
+# copy of the B rows in use, k_tile_fill, with the rows it leaves to
+# k_tile_fill_long; with a flag for another order, that order's expansion.)
+SINGLE_KERNEL_CLASSES = {"expand": "k_tile_fill", "multisplit": "k_multisplit"}
 # Sources a kernel's counter summary depends on (traffic is dropped when they change).
-KERNEL_SOURCES = {"k_expand_rows2": ["paper_2607_22866_amd/csrc/rowsplit.hip", "paper_2607_22866_amd/csrc/common.hpp"],
+KERNEL_SOURCES = {"k_tile_fill": ["paper_2607_22866_amd/csrc/tiles.hip", "paper_2607_22866_amd/csrc/common.hpp"],
+                  "k_expand_rows2": ["paper_2607_22866_amd/csrc/rowsplit.hip", "paper_2607_22866_amd/csrc/common.hpp"],
                   "k_expand_rows": ["paper_2607_22866_amd/csrc/rowsplit.hip", "paper_2607_22866_amd/csrc/common.hpp"],
                   "k_expand_split": ["paper_2607_22866_amd/csrc/expand.hip", "paper_2607_22866_amd/csrc/common.hpp"],
                   "k_expand": ["paper_2607_22866_amd/csrc/expand.hip", "paper_2607_22866_amd/csrc/common.hpp"],
@@ -336,11 +339,12 @@ def main():
         d = kernels[dom]
         kname = SINGLE_KERNEL_CLASSES[dom]
         levels = acc.get("_levels", set())
-        if dom == "expand" and (args.paper_expansion or levels == {0}):
+        ordered = args.slice_split or args.level_by_level
+        if dom == "expand" and (args.paper_expansion or (ordered and levels == {0})):
             kname = "k_expand"  # also the only expansion without a multisplit level
         elif dom == "expand" and args.slice_split:
             kname = "k_expand_split"
-        elif dom == "expand" and (args.level_by_level or levels != {2}):
+        elif dom == "expand" and args.level_by_level:
             kname = "k_expand_rows"
         bpl = d["gb_per_step"] * 1e9 / d["launches_per_step"]
         ms = d["ms_per_step"] / d["launches_per_step"]

@@ -145,7 +145,7 @@ typedef struct {
 enum {
     GMAGNUS_K_SETUP = 0,       /* row products, binning, partitions, scans */
     GMAGNUS_K_CSC = 1,         /* masked CSR->CSC of heavy rows and slice offsets */
-    GMAGNUS_K_EXPAND = 2,      /* outer-product expansion into C-hat */
+    GMAGNUS_K_EXPAND = 2,      /* outer-product expansion into C-hat, or the chunk-major copy of B's rows in its place */
     GMAGNUS_K_HISTOGRAM = 3,   /* level-0 chunk histogram */
     GMAGNUS_K_MULTISPLIT = 4,  /* multisplit levels (with fused next-level histogram) */
     GMAGNUS_K_CHUNK_SYM = 5,   /* symbolic of final chunks */

@@ -1,7 +1,7 @@
 // Host orchestration of the SpGEMM C = A*B (Algorithm 3) behind the C ABI of
 // gmagnus.h: parameter selection (Section III-D), the setup phase, the heavy
-// path (masked CSC, outer product, hierarchical multisplit, final chunks) on
-// one HIP stream and the light path on another, the C row-pointer scan, and
+// path (regions of rows gathered from a chunk-major copy of B; or masked CSC,
+// outer product, hierarchical multisplit, final chunks) on one HIP stream and the light path on another, the C row-pointer scan, and
 // the numeric phase. Also the library's caching device allocator.
 #include <algorithm>
 #include <cstring>
@@ -817,10 +817,16 @@ bool tiles_possible(const gmagnus_plan_s *p) {
     if (nc > TILE_MAX_CHUNKS || H >= ((int64_t)1 << 32) || p->n_heavy * nc >= ((int64_t)1 << 31) ||
         p->nnz_heavy * nc >= ((int64_t)1 << 40))
         return false;
+    // Below one product per (entry, chunk) most of what the lists read would be
+    // empty. R-MAT panels stay above it, and gain down to the 3.5 products of
+    // scale 23 (panels of 2e8 products, expansion -> copy: 15.5 products a pair
+    // (scale 20) 4.15 -> 3.04 ms, 5.7 (scale 22) 3.91 -> 3.48, 3.5 (scale 23)
+    // 4.25 -> 3.85).
     return H >= p->nnz_heavy * nc;
 }
 
-// ... and whether it fits, with the slices known.
+// ... and whether it takes no more memory than the expansion's columns and
+// values would (0.3 to 0.8 of them in the panels above), with the slices known.
 bool use_tiles(const gmagnus_plan_s *p, int64_t n_slices, int64_t blen_total) {
     const int64_t H = p->products_heavy, nc = tile_chunks(std::max<int64_t>(p->B.n_cols, 1));
     if (blen_total >= ((int64_t)1 << 31)) return false;
