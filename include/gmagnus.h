@@ -13,8 +13,11 @@
  * an intermediate matrix (Section III-B, Algorithm 4), split into column
  * chunks by a hierarchical multisplit (Section III-C, Algorithm 5) until every
  * chunk's column range fits a dense accumulator in LDS, and accumulated chunk
- * by chunk; light rows and light chunks use an LDS hash or dense-window
- * accumulator (Section III-E). Parameters follow Section III-D.
+ * by chunk. Unless a flag or option asks for that order, or memory speaks
+ * against it, they are instead accumulated per row and column chunk straight
+ * from a chunk-major copy of the rows of B they use, with the same C. Light
+ * rows use an LDS dense window or a bitmap-rank accumulator (Section III-E).
+ * Parameters follow Section III-D.
  *
  * Conventions shared by every entry point
  *   - All matrix arrays are DEVICE pointers (hipMalloc'ed or torch tensors on
@@ -268,7 +271,8 @@ gmagnus_status_t gmagnus_plan_static(gmagnus_plan_t *out, const gmagnus_csr_t *A
                                      const gmagnus_options_t *opts, void *hip_stream);
 
 /* Symbolic phase: runs the heavy-row expansion and hierarchical multisplit
- * (Algorithm 3, outer product and reorder), counts the distinct columns of
+ * (Algorithm 3, outer product and reorder) or the chunk-major copy in their
+ * place, counts the distinct columns of
  * every light row and final chunk, and writes the panel's row pointers:
  * c_row_ptr (device, panel_rows + 1, starting at 0) and *c_nnz (host).
  * Synchronises the stream (C.nnz is needed on the host to size C).
@@ -300,7 +304,7 @@ gmagnus_status_t gmagnus_spgemm_numeric_typed(gmagnus_plan_t plan, const int64_t
  * plan's next numeric phase has finished (they may be the arrays given at
  * gmagnus_plan, and a_val may equal b_val when A and B are one matrix). It
  * redoes only the value-producing passes of the heavy rows (the outer-product
- * expansion and the multisplit levels, on the layout symbolic computed);
+ * expansion and the multisplit levels, or the copy, on the layout symbolic computed);
  * gmagnus_spgemm_numeric then writes C for the new values into the structure
  * symbolic produced, with the same c_row_ptr. Asynchronous on the plan's
  * stream. Requires GMAGNUS_FLAG_KEEP_PATTERN at gmagnus_plan.
