@@ -1139,8 +1139,8 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(8))) void
     int32_t c[EPT];
     V v[EPT];
     dense_load<BLOCK, EPT>(L, tk.s, tk.e, c, v);
+    __syncthreads();  // everyone has read `grabbed`
     while (true) {
-        __syncthreads();  // the accumulator is clear and everyone has read `grabbed`
         if (threadIdx.x == 0) grabbed = atomicAdd(counter, 1);
         for (int64_t b = tk.s; b < tk.e; b += STEP) {
             int32_t cn[EPT];
@@ -1165,6 +1165,11 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(8))) void
         dense_emit_clear(D, width, tk.a, o.base(tk), o.c_col + tk.t, o.c_val + tk.t, o.err);
         if (nxt >= n_tasks) break;
         tk = tn;
+        // The accumulator is clear and everyone has read `grabbed`. (This barrier
+        // stays at the loop's end: at its head the compiler dropped the wait for
+        // the clearing stores, which reach the barrier over the back edge only, and
+        // a late store cleared a bit that another wave had set for the next chunk.)
+        __syncthreads();
     }
 }
 
