@@ -45,10 +45,12 @@ PAIR_WORKLOADS = {
 }
 HEAVY_KERNELS = ["expand", "histogram", "multisplit", "chunk_symbolic", "chunk_numeric"]
 # Timing classes of one kernel per panel: the roofline is reported for the one
-# of these with the largest device time. ("expand" is by default the chunk-major
-# copy of the B rows in use, k_tile_fill, with the rows it leaves to
-# k_tile_fill_long; with a flag for another order, that order's expansion.)
-SINGLE_KERNEL_CLASSES = {"expand": "k_tile_fill", "multisplit": "k_multisplit"}
+# of these with the largest device time. The kernel of "expand" follows the path
+# that the plans report: the chunk-major copy of the B rows in use (k_tile_fill,
+# with the rows it leaves to k_tile_fill_long) or an expansion.
+SINGLE_KERNEL_CLASSES = ("expand", "multisplit")
+EXPAND_KERNELS = {"copy": "k_tile_fill", "rows_two_level": "k_expand_rows2", "rows": "k_expand_rows",
+                  "slice_split": "k_expand_split", "paper": "k_expand"}
 # Sources a kernel's counter summary depends on (traffic is dropped when they change).
 KERNEL_SOURCES = {"k_tile_fill": ["paper_2607_22866_amd/csrc/tiles.hip", "paper_2607_22866_amd/csrc/common.hpp"],
                   "k_expand_rows2": ["paper_2607_22866_amd/csrc/rowsplit.hip", "paper_2607_22866_amd/csrc/common.hpp"],
@@ -91,7 +93,10 @@ def run_step(g, dA, dB, bounds, timing, acc, c_bufs, extra_flags=0, tau=0):
                                        a, b, info.check_flags))
             products += info.products_total
             acc["_heavy"] = acc.get("_heavy", 0) + info.products_heavy
-            acc.setdefault("_levels", set()).add(info.params.n_levels)
+            # the path that had most of the products names the expand class's kernel
+            paths = acc.setdefault("_paths", {})
+            name = g.PATH_NAMES[info.expansion_path]
+            paths[name] = paths.get(name, 0) + info.products_heavy
             for i, k in enumerate(g.K_NAMES):
                 acc.setdefault(k, [0.0, 0, 0.0])
                 acc[k][0] += info.kernel_ms[i]
@@ -337,15 +342,9 @@ def main():
     roofline = None
     if dom:
         d = kernels[dom]
-        kname = SINGLE_KERNEL_CLASSES[dom]
-        levels = acc.get("_levels", set())
-        ordered = args.slice_split or args.level_by_level
-        if dom == "expand" and (args.paper_expansion or (ordered and levels == {0})):
-            kname = "k_expand"  # also the only expansion without a multisplit level
-        elif dom == "expand" and args.slice_split:
-            kname = "k_expand_split"
-        elif dom == "expand" and args.level_by_level:
-            kname = "k_expand_rows"
+        kname = "k_multisplit"
+        if dom == "expand":
+            kname = EXPAND_KERNELS[max(acc["_paths"], key=acc["_paths"].get)]
         bpl = d["gb_per_step"] * 1e9 / d["launches_per_step"]
         ms = d["ms_per_step"] / d["launches_per_step"]
         achieved = bpl / (ms / 1000.0) / 1e9

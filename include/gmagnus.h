@@ -172,7 +172,7 @@ typedef struct {
     int64_t level_rows_in[GMAGNUS_MAX_LEVELS];     /* input rows of each multisplit level */
     int64_t level_elems_in[GMAGNUS_MAX_LEVELS];    /* input elements of each level */
     int64_t level_heavy_out[GMAGNUS_MAX_LEVELS];   /* heavy chunks produced by each level */
-    int32_t levels_run;            /* levels actually executed (early exit when no heavy chunk) */
+    int32_t levels_run;            /* levels actually executed (early exit when no heavy chunk; none on GMAGNUS_PATH_COPY) */
     int64_t n_leaves_dense;        /* final chunks accumulated densely */
     int64_t n_leaves_hash;         /* final chunks accumulated with the hash map */
     int64_t n_leaves_rank;         /* final chunks accumulated with the bitmap-rank accumulator */
@@ -194,14 +194,16 @@ typedef struct {
     int64_t row_tau;
 } gmagnus_plan_info_t;
 
-/* Expansion orders of the heavy rows (Section III-B), as chosen by
- * gmagnus_expansion_path and reported in gmagnus_plan_info_t. */
+/* The path of the heavy rows, reported in gmagnus_plan_info_t: an expansion
+ * order (Section III-B) as chosen by gmagnus_expansion_path, or the
+ * chunk-major copy, on which nothing is expanded and no level runs. */
 enum {
     GMAGNUS_PATH_NONE = 0,           /* no heavy rows */
     GMAGNUS_PATH_PAPER = 1,          /* C-hat written row by row (Algorithm 4), then split level by level */
     GMAGNUS_PATH_SLICE_SPLIT = 2,    /* first level split during a slice-order expansion (atomic cursors) */
     GMAGNUS_PATH_ROWS = 3,           /* first level split during a chunk-major row-order expansion */
-    GMAGNUS_PATH_ROWS_TWO_LEVEL = 4  /* both levels of a two-level hierarchy split during the row-order expansion */
+    GMAGNUS_PATH_ROWS_TWO_LEVEL = 4, /* both levels of a two-level hierarchy split during the row-order expansion */
+    GMAGNUS_PATH_COPY = 5            /* accumulated per row and column chunk from a chunk-major copy of B's rows */
 };
 
 typedef struct gmagnus_plan_s *gmagnus_plan_t;

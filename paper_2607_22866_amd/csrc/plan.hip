@@ -936,11 +936,6 @@ void tiled_symbolic(gmagnus_plan_s *p, const SliceArrays &sl, int64_t blen_total
         slot_scan(p->slot, t.nh, t.ncp, p->heavy_rows, p->row_nnz, s);
         add_bytes(p, GMAGNUS_K_ROWPTR, 16.0 * regions);
     }
-    p->info.levels_run = p->params.n_levels;
-    if (p->params.n_levels > 0) {
-        p->info.level_rows_in[0] = t.nh;
-        p->info.level_elems_in[0] = p->products_heavy;
-    }
 }
 
 // Heavy path of the symbolic phase: masked CSC, expansion, multisplit
@@ -1046,6 +1041,7 @@ void heavy_symbolic(gmagnus_plan_s *p) {
             }
             ws.hold(keep);
             if (tiled) {
+                p->info.expansion_path = GMAGNUS_PATH_COPY;
                 TileHeavy &t = p->tile;
                 t.nc = tile_chunks(p->B.n_cols);
                 t.ns = sl.n_slices;

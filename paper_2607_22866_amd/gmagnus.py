@@ -28,7 +28,7 @@ FLAG_PAPER_EXPANSION = 16
 FLAG_SLICE_SPLIT = 32
 FLAG_LEVEL_BY_LEVEL = 64
 FLAG_KEEP_PATTERN = 256
-PATH_NAMES = {0: "none", 1: "paper", 2: "slice_split", 3: "rows", 4: "rows_two_level"}
+PATH_NAMES = {0: "none", 1: "paper", 2: "slice_split", 3: "rows", 4: "rows_two_level", 5: "copy"}
 
 STATUS = {0: "SUCCESS", 1: "INVALID_VALUE", 2: "INVALID_CSR", 3: "OUT_OF_MEMORY", 4: "NOT_READY", 5: "HIP",
           6: "UNSUPPORTED"}

@@ -518,7 +518,8 @@ def test_workspace_limit(g):
     assert 0 < info.workspace_peak_bytes <= peak
 
 
-def test_timed_classes_fit_in_wall_time(g):
+@pytest.mark.parametrize("opts", [dict(), dict(dense_width_log2=13)], ids=["copy", "expansion"])
+def test_timed_classes_fit_in_wall_time(g, opts):
     # the per-class device times of one plan do not overlap: their sum stays
     # within the wall time of the calls that produced them
     import time
@@ -527,14 +528,17 @@ def test_timed_classes_fit_in_wall_time(g):
     dA = g.DeviceCSR.from_host(A)
     torch.cuda.synchronize()
     t0 = time.perf_counter()
-    with g.Plan(dA, dA, flags=g.FLAG_TIMING) as p:
+    with g.Plan(dA, dA, flags=g.FLAG_TIMING, **opts) as p:
         p.symbolic()
         p.numeric()
         torch.cuda.synchronize()
         wall_ms = 1000.0 * (time.perf_counter() - t0)
         info = p.info()
     total = sum(info.kernel_ms[i] for i in range(len(g.K_NAMES)))
-    assert info.expansion_path == 3  # one level (C.m = 2^15), split during the row-order expansion
+    # (a forced width: one level, C.m = 2^15, split during the row-order expansion)
+    assert g.PATH_NAMES[info.expansion_path] == ("rows" if opts else "copy")
+    assert info.levels_run == (1 if opts else 0)
+    assert info.level_elems_in[0] == (info.products_heavy if opts else 0)
     assert 0 < total <= wall_ms, (total, wall_ms)
     assert info.kernel_ms[2] > 0 and info.kernel_ms[6] > 0
 
