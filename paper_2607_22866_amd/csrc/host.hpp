@@ -391,7 +391,9 @@ int tile_chunks(int64_t c_m);
 int64_t tile_scan_words(int64_t n);
 // t.cnt and t.part of the slices (cm: ns * nc + 1 words of scratch)
 void tile_parts(const Csr &B, const int32_t *slice_k, const TileHeavy &t, uint32_t *cm, hipStream_t s);
-void tile_fill(const Csr &B, const int32_t *slice_k, const TileHeavy &t, int32_t *long_list, hipStream_t s);
+// (piece_words: tile_piece_words int32 of scratch, the long rows' pieces)
+int64_t tile_piece_words(int64_t n_elems);
+void tile_fill(const Csr &B, const int32_t *slice_k, const TileHeavy &t, int32_t *piece_words, hipStream_t s);
 // cls[k] = 0 for the non-empty B rows that the heavy rows meet, else 1; then
 // (perm: those rows) their numbers, lengths and places
 void tile_mark(const Csr &A, const Csr &B, const int64_t *heavy_rows, int64_t n_heavy, int64_t r0,

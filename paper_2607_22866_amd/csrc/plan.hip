@@ -849,7 +849,6 @@ void tiled_symbolic(gmagnus_plan_s *p, const SliceArrays &sl, int64_t blen_total
     t.ncp = (((int64_t)t.nc + (1 << t.slog) - 1) >> t.slog) << t.slog;
     const int64_t regions = t.nh * t.ncp;
     p->n_slots = t.ncp;
-    int32_t *long_list;
     int64_t n_seg;
     {
         Timed tm(p, GMAGNUS_K_HISTOGRAM, s);
@@ -866,11 +865,11 @@ void tiled_symbolic(gmagnus_plan_s *p, const SliceArrays &sl, int64_t blen_total
         Timed tm(p, GMAGNUS_K_EXPAND, s);
         t.col = ws.alloc<uint16_t>(blen_total);
         t.val = ws.alloc_bytes(VS * std::max<int64_t>(blen_total, 1));
-        long_list = ws.alloc<int32_t>(t.ns + 1);
+        int32_t *pieces = ws.alloc<int32_t>(tile_piece_words(blen_total));
         const TileHeavy tv = t;
         const int32_t *slice_k = sl.slice_k;
-        values_step([=](const Csr &, const Csr &B, hipStream_t st) { tile_fill(B, slice_k, tv, long_list, st); });
-        ws.free(long_list);
+        values_step([=](const Csr &, const Csr &B, hipStream_t st) { tile_fill(B, slice_k, tv, pieces, st); });
+        ws.free(pieces);
         p->info.kernel_launches[GMAGNUS_K_EXPAND] += 1;
         add_bytes(p, GMAGNUS_K_EXPAND, (CS + VS + 2.0 + VS) * blen_total + 4.0 * t.ns * t.nc);
     }

@@ -248,65 +248,67 @@ GM_DEV void tile_copy_row(const CI *row, const V *val, int64_t p0, int64_t p1, i
 }
 
 constexpr int TF_WAVES = 4;
-constexpr int64_t TF_LONG = 2048;  // longer rows are copied in pieces of this many elements by many waves
+constexpr int64_t TF_LONG = 2048;  // longer rows are copied in pieces of this many elements, a wave each
 
-// Rows of at most TF_LONG elements, one wave each; longer ones are listed.
+// Rows of at most TF_LONG elements, one wave each; of longer ones the pieces
+// (slice, first element / TF_LONG) are listed.
 // (A work group per 64 consecutive slices, whose parts share lines in every
 // chunk: 0.79 instead of 0.64 ms, the rows' lengths being too uneven.)
 template <typename CI, typename V>
 __global__ __launch_bounds__(TF_WAVES * GM_WAVE) void k_tile_fill(CsrV<CI, V> B, const int32_t *slice_k, int64_t ns,
                                                                   int nc, const uint32_t *part, int64_t n_elems,
-                                                                  uint16_t *out_col, V *out_val, int32_t *n_long,
-                                                                  int32_t *long_list) {
+                                                                  uint16_t *out_col, V *out_val, int32_t *n_pieces,
+                                                                  int2 *pieces) {
     const int64_t nwaves = (int64_t)gridDim.x * TF_WAVES;
     for (int64_t s = blockIdx.x * (int64_t)TF_WAVES + threadIdx.x / GM_WAVE; s < ns; s += nwaves) {
         const int32_t k = slice_k[s];
         const int64_t b0 = B.rp[k], len = B.rp[k + 1] - b0;
         if (len > TF_LONG) {
-            if ((threadIdx.x & (GM_WAVE - 1)) == 0) long_list[atomicAdd(n_long, 1)] = (int32_t)s;
+            const int lane = threadIdx.x & (GM_WAVE - 1), n = (int)((len + TF_LONG - 1) / TF_LONG);
+            int at = 0;
+            if (lane == 0) at = atomicAdd(n_pieces, n);
+            at = __builtin_amdgcn_readfirstlane(at);
+            for (int q = lane; q < n; q += GM_WAVE) pieces[at + q] = make_int2((int)s, q);
             continue;
         }
         tile_copy_row<CI, V>(B.ci + b0, B.v + b0, 0, len, nc, part + s * nc, n_elems, -1, 0, out_col, out_val);
     }
 }
 
-// The listed rows: blockIdx.y strides over the list, the waves of blockIdx.x
-// over a row's pieces.
+// The listed pieces, one wave each. (A list of rows, 32 waves a row: 5.5 ms for
+// 3.3e4 rows of 3072 elements, two of whose 32 waves had work; so 1.4.)
 template <typename CI, typename V>
 __global__ __launch_bounds__(TF_WAVES * GM_WAVE) void k_tile_fill_long(CsrV<CI, V> B, const int32_t *slice_k,
                                                                        int64_t ns, int nc, const uint32_t *part,
                                                                        int64_t n_elems, uint16_t *out_col, V *out_val,
-                                                                       const int32_t *n_long,
-                                                                       const int32_t *long_list) {
+                                                                       const int32_t *n_pieces, const int2 *pieces) {
     const int lane = threadIdx.x & (GM_WAVE - 1);
-    const int n = *n_long;
-    for (int i = blockIdx.y; i < n; i += gridDim.y) {
-        const int64_t s = long_list[i];
+    const int n = *n_pieces, nwaves = (int)gridDim.x * TF_WAVES;
+    for (int i = (int)blockIdx.x * TF_WAVES + (int)(threadIdx.x / GM_WAVE); i < n; i += nwaves) {
+        const int2 piece = pieces[i];
+        const int64_t s = piece.x, p0 = piece.y * TF_LONG;
         const int32_t k = slice_k[s];
         const int64_t b0 = B.rp[k], len = B.rp[k + 1] - b0;
         const CI *row = B.ci + b0;
-        const int64_t step = (int64_t)gridDim.x * TF_WAVES * TF_LONG;
-        for (int64_t p0 = (blockIdx.x * (int64_t)TF_WAVES + threadIdx.x / GM_WAVE) * TF_LONG; p0 < len; p0 += step) {
-            // chunk open at p0 and where it starts in the row: 64 bounds a step
-            // (a chain of binary search steps took longer than the copy)
-            const int64_t f64 = (int64_t)row[p0] >> TILE_LOG2;
-            int64_t lo = 0, hi = p0;  // the answer is in [lo, hi]
-            while (hi > lo) {
-                const int64_t span = hi - lo, x = lo + span * lane / GM_WAVE;
-                const uint64_t below = ballot(((int64_t)row[x] >> TILE_LOG2) < f64);
-                const int c = __popcll(below);  // (a prefix: the row is sorted)
-                if (c == 0) {
-                    hi = lo;
-                    break;
-                }
-                const int64_t nlo = lo + span * (c - 1) / GM_WAVE + 1;
-                if (c < GM_WAVE) hi = lo + span * c / GM_WAVE;
-                lo = nlo;
+        // chunk open at p0 and where it starts in the row: 64 bounds a step
+        // (a chain of binary search steps took longer than the copy)
+        const int64_t f64 = (int64_t)row[p0] >> TILE_LOG2;
+        int64_t lo = 0, hi = p0;  // the answer is in [lo, hi]
+        while (hi > lo) {
+            const int64_t span = hi - lo, x = lo + span * lane / GM_WAVE;
+            const uint64_t below = ballot(((int64_t)row[x] >> TILE_LOG2) < f64);
+            const int c = __popcll(below);  // (a prefix: the row is sorted)
+            if (c == 0) {
+                hi = lo;
+                break;
             }
-            const int64_t p1 = p0 + TF_LONG < len ? p0 + TF_LONG : len;
-            tile_copy_row<CI, V>(row, B.v + b0, p0, p1, nc, part + s * nc, n_elems, (int)(f64 < nc ? f64 : nc - 1), lo,
-                                 out_col, out_val);
+            const int64_t nlo = lo + span * (c - 1) / GM_WAVE + 1;
+            if (c < GM_WAVE) hi = lo + span * c / GM_WAVE;
+            lo = nlo;
         }
+        const int64_t p1 = p0 + TF_LONG < len ? p0 + TF_LONG : len;
+        tile_copy_row<CI, V>(row, B.v + b0, p0, p1, nc, part + s * nc, n_elems, (int)(f64 < nc ? f64 : nc - 1), lo, out_col,
+                             out_val);
     }
 }
 
@@ -1055,18 +1057,25 @@ void tile_parts(const Csr &B, const int32_t *slice_k, const TileHeavy &t, uint32
 
 int64_t tile_scan_words(int64_t n) { return (n + SC_TILE - 1) / SC_TILE + 1; }
 
-void tile_fill(const Csr &B, const int32_t *slice_k, const TileHeavy &t, int32_t *long_list, hipStream_t s) {
+// The rows in pieces hold more than TF_LONG elements each: fewer than twice as many pieces as whole TF_LONGs.
+int64_t tile_most_pieces(int64_t n_elems) { return n_elems > TF_LONG ? 2 * (n_elems / TF_LONG) + 1 : 0; }
+int64_t tile_piece_words(int64_t n_elems) { return 2 + 2 * tile_most_pieces(n_elems); }
+
+void tile_fill(const Csr &B, const int32_t *slice_k, const TileHeavy &t, int32_t *piece_words, hipStream_t s) {
     if (t.ns <= 0) return;
-    fill<int32_t>(long_list, 0, 1, s);
+    int2 *pieces = reinterpret_cast<int2 *>(piece_words + 2);
+    fill<int32_t>(piece_words, 0, 1, s);
     with_types(B, [&](auto ci, auto v) {
         using CI = decltype(ci);
         using V = decltype(v);
         V *ov = static_cast<V *>(t.val);
         hipLaunchKernelGGL((k_tile_fill<CI, V>), dim3(grid_for(t.ns, TF_WAVES, 65536)), dim3(TF_WAVES * GM_WAVE), 0, s,
-                           typed<CI, V>(B), slice_k, t.ns, t.nc, t.part, t.n_elems, t.col, ov, long_list, long_list + 1);
+                           typed<CI, V>(B), slice_k, t.ns, t.nc, t.part, t.n_elems, t.col, ov, piece_words, pieces);
         GM_CHECK_LAUNCH();
-        hipLaunchKernelGGL((k_tile_fill_long<CI, V>), dim3(8, 2048), dim3(TF_WAVES * GM_WAVE), 0, s, typed<CI, V>(B),
-                           slice_k, t.ns, t.nc, t.part, t.n_elems, t.col, ov, long_list, long_list + 1);
+        const int64_t most = tile_most_pieces(t.n_elems);
+        if (most == 0) return;
+        hipLaunchKernelGGL((k_tile_fill_long<CI, V>), dim3(grid_for(most, TF_WAVES, 16384)), dim3(TF_WAVES * GM_WAVE), 0,
+                           s, typed<CI, V>(B), slice_k, t.ns, t.nc, t.part, t.n_elems, t.col, ov, piece_words, pieces);
         GM_CHECK_LAUNCH();
     });
 }

@@ -28,7 +28,7 @@ def g():
     return gmagnus
 
 
-def _product(g, A, B, it=torch.int32, vt=torch.float64, **opts):
+def _product(g, A, B, it=torch.int32, vt=torch.float64, path=None, **opts):
     dA, dB = (g.DeviceCSR.from_host(m, index_dtype=it, value_dtype=vt) for m in (A, B))
     with g.Plan(dA, dB, **opts) as p:
         rp, _ = p.symbolic()
@@ -36,6 +36,8 @@ def _product(g, A, B, it=torch.int32, vt=torch.float64, **opts):
         info = p.info()
     torch.cuda.synchronize()
     assert info.check_flags == 0 and info.n_heavy_rows > 0
+    if path:
+        assert g.PATH_NAMES[info.expansion_path] == path
     return rp.cpu().numpy(), col.cpu().numpy(), val.cpu().numpy()
 
 
@@ -83,6 +85,23 @@ def test_types(g, it, vt, m, k, n, a_d, b_d):
     if f32:
         A, B = (x.with_values(x.val.astype(np.float32).astype(np.float64)) for x in (A, B))
     compare_full(*_product(g, A, B, it, vt), oracle.spgemm(A, B), f32=f32)
+
+
+@pytest.mark.parametrize("it,vt", [(torch.int32, torch.float64), (torch.int64, torch.float32)])
+def test_rows_copied_in_pieces(g, it, vt):
+    # B rows around whole pieces of 2048 elements, in no order of length (an
+    # empty one among them), over three chunks
+    lens = [2049, 1, 2048, 4097, 0, 2047, 4096, 6145, 64, 4095, 12289]
+    n = 40_000
+    rng = np.random.default_rng(31)
+    cols = [np.sort(rng.choice(n, k, replace=False)) for k in lens]
+    rp = np.concatenate([[0], np.cumsum(lens)])
+    B = wl.CSR(len(lens), n, rp.astype(np.int64), np.concatenate(cols).astype(np.int32), rng.random(int(rp[-1])))
+    A = wl.uniform(24, len(lens), 0.8, 32)
+    f32 = vt == torch.float32
+    if f32:
+        A, B = (x.with_values(x.val.astype(np.float32).astype(np.float64)) for x in (A, B))
+    compare_full(*_product(g, A, B, it, vt, path="copy"), oracle.spgemm(A, B), f32=f32)
 
 
 @pytest.mark.parametrize("seed,skew", [(5, (0.57, 0.19, 0.19)), (6, (0.7, 0.12, 0.12))])
