@@ -55,6 +55,12 @@ SIZES = [
     (8, 4000, 16 * 16384 + 1, 300, 20),    # and one column past it
     (8, 4000, 37 * 16384 - 3, 300, 40),    # several groups, merged regions
     (12, 500, 17 * 16384, 60, 100),        # about 350 products a region group
+    # regions of up to 2048 and up to 4096 distinct columns: the most that are
+    # summed by 16-wave groups, and one more
+    (512, 300, 2000, 60, 60),
+    (513, 300, 2000, 60, 60),
+    (512, 300, 3500, 60, 60),
+    (513, 300, 3500, 60, 60),
     # the lists' tiles of 8, 16, 32 and 64 chunks: full, and a chunk past it
     (8, 2000, 8 * 16384, 300, 20),
     (8, 2000, 8 * 16384 + 1, 300, 20),
