@@ -47,34 +47,40 @@ SIZES = [
     (9, 300, 16384, 40, 200),     # exactly one chunk
     (9, 300, 16385, 40, 200),     # one column in a second chunk
     (5, 40, 300, 30, 290),        # fewer columns than a wave's words
-    (6, 300, 3 * 16384 + 5, 250, 40),      # regions of about 3300 products
-    (4, 400, 40000, 200, 900),    # dense: over 7168 distinct columns a chunk
-    (3, 300, 32768, 280, 1000),   # more long parts than the shared list holds
-    (3, 50, 70000, 6, 20000),     # B rows copied in pieces, parts of thousands
-    (8, 4000, 16 * 16384, 300, 20),        # one whole group of 16 chunks
-    (8, 4000, 16 * 16384 + 1, 300, 20),    # and one column past it
-    (8, 4000, 37 * 16384 - 3, 300, 40),    # several groups, merged regions
-    (12, 500, 17 * 16384, 60, 100),        # about 350 products a region group
+    (9, 300, 3 * 16384 + 5, 250, 40),      # regions of about 3300 products
+    (9, 400, 40000, 200, 900),    # dense: over 7168 distinct columns a chunk
+    (9, 300, 32768, 280, 1000),   # more long parts than the shared list holds
+    (9, 50, 70000, 6, 20000),     # B rows copied in pieces, parts of thousands
+    # regions of 4, 8 and 16 merged chunks, and of both sizes of group
+    (12, 250, 17 * 16384, 60, 100),
+    (40, 100, 16 * 16384, 60, 64),
+    (40, 100, 32 * 16384, 40, 96),
+    (40, 100, 37 * 16384 - 3, 40, 111),
+    # the lists' tiles of 8, 16, 32 and 64 chunks (16: also the most chunks whose
+    # lists are adjacent): full, and a chunk past it
+    (9, 300, 8 * 16384, 200, 64),
+    (9, 300, 8 * 16384 + 1, 200, 64),
+    (9, 300, 16 * 16384, 150, 100),
+    (9, 300, 16 * 16384 + 1, 150, 100),
+    (9, 300, 32 * 16384, 100, 200),
+    (9, 300, 32 * 16384 + 1, 100, 200),
+    (9, 300, 64 * 16384, 100, 400),
+    (9, 300, 64 * 16384 + 1, 100, 400),
     # regions of up to 2048 and up to 4096 distinct columns: the most that are
     # summed by 16-wave groups, and one more
     (512, 300, 2000, 60, 60),
     (513, 300, 2000, 60, 60),
     (512, 300, 3500, 60, 60),
     (513, 300, 3500, 60, 60),
-    # the lists' tiles of 8, 16, 32 and 64 chunks: full, and a chunk past it
-    (8, 2000, 8 * 16384, 300, 20),
-    (8, 2000, 8 * 16384 + 1, 300, 20),
-    (8, 2000, 32 * 16384, 300, 20),
-    (8, 2000, 32 * 16384 + 1, 300, 20),
-    (8, 2000, 65 * 16384, 300, 20),
 ]
+DENSE, LONG_PARTS, MERGED = SIZES[5], SIZES[6], SIZES[10]
 
 
 @pytest.mark.parametrize("m,k,n,a_d,b_d", SIZES)
 def test_sizes(g, m, k, n, a_d, b_d):
     A, B = wl.erdos_renyi(m, k, a_d, 11), wl.erdos_renyi(k, n, b_d, 12)
     ref = oracle.spgemm(A, B)
-    rp, col, val = _product(g, A, B)
+    rp, col, val = _product(g, A, B, path="copy")
     compare_full(rp, col, val, ref)
     rp2, col2, _ = _product(g, A, B, flags=g.FLAG_LEVEL_BY_LEVEL)
     assert np.array_equal(rp, rp2) and np.array_equal(col, col2)
@@ -82,7 +88,7 @@ def test_sizes(g, m, k, n, a_d, b_d):
 
 @pytest.mark.parametrize("it,vt", [(torch.int32, torch.float32), (torch.int64, torch.float64),
                                    (torch.int64, torch.float32)])
-@pytest.mark.parametrize("m,k,n,a_d,b_d", [SIZES[5], SIZES[6], SIZES[10]])
+@pytest.mark.parametrize("m,k,n,a_d,b_d", [DENSE, LONG_PARTS, MERGED])
 def test_types(g, it, vt, m, k, n, a_d, b_d):
     if it == torch.int32 and vt == torch.float32:
         n = min(n, 1 << 18)  # (fp32 values with int32 columns: one multisplit level at most)
@@ -90,7 +96,7 @@ def test_types(g, it, vt, m, k, n, a_d, b_d):
     f32 = vt == torch.float32
     if f32:
         A, B = (x.with_values(x.val.astype(np.float32).astype(np.float64)) for x in (A, B))
-    compare_full(*_product(g, A, B, it, vt), oracle.spgemm(A, B), f32=f32)
+    compare_full(*_product(g, A, B, it, vt, path="copy"), oracle.spgemm(A, B), f32=f32)
 
 
 @pytest.mark.parametrize("it,vt", [(torch.int32, torch.float64), (torch.int64, torch.float32)])
@@ -126,6 +132,6 @@ def test_rmat_panel_and_new_values(g, seed, skew):
             if X is A2:
                 p.update_values(torch.from_numpy(A2.val).cuda())
             col, val = p.numeric()
-            assert p.info().check_flags == 0 and p.info().n_heavy_rows > 0
+            assert p.info().check_flags == 0 and g.PATH_NAMES[p.info().expansion_path] == "copy"
             compare_full(rp.cpu().numpy(), col.cpu().numpy(), val.cpu().numpy(),
                          oracle.spgemm(X, X, rows=np.arange(r1)))
