@@ -802,6 +802,25 @@ int32_t expansion_path(const gmagnus_params_t &P, int64_t n_heavy, int64_t produ
 
 namespace {
 
+// Memory of that path, about: the slices' counts and starts, the copy, the
+// entries, the regions, the lists, the bitmaps.
+int64_t tile_bytes(const gmagnus_plan_s *p, int64_t n_slices, int64_t blen_total) {
+    const int64_t nc = tile_chunks(std::max<int64_t>(p->B.n_cols, 1));
+    return n_slices * nc * 10 + blen_total * (2 + p->vsize) + p->nnz_heavy * (8 + p->vsize) + p->n_heavy * nc * 74 +
+           p->nnz_heavy * nc * 12 + 2 * p->products_heavy;
+}
+
+// The heavy rows meet B rows about as long as the average one: nothing is popular.
+bool even_rows(const gmagnus_plan_s *p) {
+    return 4.0 * (double)p->products_heavy * (double)p->B.n_rows < 5.0 * (double)p->nnz_heavy * (double)p->B.nnz;
+}
+
+// The expansion's first level makes chunks of 384 products or more (288: 5.0 ms
+// for 2e8 products on 256 chunks, 700: 3.7, 2000: 3.3).
+bool split_cheap(const gmagnus_plan_s *p) {
+    return p->params.n_levels > 0 && p->products_heavy >= 384 * p->n_heavy * (int64_t)p->params.v_chunks[0];
+}
+
 // Whether the heavy rows are accumulated straight from a chunk-major copy of
 // the B rows they use (tiles.hip) instead of being expanded and split in
 // memory. A caller that forces a hierarchy or an order gets it.
@@ -818,11 +837,22 @@ bool tiles_possible(const gmagnus_plan_s *p) {
         p->nnz_heavy * nc >= ((int64_t)1 << 40))
         return false;
     // Below one product per (entry, chunk) most of what the lists read would be
-    // empty. R-MAT panels stay above it, and gain down to the 3.5 products of
-    // scale 23 (panels of 2e8 products, expansion -> copy: 15.5 products a pair
-    // (scale 20) 4.15 -> 3.04 ms, 5.7 (scale 22) 3.91 -> 3.48, 3.5 (scale 23)
-    // 4.25 -> 3.85).
-    return H >= p->nnz_heavy * nc;
+    // empty, and their memory is refused below. (R-MAT panels of 1e8 to 3e8
+    // products, expansion -> copy: 17 products a pair (scale 20) 4.6 -> 3.2 ms, 6.3
+    // (scale 22) 4.4 -> 3.5, 4.4 (scale 23) 5.7 -> 4.6; uniform rows on 64 chunks 1.5
+    // products a pair 5.4 -> 3.8.)
+    if (H < p->nnz_heavy * nc) return false;
+    if (tile_bytes(p, 0, 0) > H * (4 + p->vsize)) return false;
+    // Few rows: each B row serves only a few entries, and a region is one work
+    // group's (uniform rows, 2 of 5e6 products a chunk 2.5 -> 3.5 ms, 4 rows 3.0 ->
+    // 3.6, 8 rows 3.9 -> 3.9, 16 rows 5.2 -> 4.3; the first 4 rows of R-MAT 18 1.44 ->
+    // 1.22, of R-MAT 20 2.57 -> 2.36, 4.9 either way of R-MAT 22). Without a level
+    // the expansion has no more work groups either (2 uniform rows 5.1 -> 3.5).
+    if (p->n_heavy < 8 && p->params.n_levels > 0 && (nc > 128 || even_rows(p))) return false;
+    // Short parts of uniform rows on many chunks, 256 of them: 2 products a part
+    // 3.7 -> 4.1 ms, 3 products 3.6 -> 3.7, 4 products 3.7 -> 3.5 (128 chunks, 2
+    // products: 3.6 -> 3.3).
+    return !(nc > 128 && even_rows(p) && split_cheap(p) && 2 * H < 5 * p->nnz_heavy * nc);
 }
 
 // ... and whether it takes no more memory than the expansion's columns and
@@ -830,9 +860,18 @@ bool tiles_possible(const gmagnus_plan_s *p) {
 bool use_tiles(const gmagnus_plan_s *p, int64_t n_slices, int64_t blen_total) {
     const int64_t H = p->products_heavy, nc = tile_chunks(std::max<int64_t>(p->B.n_cols, 1));
     if (blen_total >= ((int64_t)1 << 31)) return false;
-    const int64_t bytes = n_slices * nc * 10 + blen_total * (2 + p->vsize) + p->nnz_heavy * (8 + p->vsize) +
-                          p->n_heavy * nc * 74 + p->nnz_heavy * nc * 12 + 2 * H;
-    return bytes <= H * (4 + p->vsize);
+    if (tile_bytes(p, n_slices, blen_total) > H * (4 + p->vsize)) return false;
+    if (nc <= 64 || !even_rows(p) || !split_cheap(p)) return true;
+    // Uniform rows on many chunks, again. Parts of 5 products and more: as long as
+    // the copy is used often enough (6 products a part: 2 products per element of
+    // the copy 3.7 -> 4.7 ms, 3 per element 5.5 -> 5.2, 6 per element 3.6 -> 3.2).
+    if (H >= 5 * p->nnz_heavy * nc) return 2 * H >= 5 * blen_total;
+    // Shorter parts: they come from wherever the chunks that a region spans lie in
+    // the copy; past 16 MB of these each part costs lines from behind the L2s
+    // (4 products a part: 8 MB 2.07 -> 1.84 ms, 16 MB 2.12 -> 2.12, 31 MB 2.16 -> 2.55).
+    int64_t span = 1;
+    while (span < 16 && 2 * span * H <= TILE_MERGE * p->n_heavy * nc) span *= 2;
+    return blen_total * (2 + p->vsize) * span <= nc * ((int64_t)16 << 20);
 }
 
 // The tiled heavy path from the slices on: chunk-major B, region sizes and

@@ -1,7 +1,7 @@
 """Heavy rows accumulated from the chunk-major copy of B (the default path of
 rows of more than 3456 products when a row's entries meet a chunk of 2^14
-columns with one product or more on average), at the sizes where it can go
-wrong: column counts around whole chunks and whole groups of 16 chunks, every
+columns with one product or more on average; test_rule has the rule's lines), at
+the sizes where it can go wrong: column counts around whole chunks and whole groups of 16 chunks, every
 region size (one wave up to the dense accumulator), parts long enough to be
 shared by a work group's waves (and more of them than the shared list holds),
 B rows copied in pieces, all type pairs, new values on kept patterns. Every
@@ -97,6 +97,21 @@ def test_types(g, it, vt, m, k, n, a_d, b_d):
     if f32:
         A, B = (x.with_values(x.val.astype(np.float32).astype(np.float64)) for x in (A, B))
     compare_full(*_product(g, A, B, it, vt, path="copy"), oracle.spgemm(A, B), f32=f32)
+
+
+@pytest.mark.parametrize("m,k,n,a_d,b_d,path", [
+    (7, 300, 16384, 250, 200, "rows"),  # fewer than 8 uniform rows
+    (8, 300, 16384, 250, 200, "copy"),
+    (7, 300, 8192, 250, 200, "copy"),   # ... but without a level
+    (9, 300, 64 * 16384, 150, 30, "rows_two_level"),     # fewer products than (entry, chunk) pairs
+    (9, 100, 256 * 16384, 100, 512, "rows_two_level"),   # 2 products a pair of uniform rows on 256 chunks
+    (9, 100, 256 * 16384, 100, 1024, "copy"),            # 4 products a pair
+    (40, 100, 256 * 16384, 20, 560, "copy"),             # 2.2 products a pair, small first-level chunks
+])
+def test_rule(g, m, k, n, a_d, b_d, path):
+    # uniform rows on both sides of each line of the rule
+    A, B = wl.erdos_renyi(m, k, a_d, 41), wl.erdos_renyi(k, n, b_d, 42)
+    compare_full(*_product(g, A, B, path=path), oracle.spgemm(A, B))
 
 
 @pytest.mark.parametrize("it,vt", [(torch.int32, torch.float64), (torch.int64, torch.float32)])
