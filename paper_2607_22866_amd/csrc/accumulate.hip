@@ -117,7 +117,7 @@ template <int TS>
 GM_DEV void hash_insert_key(int32_t *keys, int32_t c, int32_t *counter) {
     uint32_t h = hash_slot<TS>(c);
     for (int probe = 0; probe < TS; ++probe) {
-        int32_t old = ((volatile int32_t *)keys)[h];
+        int32_t old = lds_peek(&keys[h]);
         if (old == -1) {
             old = atomicCAS(&keys[h], -1, c);
             if (old == -1) {
@@ -134,7 +134,7 @@ template <int TS, typename V>
 GM_DEV void hash_insert_add(int32_t *keys, V *vals, int32_t c, V v) {
     uint32_t h = hash_slot<TS>(c);
     for (int probe = 0; probe < TS; ++probe) {
-        int32_t old = ((volatile int32_t *)keys)[h];
+        int32_t old = lds_peek(&keys[h]);
         if (old == -1) {
             old = atomicCAS(&keys[h], -1, c);
             if (old == -1) old = c;
@@ -236,7 +236,7 @@ GM_DEV void dense_clear(DenseLdsT<BLOCK, WMAX, VALS, V> &L, int width, bool num)
 template <int BLOCK, int WMAX, bool VALS, typename V>
 GM_DEV void dense_set(DenseLdsT<BLOCK, WMAX, VALS, V> &L, int c) {
     const uint32_t bit = 1u << (c & 31);
-    if (!(((volatile uint32_t *)L.bits)[c >> 5] & bit)) atomicOr(&L.bits[c >> 5], bit);
+    if (!(lds_peek(&L.bits[c >> 5]) & bit)) atomicOr(&L.bits[c >> 5], bit);
 }
 
 template <int BLOCK, int WMAX, typename V>
@@ -460,7 +460,7 @@ __global__ __launch_bounds__(GM_WAVE) void k_light_hash_sym(CsrV<CI, NoV> A, Csr
     gustavson_row<GM_WAVE, false>(A, B, A.rp[r0 + r], A.rp[r0 + r + 1], light_base(minc, r), G, [&](int32_t c, NoV) {
         uint32_t h = ((uint32_t)c * 0x9E3779B1u) >> shift;
         for (int probe = 0; probe <= mask; ++probe) {  // (as hash_insert_key)
-            int32_t old = ((volatile int32_t *)keys)[h];
+            int32_t old = lds_peek(&keys[h]);
             if (old == -1) {
                 old = atomicCAS(&keys[h], -1, c);
                 if (old == -1) {
@@ -1240,7 +1240,7 @@ GM_DEV uint32_t rank_mark(uint32_t *bits, int nwords, const int32_t (&c)[EPT], i
             const int cq = c[q] - lo;
             const int w = cq >> 5;
             const uint32_t bit = 1u << (cq & 31);
-            if (!(((volatile uint32_t *)bits)[w] & bit)) {
+            if (!(lds_peek(&bits[w]) & bit)) {
                 const uint32_t old = atomicOr(&bits[w], bit);
                 if (!(old & bit)) {
                     fresh |= 1u << q;

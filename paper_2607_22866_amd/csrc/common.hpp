@@ -89,6 +89,12 @@ GM_DEV void wave_lds_fence() {
     __builtin_amdgcn_wave_barrier();
 }
 
+// A word of LDS that other threads of the work group may be changing, read now.
+// (A volatile read keeps the generic address: a flat load, through the memory
+// pipeline.)
+template <typename T>
+GM_DEV T lds_peek(const T *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); }
+
 template <typename T>
 GM_DEV T wave_incl_scan(T x) {
     const int lane = threadIdx.x & (GM_WAVE - 1);

@@ -80,7 +80,7 @@ struct RankLds {
 // several lanes on one word take turns.)
 GM_DEV bool rank_mark(RankWord *w, uint32_t bit) {
     const uint32_t m = 1u << bit;
-    if (((volatile uint32_t &)w->bits) & m) return false;
+    if (lds_peek(&w->bits) & m) return false;
     return !(__hip_atomic_fetch_or(&w->bits, m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) & m);
 }
 

@@ -841,7 +841,7 @@ __global__ __launch_bounds__(BLOCK) void k_tile_sym(TileArgs<float> t, uint32_t 
                                     [&](uint32_t c, float) {
                                         // (most products of a large region meet a column already marked, and
                                         // atomics of several lanes on one word take turns)
-                                        if (!(((volatile uint32_t *)bits)[c >> 5] & (1u << (c & 31)))) bit_or(bits, c);
+                                        if (!(lds_peek(&bits[c >> 5]) & (1u << (c & 31)))) bit_or(bits, c);
                                     });
     __syncthreads();
     int32_t n = 0;
