@@ -330,17 +330,25 @@ constexpr int TAU_MAX = 6912;    // products of a light chunk at most
 constexpr int LIGHT_MAX = 3456;  // products of a light row at most
 
 // Bins of the light rows outside a window, by products: one wave (4 or 8
-// products a lane) up to 512, then work groups of 4 products a thread. The
-// numeric phase sums by rank (rank.hpp), the symbolic phase counts by rank
-// above 512 products and with a hash table up to there. Against the LSD radix
+// products a lane) up to 512, then work groups of 4 products a thread (8 in the
+// last bin). The numeric phase sums by rank (rank.hpp); the symbolic phase counts
+// by rank from 513 to 2048 products, else with a hash table. Against the LSD radix
 // sort, the hash table with a bitonic sort and the hash counts that these rows
 // took before (ms, one MI355X): 16 x 16 products a row over 2^22 columns
 // numeric 10.4 -> 8.9; 40 x 40 over 250007 columns (64-bit) numeric 7.8 -> 3.8,
 // symbolic 1.55 -> 1.20; 27-point stencil numeric 4.2 -> 2.9, symbolic 2.0 ->
 // 1.8; 6 x 9 products a row numeric 0.63 -> 0.26. Counting by rank up to 512
 // products lost to the hash table: 5.8 against 3.5 for 256 products over 2^22
-// columns (three levels of words), 0.19 against 0.17 for 54.
+// columns (three levels of words), 0.19 against 0.17 for 54. So it did in the
+// last bin, whatever the repeats (1e5 rows of 2401 products over 2^22 columns 2.37
+// against 0.92, over 250007 1.78 against 0.94; 5e4 rows of 3000 products on 1000
+// columns 1.00 against 0.40, on 100 columns 0.90 against 0.29). Between, rows over
+// few columns in all gain by rank (1e5 of 2025 products, 250007 columns: 0.49
+// against 0.71 with a table of 8192), rows with many repeats lose (5e4 of 2000
+// products on 32 columns: 0.22 against 0.20).
 constexpr int RB_CAP[5] = {256, 512, 1024, 2048, 3584};
+constexpr int HASH_R4 = 8192;  // slots (16384: 1.37 against 0.92 ms for the first of these, half the work groups a CU)
+static_assert(HASH_R4 >= 2 * LIGHT_MAX, "at least two slots a product");
 static_assert(RB_CAP[4] >= LIGHT_MAX, "the largest bin holds every light row");
 GM_DEV int rank_bin(int64_t p) { return p <= RB_CAP[0] ? 0 : p <= RB_CAP[1] ? 1 : p <= RB_CAP[2] ? 2 : p <= RB_CAP[3] ? 3 : 4; }
 
@@ -440,24 +448,24 @@ GM_DEV CI light_base(const CI *minc, int64_t r) {
     return sizeof(CI) == 8 ? minc[r] : (CI)0;
 }
 
-// Counts the distinct columns of a small row, one wave per row: the table
-// takes the smallest power of two of at least four slots a product (16 x 16
-// products a row over 2^22 columns: 3.5 ms with four slots, 4.7 with two).
-template <int TS, typename CI>
-__global__ __launch_bounds__(GM_WAVE) void k_light_hash_sym(CsrV<CI, NoV> A, CsrV<CI, NoV> B, int64_t r0,
+// Counts the distinct columns of a row: the table takes the smallest power of
+// two of at least four slots a product (16 x 16 products a row over 2^22 columns:
+// 3.5 ms with four slots, 4.7 with two), at most TS.
+template <int BLOCK, int TS, typename CI>
+__global__ __launch_bounds__(BLOCK) void k_light_hash_sym(CsrV<CI, NoV> A, CsrV<CI, NoV> B, int64_t r0,
                                                             const int64_t *items, const int64_t *ip, const CI *minc,
                                                             int64_t *row_nnz) {
     __shared__ __align__(16) int32_t keys[TS];
-    __shared__ GusLds<GM_WAVE, NoV> G;
+    __shared__ GusLds<BLOCK, NoV> G;
     __shared__ int32_t counter;
     const int64_t r = items[xcd_run()];
     const int p = (int)ip[r];
     const int lg = 32 - __clz(4 * p - 1) > 6 ? 32 - __clz(4 * p - 1) : 6;
     const int shift = 32 - (1 << lg <= TS ? lg : __builtin_ctz(TS)), mask = (1 << (32 - shift)) - 1;
-    for (int i = threadIdx.x * 4; i <= mask; i += GM_WAVE * 4) *(int4 *)&keys[i] = make_int4(-1, -1, -1, -1);
+    for (int i = threadIdx.x * 4; i <= mask; i += BLOCK * 4) *(int4 *)&keys[i] = make_int4(-1, -1, -1, -1);
     if (threadIdx.x == 0) counter = 0;
     __syncthreads();
-    gustavson_row<GM_WAVE, false>(A, B, A.rp[r0 + r], A.rp[r0 + r + 1], light_base(minc, r), G, [&](int32_t c, NoV) {
+    gustavson_row<BLOCK, false>(A, B, A.rp[r0 + r], A.rp[r0 + r + 1], light_base(minc, r), G, [&](int32_t c, NoV) {
         uint32_t h = ((uint32_t)c * 0x9E3779B1u) >> shift;
         for (int probe = 0; probe <= mask; ++probe) {  // (as hash_insert_key)
             int32_t old = lds_peek(&keys[h]);
@@ -1584,10 +1592,10 @@ void light_symbolic(const Csr &A, const Csr &B, int64_t r0, int bin, const int64
             launch_items(k_light_win_sym<512, WIN2, CI>, 512, n, s, a, b, r0, items, minc, maxc, row_nnz);
             break;
         case LIGHT_R0:
-            launch_items(k_light_hash_sym<4 * RB_CAP[0], CI>, 64, n, s, a, b, r0, items, ip, minc, row_nnz);
+            launch_items(k_light_hash_sym<64, 4 * RB_CAP[0], CI>, 64, n, s, a, b, r0, items, ip, minc, row_nnz);
             break;
         case LIGHT_R1:
-            launch_items(k_light_hash_sym<4 * RB_CAP[1], CI>, 64, n, s, a, b, r0, items, ip, minc, row_nnz);
+            launch_items(k_light_hash_sym<64, 4 * RB_CAP[1], CI>, 64, n, s, a, b, r0, items, ip, minc, row_nnz);
             break;
         case LIGHT_R2:
             launch_rank(k_light_rank_sym<256, RB_CAP[2], 1, CI>, 256, 1, n, s, a, b, r0, items, n, minc, maxc, row_nnz);
@@ -1596,7 +1604,7 @@ void light_symbolic(const Csr &A, const Csr &B, int64_t r0, int bin, const int64
             launch_rank(k_light_rank_sym<512, RB_CAP[3], 1, CI>, 512, 1, n, s, a, b, r0, items, n, minc, maxc, row_nnz);
             break;
         case LIGHT_R4:
-            launch_rank(k_light_rank_sym<896, RB_CAP[4], 1, CI>, 896, 1, n, s, a, b, r0, items, n, minc, maxc, row_nnz);
+            launch_items(k_light_hash_sym<512, HASH_R4, CI>, 512, n, s, a, b, r0, items, ip, minc, row_nnz);
             break;
         default: break;
         }

@@ -86,3 +86,15 @@ def test_empty_and_long_parts(g):
     col = np.concatenate(rows).astype(np.int32)
     A = wl.CSR(4, 4000, rp, col, np.random.default_rng(9).uniform(-1.0, 1.0, col.size))
     check(g, A, B)
+
+
+@pytest.mark.parametrize("per_row", [20, 40, 41, 60, 69])
+@pytest.mark.parametrize("distinct", [50, 51, 300])
+def test_many_repeats(g, per_row, distinct):
+    # rows of 1000, 2000, 2050, 3000 and 3450 products that meet `distinct` columns
+    # spread over 2^20, up to 69 times each
+    rng = np.random.default_rng(12)
+    pool = np.sort(rng.choice(1 << 20, distinct, replace=False)).astype(np.int32)
+    cols = [pool[np.sort(rng.choice(distinct, 50, replace=False))] for _ in range(80)]
+    B = wl.CSR(80, 1 << 20, np.arange(81, dtype=np.int64) * 50, np.concatenate(cols), rng.uniform(-1.0, 1.0, 4000))
+    check(g, wl.erdos_renyi(30, 80, per_row, 13), B)
