@@ -114,6 +114,34 @@ def test_rule(g, m, k, n, a_d, b_d, path):
     compare_full(*_product(g, A, B, path=path), oracle.spgemm(A, B))
 
 
+# (memory next to what the rule admits: most of it the copy, the lists, the regions)
+@pytest.mark.parametrize("m,k,n,a_d,b_d", [(9, 2000, 16384, 40, 200), (40, 100, 32 * 16384, 100, 46),
+                                           (40, 100, 256 * 16384, 20, 560), DENSE])
+@pytest.mark.parametrize("flags", [0, 256], ids=["", "keep_pattern"])
+def test_memory(g, m, k, n, a_d, b_d, flags):
+    # a workspace limit that the expansion of the same product keeps to is no
+    # hindrance, nor is the copy's own peak; below it the call fails cleanly
+    A, B = wl.erdos_renyi(m, k, a_d, 51), wl.erdos_renyi(k, n, b_d, 52)
+    dA, dB = g.DeviceCSR.from_host(A), g.DeviceCSR.from_host(B)
+
+    def peak(path, **opts):
+        with g.Plan(dA, dB, flags=flags, **opts) as p:
+            p.symbolic()
+            p.numeric()
+            info = p.info()
+        assert info.check_flags == 0 and (g.PATH_NAMES[info.expansion_path] == "copy") == (path == "copy")
+        return info.workspace_peak_bytes
+
+    mine, other = peak("copy"), peak("expansion", dense_width_log2=13)
+    assert mine <= other
+    for limit in (other, mine):
+        assert peak("copy", workspace_limit_bytes=limit) <= limit
+    with pytest.raises(g.GmagnusError) as e:
+        peak("copy", workspace_limit_bytes=mine // 4)
+    assert e.value.status == 3 and "workspace limit" in str(e.value)
+    assert peak("copy") == mine
+
+
 @pytest.mark.parametrize("it,vt", [(torch.int32, torch.float64), (torch.int64, torch.float32)])
 def test_rows_copied_in_pieces(g, it, vt):
     # B rows around whole pieces of 2048 elements, in no order of length (an
