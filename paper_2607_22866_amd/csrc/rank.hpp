@@ -40,7 +40,7 @@ GM_DEV void region_sync() {
 // group with one barrier: `sm` must not be the one of the previous scan).
 template <int BLOCK>
 GM_DEV uint32_t region_scan(uint32_t x, uint32_t *sm, uint32_t *total) {
-    const uint32_t inc = (uint32_t)wave_incl_scan<int32_t>((int32_t)x);
+    const uint32_t inc = wave_incl_scan<uint32_t>(x);
     if constexpr (BLOCK == GM_WAVE) {
         *total = (uint32_t)__builtin_amdgcn_readlane((int)inc, GM_WAVE - 1);
         return inc - x;
@@ -187,7 +187,7 @@ GM_DEV uint32_t rank_region(const Src &src, uint32_t width, RankLds<BLOCK, CAP, 
             b[q] = tid * PER + q < NE ? L.ends[tid * PER + q].bits : 0u;
             cnt += (uint32_t)__popc(b[q]);
         }
-        uint32_t run = (uint32_t)wave_incl_scan<int32_t>((int32_t)cnt) - cnt;
+        uint32_t run = wave_incl_scan<uint32_t>(cnt) - cnt;
 #pragma unroll
         for (int q = 0; q < PER; ++q) {
             if (tid * PER + q < NE) L.ends[tid * PER + q].rank = run;

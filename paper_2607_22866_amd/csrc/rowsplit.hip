@@ -149,16 +149,6 @@ __global__ __launch_bounds__(PRE_CARRY_BLOCK) void k_pre_carry(const int64_t *ag
 // inside one (chunk, row) region are below 2^32, so the stored values are
 // exact. Lane c keeps the chunk-c total of the row that is open at the end of
 // the group (pass 2's carry at the wave's first row).
-GM_DEV uint32_t wave_incl_scan_u32(uint32_t x) {
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, false);  // row_shr:1
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, false);  // row_shr:2
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, false);  // row_shr:4
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, false);  // row_shr:8
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, false);  // row_bcast:15
-    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, false);  // row_bcast:31
-    return x;
-}
-
 // (NC > 0: the chunk count fixed at compile time, so a lane's chunk bounds
 // are read once into registers; NC = 0: any count, read per chunk)
 template <int NC>
@@ -186,7 +176,7 @@ __global__ __launch_bounds__(256) void k_pre_write(RowEntries ent, int64_t n_ent
         const bool cont = mine == 0;  // no row start at or before this lane: the open row continues
         const int seg0 = cont ? 0 : 63 - __clzll((long long)mine);
         auto chunk = [&](int c, uint32_t lo, uint32_t size) {
-            const uint32_t incl = wave_incl_scan_u32(size);
+            const uint32_t incl = wave_incl_scan<uint32_t>(size);
             const uint32_t before = (uint32_t)__shfl((int)incl, seg0 > 0 ? seg0 - 1 : 0, GM_WAVE);
             const uint32_t carry_c = (uint32_t)__builtin_amdgcn_readlane((int)open, c);
             const uint32_t excl = incl - size - (seg0 > 0 ? before : 0u) + (cont ? carry_c : 0u);

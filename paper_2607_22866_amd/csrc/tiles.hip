@@ -152,39 +152,39 @@ GM_DEV void sc_load(const uint32_t *a, int64_t base, int64_t n, uint32_t (&v)[SC
 }
 
 __global__ __launch_bounds__(SC_BLOCK) void k_tile_scan_sums(const uint32_t *a, int64_t n, uint32_t *sums) {
-    __shared__ int32_t sm[SC_BLOCK / GM_WAVE];
+    __shared__ uint32_t sm[SC_BLOCK / GM_WAVE];
     uint32_t v[SC_ITEMS];
     sc_load(a, blockIdx.x * SC_TILE + (int64_t)threadIdx.x * SC_ITEMS, n, v);
     uint32_t s = 0;
 #pragma unroll
     for (int j = 0; j < SC_ITEMS; ++j) s += v[j];
-    const int32_t tot = block_reduce_sum<SC_BLOCK>((int32_t)s, sm);
-    if (threadIdx.x == 0) sums[blockIdx.x] = (uint32_t)tot;
+    const uint32_t tot = block_reduce_sum<SC_BLOCK>(s, sm);
+    if (threadIdx.x == 0) sums[blockIdx.x] = tot;
 }
 
 __global__ __launch_bounds__(1024) void k_tile_scan_mid(uint32_t *sums, int64_t n) {
-    __shared__ int32_t sm[1024 / GM_WAVE];
-    int32_t carry = 0;
+    __shared__ uint32_t sm[1024 / GM_WAVE];
+    uint32_t carry = 0;
     for (int64_t b = 0; b < n; b += 1024) {
         const int64_t i = b + threadIdx.x;
-        const int32_t x = i < n ? (int32_t)sums[i] : 0;
-        int32_t tot;
-        const int32_t ex = block_excl_scan<1024>(x, sm, &tot);
-        if (i < n) sums[i] = (uint32_t)(carry + ex);
+        const uint32_t x = i < n ? sums[i] : 0u;
+        uint32_t tot;
+        const uint32_t ex = block_excl_scan<1024>(x, sm, &tot);
+        if (i < n) sums[i] = carry + ex;
         carry += tot;
     }
 }
 
 // (also writes the total at a[n])
 __global__ __launch_bounds__(SC_BLOCK) void k_tile_scan_apply(uint32_t *a, int64_t n, const uint32_t *sums) {
-    __shared__ int32_t sm[SC_BLOCK / GM_WAVE];
+    __shared__ uint32_t sm[SC_BLOCK / GM_WAVE];
     const int64_t base = blockIdx.x * SC_TILE + (int64_t)threadIdx.x * SC_ITEMS;
     uint32_t v[SC_ITEMS];
     sc_load(a, base, n, v);
     uint32_t s = 0;
 #pragma unroll
     for (int j = 0; j < SC_ITEMS; ++j) s += v[j];
-    uint32_t run = sums[blockIdx.x] + (uint32_t)block_excl_scan<SC_BLOCK>((int32_t)s, sm);
+    uint32_t run = sums[blockIdx.x] + block_excl_scan<SC_BLOCK>(s, sm);
 #pragma unroll
     for (int j = 0; j < SC_ITEMS; ++j) {
         const uint32_t x = v[j];
@@ -673,7 +673,7 @@ constexpr int TENDS = TWIN / 32;
 template <bool NUM, typename V, class F>
 GM_DEV void wave_parts(const uint16_t *col, const V *val, uint32_t st, uint32_t len, V a, uint32_t *ends, F &&f) {
     const int lane = threadIdx.x & (GM_WAVE - 1);
-    const uint32_t inc = (uint32_t)wave_incl_scan<int32_t>((int32_t)len);
+    const uint32_t inc = wave_incl_scan<uint32_t>(len);
     const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)inc, GM_WAVE - 1);
     const uint32_t rel = st - (inc - len);
     const uint32_t st0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)st);
