@@ -1574,8 +1574,15 @@ void light_symbolic_narrow(const Csr &A, const Csr &B, int64_t r0, const int64_t
     });
 }
 
+// Rows of one launch at most: up to 512 threads a row, and fewer than 2^32 threads.
+constexpr int64_t LIGHT_LAUNCH = (int64_t)1 << 22;
+
 void light_symbolic(const Csr &A, const Csr &B, int64_t r0, int bin, const int64_t *items, int64_t n,
                     const int64_t *ip, const void *minc_v, const void *maxc_v, int64_t *row_nnz, hipStream_t s) {
+    if (n > LIGHT_LAUNCH) {
+        light_symbolic(A, B, r0, bin, items, LIGHT_LAUNCH, ip, minc_v, maxc_v, row_nnz, s);
+        return light_symbolic(A, B, r0, bin, items + LIGHT_LAUNCH, n - LIGHT_LAUNCH, ip, minc_v, maxc_v, row_nnz, s);
+    }
     with_index_type(B.ci64, [&](auto ci) {
         using CI = decltype(ci);
         const auto a = typed<CI, NoV>(A);
@@ -1614,6 +1621,11 @@ void light_symbolic(const Csr &A, const Csr &B, int64_t r0, int bin, const int64
 void light_numeric(const Csr &A, const Csr &B, int64_t r0, int bin, const int64_t *items, int64_t n,
                    const void *minc_v, const void *maxc_v, const int64_t *c_row_ptr, void *c_col_v, void *c_val_v,
                    int32_t *err, hipStream_t s) {
+    if (n > LIGHT_LAUNCH) {
+        light_numeric(A, B, r0, bin, items, LIGHT_LAUNCH, minc_v, maxc_v, c_row_ptr, c_col_v, c_val_v, err, s);
+        return light_numeric(A, B, r0, bin, items + LIGHT_LAUNCH, n - LIGHT_LAUNCH, minc_v, maxc_v, c_row_ptr, c_col_v, c_val_v,
+                             err, s);
+    }
     with_types(B, [&](auto ci, auto v) {
         using CI = decltype(ci);
         using V = decltype(v);

@@ -832,9 +832,10 @@ bool tiles_possible(const gmagnus_plan_s *p) {
     // (64 first-level chunks, fp32 values of more than 2^18 int32 columns: refused as before)
     if (p->params.n_levels > 0 && p->params.v_chunks[0] >= GM_WAVE) return false;
     const int64_t H = p->products_heavy, nc = tile_chunks(std::max<int64_t>(p->B.n_cols, 1));
-    // part positions and region ids in 31 bits, products of a region in 32
+    // region ids in 31 bits, products of a region and the number of parts in 32
+    // (each part holds one); launches of four threads an entry
     if (nc > TILE_MAX_CHUNKS || H >= ((int64_t)1 << 32) || p->n_heavy * nc >= ((int64_t)1 << 31) ||
-        p->nnz_heavy * nc >= ((int64_t)1 << 40))
+        p->nnz_heavy >= ((int64_t)1 << 29))
         return false;
     // Below one product per (entry, chunk) most of what the lists read would be
     // empty, and their memory is refused below. (R-MAT panels of 1e8 to 3e8

@@ -1019,7 +1019,8 @@ constexpr int64_t RANK_FEW = 512;
 template <class K, class... Args>
 void launch_regions(K kernel, int block, int64_t groups, hipStream_t s, Args... args) {
     if (groups <= 0) return;
-    GM_REQUIRE(groups < (int64_t)1 << 31, GMAGNUS_ERROR_UNSUPPORTED, "too many regions for one launch");
+    // (cannot happen below 2^32 products, which the rule admits)
+    GM_REQUIRE(groups * block < (int64_t)1 << 32, GMAGNUS_ERROR_UNSUPPORTED, "too many regions for one launch");
     hipLaunchKernelGGL(kernel, dim3((unsigned)groups), dim3(block), 0, s, args...);
     GM_CHECK_LAUNCH();
 }

@@ -98,3 +98,11 @@ def test_many_repeats(g, per_row, distinct):
     cols = [pool[np.sort(rng.choice(distinct, 50, replace=False))] for _ in range(80)]
     B = wl.CSR(80, 1 << 20, np.arange(81, dtype=np.int64) * 50, np.concatenate(cols), rng.uniform(-1.0, 1.0, 4000))
     check(g, wl.erdos_renyi(30, 80, per_row, 13), B)
+
+
+def test_more_rows_than_one_launch(g):
+    # 2^22 light rows and three more, of two products each
+    m = (1 << 22) + 3
+    rng = np.random.default_rng(14)
+    A = wl.CSR(m, 1000, np.arange(m + 1, dtype=np.int64), rng.integers(0, 1000, m).astype(np.int32), rng.uniform(-1.0, 1.0, m))
+    check(g, A, ragged(np.full(1000, 2), 1 << 20, 15))
