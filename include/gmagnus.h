@@ -149,10 +149,10 @@ enum {
     GMAGNUS_K_SETUP = 0,       /* row products, binning, partitions, scans */
     GMAGNUS_K_CSC = 1,         /* masked CSR->CSC of heavy rows and slice offsets */
     GMAGNUS_K_EXPAND = 2,      /* outer-product expansion into C-hat, or the chunk-major copy of B's rows in its place */
-    GMAGNUS_K_HISTOGRAM = 3,   /* level-0 chunk histogram */
+    GMAGNUS_K_HISTOGRAM = 3,   /* level-0 chunk histogram, or the copy's part sizes, regions and lists */
     GMAGNUS_K_MULTISPLIT = 4,  /* multisplit levels (with fused next-level histogram) */
-    GMAGNUS_K_CHUNK_SYM = 5,   /* symbolic of final chunks */
-    GMAGNUS_K_CHUNK_NUM = 6,   /* numeric of final chunks (writes C) */
+    GMAGNUS_K_CHUNK_SYM = 5,   /* symbolic of final chunks (or of the copy's regions) */
+    GMAGNUS_K_CHUNK_NUM = 6,   /* numeric of final chunks or regions (writes C) */
     GMAGNUS_K_LIGHT_SYM = 7,   /* symbolic of light rows */
     GMAGNUS_K_LIGHT_NUM = 8,   /* numeric of light rows (writes C) */
     GMAGNUS_K_ROWPTR = 9,      /* fragment offsets and the C row-pointer scan */
@@ -184,7 +184,8 @@ typedef struct {
     int32_t index_type;            /* gmagnus_index_type_t of A, B and C */
     int32_t value_type;            /* gmagnus_value_type_t of A, B and C */
     /* Under GMAGNUS_FLAG_TIMING: summed device milliseconds, launches and
-     * algorithmic (compulsory) HBM bytes per kernel class. */
+     * algorithmic (compulsory) HBM bytes per kernel class: what its kernels
+     * cannot do without, each array in memory read once and written once. */
     double kernel_ms[GMAGNUS_K_COUNT];
     int64_t kernel_launches[GMAGNUS_K_COUNT];
     double kernel_bytes[GMAGNUS_K_COUNT];

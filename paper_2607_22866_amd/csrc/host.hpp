@@ -382,6 +382,7 @@ struct TileHeavy {
     uint32_t *seg_e = nullptr;             // ... and the A entry
     uint32_t *bitmap = nullptr;            // present columns of the regions of more than TILE_MERGE products
     TileTask *tasks = nullptr;             // the non-empty regions' records (symbolic), by bin
+    double num_bytes = 0;                  // compulsory bytes of the numeric phase, C's apart
     int64_t *large_perm = nullptr;         // the regions of more than TILE_MERGE products by numeric bin
     int64_t bins[TILE_NBINS + 1] = {0};
 };

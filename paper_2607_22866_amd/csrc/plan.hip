@@ -917,7 +917,7 @@ void tiled_symbolic(gmagnus_plan_s *p, const SliceArrays &sl, int64_t blen_total
     t.nnz = ws.alloc<uint32_t>(regions);
     p->slot = ws.alloc<int64_t>(regions);
     {
-        Timed tm(p, GMAGNUS_K_SETUP, s);
+        Timed tm(p, GMAGNUS_K_HISTOGRAM, s);
         unsigned long long *size = ws.alloc<unsigned long long>(regions);
         uint8_t *cls = ws.alloc<uint8_t>(regions);
         int64_t *bins = ws.alloc<int64_t>(TILE_NBINS + 2);  // class bounds, then the number of parts
@@ -948,7 +948,12 @@ void tiled_symbolic(gmagnus_plan_s *p, const SliceArrays &sl, int64_t blen_total
         t.bitmap = ws.alloc<uint32_t>((t.bins[TILE_M + 1] - t.bins[TILE_D_BIG]) * (TILE_COLS / 32));
         t.tasks = ws.alloc<TileTask>(tile_items(t));
         tile_tasks(t, s);
+        p->info.kernel_launches[GMAGNUS_K_HISTOGRAM] += 1;
+        add_bytes(p, GMAGNUS_K_HISTOGRAM, 8.0 * t.n_ent + 6.0 * t.ns * t.nc + 12.0 * (double)n_seg);
     }
+    // the copy and the lists read once by the regions' kernels (they are read once
+    // a product or part, mostly from the caches; the numeric phase's are kept for it)
+    t.num_bytes = (2.0 + VS) * blen_total + 12.0 * (double)n_seg + VS * (double)t.n_ent;
     {
         Timed tm(p, GMAGNUS_K_CHUNK_SYM, s);
         for (int b = TILE_D_BIG; b < TILE_NBINS; ++b) {
@@ -957,7 +962,7 @@ void tiled_symbolic(gmagnus_plan_s *p, const SliceArrays &sl, int64_t blen_total
             if (n) p->info.kernel_launches[GMAGNUS_K_CHUNK_SYM] += 1;
             (b <= TILE_D ? p->info.n_leaves_dense : p->info.n_leaves_rank) += n;
         }
-        add_bytes(p, GMAGNUS_K_CHUNK_SYM, 2.0 * p->products_heavy + 8.0 * (double)n_seg);
+        add_bytes(p, GMAGNUS_K_CHUNK_SYM, 2.0 * blen_total + 8.0 * (double)n_seg);
     }
     {
         Timed tm(p, GMAGNUS_K_SETUP, s);
@@ -1733,7 +1738,7 @@ void do_numeric(gmagnus_plan_s *p, const int64_t *c_row_ptr, void *c_col, void *
                 tile_numeric(p->tile, p->large_bins, tasks, p->heavy_rows, c_row_ptr, p->slot, p->B.ci64, p->B.v32, c_col,
                              c_val, p->err, s);
             p->ws->free(tasks);
-            add_bytes(p, GMAGNUS_K_CHUNK_NUM, (2.0 + p->vsize) * p->products_heavy);
+            add_bytes(p, GMAGNUS_K_CHUNK_NUM, p->tile.num_bytes);
         }
         for (auto &lv : p->leaves) {
             const int64_t nl = lv.set.hi - lv.set.lo;

@@ -142,6 +142,25 @@ def test_memory(g, m, k, n, a_d, b_d, flags):
     assert peak("copy") == mine
 
 
+def test_bytes_are_compulsory(g):
+    # the copy and the lists are counted once, not once a product
+    m, k, n, a_d, b_d = DENSE
+    A, B = wl.erdos_renyi(m, k, a_d, 53), wl.erdos_renyi(k, n, b_d, 54)
+    dA, dB = g.DeviceCSR.from_host(A), g.DeviceCSR.from_host(B)
+    with g.Plan(dA, dB) as p:
+        _, nnz = p.symbolic()
+        p.numeric()
+        info = p.info()
+    assert g.PATH_NAMES[info.expansion_path] == "copy"
+    parts = np.array([np.unique(r >> 14).size for r in np.split(B.col, B.row_ptr[1:-1])])
+    used = np.unique(A.col)
+    elems, segs = b_d * used.size, int(parts[A.col].sum())
+    by = {name: info.kernel_bytes[i] for i, name in enumerate(g.K_NAMES)}
+    assert by["chunk_symbolic"] == 2 * elems + 8 * segs
+    assert by["chunk_numeric"] == 10 * elems + 12 * segs + 8 * A.nnz + 12 * nnz
+    assert by["expand"] == 22 * elems + 4 * 3 * used.size
+
+
 @pytest.mark.parametrize("it,vt", [(torch.int32, torch.float64), (torch.int64, torch.float32)])
 def test_rows_copied_in_pieces(g, it, vt):
     # B rows around whole pieces of 2048 elements, in no order of length (an
