@@ -327,7 +327,14 @@ GM_DEV int hash_bin_num(int64_t nnz) {
     return nnz <= HN_CAP[0] ? 0 : nnz <= HN_CAP[1] ? 1 : nnz <= HN_CAP[2] ? 2 : 3;
 }
 constexpr int TAU_MAX = 6912;    // products of a light chunk at most
-constexpr int LIGHT_MAX = 3456;  // products of a light row at most
+// Products of a light row at most: what the largest rank launch holds with two work
+// groups a CU (60 KB of LDS each, fp64). No crossing: just below, light rows still beat
+// the heavy path (35067 rows of 3422 products, 1.2e8 in all: 1000 distinct columns
+// spread over 4e6 1.21 ms a product against 3.92, all of 4e6 1.73 against 8.59, all of
+// 250007 1.52 against 1.73); on R-MAT rows, whose copy the heavy rows share, it is
+// the other way round (R-MAT 22 with the heavy path from 3457 products 1441 -> 1425 ms,
+// timed with the expansion and sorted light rows).
+constexpr int LIGHT_MAX = 3456;
 
 // Bins of the light rows outside a window, by products: one wave (4 or 8
 // products a lane) up to 512, then work groups of 4 products a thread (8 in the
@@ -345,7 +352,13 @@ constexpr int LIGHT_MAX = 3456;  // products of a light row at most
 // columns 1.00 against 0.40, on 100 columns 0.90 against 0.29). Between, rows over
 // few columns in all gain by rank (1e5 of 2025 products, 250007 columns: 0.49
 // against 0.71 with a table of 8192), rows with many repeats lose (5e4 of 2000
-// products on 32 columns: 0.22 against 0.20).
+// products on 32 columns: 0.22 against 0.20). The numeric phase by rank loses to a
+// 256-slot table of one wave only where more than 1024 products meet 64 columns or
+// fewer, spread too wide for a window (whole products: 8e4 rows of 1500 products on 64
+// columns 0.99 against 0.78, on 96 columns 1.02 against 1.01; 4e4 rows of 3025 on 64
+// columns 1.02 against 0.97, on 96 1.02 against 1.14). A launch of that table for such
+// rows gave 0.94 and 0.86 at 64 columns, 1.18 and 1.08 at 96, and the test that skips
+// them in the rank kernels took 3 % of the stencil, so they stay by rank.
 constexpr int RB_CAP[5] = {256, 512, 1024, 2048, 3584};
 constexpr int HASH_R4 = 8192;  // slots (16384: 1.37 against 0.92 ms for the first of these, half the work groups a CU)
 static_assert(HASH_R4 >= 2 * LIGHT_MAX, "at least two slots a product");

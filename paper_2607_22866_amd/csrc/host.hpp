@@ -346,6 +346,15 @@ constexpr int TILE_LOG2 = 14, TILE_COLS = 1 << TILE_LOG2;
 constexpr int TILE_MAX_CHUNKS = 1024;
 // region bins by product count (the big dense ones launch first)
 enum TileBin : uint8_t { TILE_EMPTY = 0, TILE_D_BIG, TILE_D, TILE_M, TILE_L, TILE_S, TILE_T, TILE_NBINS };
+// Where the bins end (ms of the R-MAT 23 panel of 1.5e9 products / the R-MAT 22
+// panel of 2e9, 17.1 / 14.1 as they are; runs of one build differ by 0.03):
+// by rank, 4 products a lane of one wave (128: 17.2 / 14.1, 512: 17.7 / 14.2), of 4
+// waves (512: 18.1 / 14.4, 2048: 19.1 / 14.5) and of 8 waves (the regions that may
+// span several chunks: 1024, longer ones on a bitmap of one chunk, 17.3 / 14.1, 4096:
+// 20.2 / 15.4); above, the waves that mark one bitmap, 4 up to TILE_M_MAX (2048: 17.3
+// / 14.1, 8192: 17.1 / 14.1, the R-MAT 17 square 6.06 ms: 6.19 and 6.02) and 8 up to
+// TILE_D_MAX (32768: 17.0 / 14.1, 131072: 17.1 / 14.2, the fp32 R-MAT 18 panel of 1e9
+// products 8.77 ms: 9.06 and 8.86), 16 past it.
 constexpr int TILE_T_MAX = 256, TILE_S_MAX = 1024, TILE_M_MAX = 4096, TILE_D_MAX = 65536;
 constexpr int TILE_MERGE = 2048;  // most products of a region of several chunks
 // distinct columns of the large regions summed by rank, by launch (two 16-wave, four 8-wave, seven 4-wave groups per CU)

@@ -14,8 +14,10 @@
 // (each is read once and stays in registers); the column range only adds a
 // level per factor of 32.
 //
-// What bounds it: LDS (about 12 accesses a product) and the latency of the
-// chain row -> parts -> products; the vector units are a third busy.
+// What bounds it: LDS (about 12 accesses a product; 40 to 54 % of its cycles, a
+// third to a half of these bank conflicts) and the latency of the chain row ->
+// parts -> products; the vector units are 43 to 60 % busy, 61 to 78 % where
+// columns are only counted. Sums of fp32 values keep the LDS at 77 to 79 %.
 #pragma once
 
 #include "common.hpp"
