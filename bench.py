@@ -59,7 +59,8 @@ KERNEL_SOURCES = {"k_tile_fill": ["paper_2607_22866_amd/csrc/tiles.hip", "paper_
                   "k_expand": ["paper_2607_22866_amd/csrc/expand.hip", "paper_2607_22866_amd/csrc/common.hpp"],
                   "k_multisplit": ["paper_2607_22866_amd/csrc/multisplit.hip",
                                    "paper_2607_22866_amd/csrc/common.hpp"]}
-TRAFFIC_FILES = {"k_expand_rows2": "profiles/expand_rows2_rmat22_traffic.md",
+TRAFFIC_FILES = {"k_tile_fill": "profiles/tile_fill_rmat22_traffic.md",
+                 "k_expand_rows2": "profiles/expand_rows2_rmat22_traffic.md",
                  "k_expand_rows": "profiles/expand_rows_rmat22_traffic.md",
                  "k_expand_split": "profiles/expand_split_rmat22_traffic.md",
                  "k_multisplit": "profiles/multisplit_rmat22_traffic.md"}
