@@ -188,7 +188,7 @@ def test_banded_window_and_hash(g):
     A = wl.banded(4096, 13, 3)
     info = check(g, A, A)
     assert info.n_heavy_rows == 0
-    check(g, A, A, flags=4)  # hash accumulator instead of the dense window
+    check(g, A, A, flags=4)  # by rank instead of the dense window
     W = wl.banded(3000, 300, 4)  # 601-wide rows: wider window bin
     check(g, W, W)
 
